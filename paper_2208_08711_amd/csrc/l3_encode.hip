@@ -12,8 +12,8 @@
  * Patch sizes 32, 64 and 128 (the ones the paper's rule picks) take three kernels:
  *   strip    a workgroup of three waves (one per channel) owns a strip of adjacent
  *            patches, 4 pixels per lane as two packed pairs of 16-bit fields: per
- *            row it filters, reduces min and max over the patch's lanes, packs the
- *            deltas with LDS atomic OR into a small ring per patch and streams the
+ *            four rows it filters, reduces their min and max over the patch's lanes, packs
+ *            the deltas with LDS atomic OR into a small ring per patch and streams the
  *            finished 16-byte granules to a fixed-size slot of a workspace; the
  *            patch's byte size goes to a table;
  *   layout   one workgroup per image: exclusive prefix sum of the patch sizes ->
@@ -159,16 +159,19 @@ template <int N>
 struct StripGeom {
     static constexpr int LPT = N / 4;              /* lanes per patch, 4 pixels each */
     static constexpr int TPW = 64 / LPT;           /* patches per wave */
-    static constexpr int P = 3;                    /* rows between two flushes of the rings */
-    static constexpr int ROW_MAX = N + 3;          /* bytes a row can touch: ceil((12 + 8N)/8) + 1 */
+    static constexpr int P = 4;                    /* rows of a period: filtered, reduced and packed together */
     static constexpr int RING = 8 * N;             /* ring bytes per patch and channel */
     static constexpr int RING_WORDS = RING / 4 + 4; /* + a word that stands for word 0 of the next lap (and padding to 16 bytes) */
     /* the longest patch stream, rounded up to whole 16-byte granules */
     static constexpr uint32_t SLOT = ((uint32_t)N * (12 + 8 * N) / 8 + 1 + 15) / 16 * 16;
-    /* one flush round (a granule per lane of the patch) takes everything that P rows
-     * and a pending partial granule can have completed, and the ring holds it */
-    static_assert(LPT * 16 >= P * ROW_MAX + 15, "a flush round empties a period");
-    static_assert(RING >= 2 * (P * ROW_MAX + 16), "ring holds a period beside the granules being cleared");
+    /* A flush round takes one granule per lane of the patch, 4N bytes; P rows add at most
+     * 4N + 6, so the stream's unflushed part may grow by 6 bytes a period over the patch's
+     * N / 4 periods, beside a partial granule.  The ring holds that and the period being
+     * packed; FINAL_ROUNDS rounds empty it behind the last row. */
+    static constexpr int PERIOD_MAX = P * (12 + 8 * N) / 8;
+    static constexpr int BACKLOG = 15 + (N / P) * (PERIOD_MAX - LPT * 16);
+    static constexpr int FINAL_ROUNDS = (BACKLOG + PERIOD_MAX + 15 + LPT * 16 - 1) / (LPT * 16);
+    static_assert(RING >= BACKLOG + PERIOD_MAX + 1 + 8, "ring holds a period behind the backlog");
     static_assert((RING & (RING - 1)) == 0, "ring size is a power of two");
 };
 
@@ -179,9 +182,10 @@ __host__ __device__ constexpr uint32_t strip_slot_bytes(uint32_t n) {
 typedef __attribute__((address_space(1))) const u32x3_any global_const_u32x3_any;
 typedef __attribute__((address_space(1))) u32x4 global_u32x4;
 
-__device__ __forceinline__ uint32_t pk_sub_u16_sat(uint32_t a, uint32_t b) {   /* max(a - b, 0) per field */
+/* max((low half of a) - b, 0) in both 16-bit halves */
+__device__ __forceinline__ uint32_t pk_sub_u16_sat_from_low(uint32_t a, uint32_t b) {
     uint32_t d;
-    asm("v_pk_sub_u16 %0, %1, %2 clamp" : "=v"(d) : "v"(a), "v"(b));
+    asm("v_pk_sub_u16 %0, %1, %2 op_sel_hi:[0,1] clamp" : "=v"(d) : "v"(a), "v"(b));
     return d;
 }
 __device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
@@ -193,21 +197,68 @@ __device__ __forceinline__ uint32_t dpp_move(uint32_t v) {
     /* every lane has a source lane under these controls, so the "old" value is never used */
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
 }
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;                  /* quad_perm [1,0,3,2], [2,3,0,1] */
+constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;        /* inside 8 and 16 lanes */
 
-/* Minimum of both 16-bit fields, separately, over the LPT lanes of a patch; every
- * lane gets the result.  Butterfly: lane ^ 1, ^ 2 inside quads, then mirrors inside 8
- * and 16 lanes, then the swap of neighbouring 16-lane rows. */
+__device__ __forceinline__ uint32_t pk_max_i16(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s16x2, a),
+                                                                  __builtin_bit_cast(s16x2, b)));
+}
+
+/* Row minima of four rows over the LPT lanes of a patch (both 16-bit fields separately), all at
+ * once: while lanes are folded onto each other, the two lanes of a pair take different rows, so
+ * that after two such steps one register holds all four rows and the remaining steps are paid
+ * once instead of four times.  In lane i of the patch the result is that of row
+ * reduced_row<LPT>(i); the order of the rows is turned round in every other quad, so that the
+ * mirrors inside 8 and 16 lanes bring equal rows together.  22 instructions for four rows with
+ * the way back at N = 128 instead of 40 for four separate butterflies. */
 template <int LPT>
-__device__ __forceinline__ uint32_t patch_min_u16x2(uint32_t v) {
-    v = pk_min_u16(v, dpp_move<0xB1>(v));    /* quad_perm [1,0,3,2] */
-    v = pk_min_u16(v, dpp_move<0x4E>(v));    /* quad_perm [2,3,0,1] */
-    v = pk_min_u16(v, dpp_move<0x141>(v));   /* row_half_mirror */
-    if (LPT >= 16) v = pk_min_u16(v, dpp_move<0x140>(v));   /* row_mirror */
-    if (LPT >= 32) {
-        const auto both = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        v = pk_min_u16((uint32_t)both[0], (uint32_t)both[1]);
+__device__ __forceinline__ uint32_t reduced_row(uint32_t lane) {
+    const uint32_t turned = (lane & 4u) ? 3u : 0u;
+    return LPT == 32 ? ((lane >> 4) & 1u) + 2u * ((lane ^ turned) & 1u) : ((lane ^ turned) & 3u);
+}
+template <int CTRL>
+__device__ __forceinline__ uint32_t fold_two_rows(uint32_t a, uint32_t b, bool second) {
+    const uint32_t keep = second ? b : a, send = second ? a : b;
+    return pk_min_u16(keep, dpp_move<CTRL>(send));
+}
+template <int LPT>
+__device__ __forceinline__ uint32_t patch_min_of_rows(const uint32_t (&v)[4], uint32_t my_row) {
+    uint32_t m;
+    if constexpr (LPT == 32) {
+        /* the swap of neighbouring 16-lane rows between two registers is the first such step */
+        const auto p = __builtin_amdgcn_permlane16_swap(v[0], v[1], false, false);
+        const auto q = __builtin_amdgcn_permlane16_swap(v[2], v[3], false, false);
+        const uint32_t v01 = pk_min_u16((uint32_t)p[0], (uint32_t)p[1]);
+        const uint32_t v23 = pk_min_u16((uint32_t)q[0], (uint32_t)q[1]);
+        m = fold_two_rows<kDppXor1>(v01, v23, (my_row & 2u) != 0);
+        m = pk_min_u16(m, dpp_move<kDppXor2>(m));
+    } else {
+        const uint32_t v01 = fold_two_rows<kDppXor1>(v[0], v[1], (my_row & 1u) != 0);
+        const uint32_t v23 = fold_two_rows<kDppXor1>(v[2], v[3], (my_row & 1u) != 0);
+        m = fold_two_rows<kDppXor2>(v01, v23, (my_row & 2u) != 0);
     }
-    return v;
+    m = pk_min_u16(m, dpp_move<kDppHalfMirror>(m));
+    if (LPT >= 16) m = pk_min_u16(m, dpp_move<kDppMirror>(m));
+    return m;
+}
+/* The way back: value of row i in every lane of the patch. */
+template <int LPT>
+__device__ __forceinline__ void rows_to_all_lanes(uint32_t v, uint32_t (&row)[4]) {
+    /* the turned quads (banks 1 and 3 of a 16-lane row) back in order */
+    v = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, LPT == 32 ? kDppXor1 : 0x1B /* quad_perm [3,2,1,0] */, 0xF, 0xA, false);
+    if constexpr (LPT == 32) {
+        const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        row[0] = dpp_move<0x00>((uint32_t)p[0]);      /* quad_perm [0,0,0,0] */
+        row[1] = dpp_move<0x00>((uint32_t)p[1]);
+        row[2] = dpp_move<0x55>((uint32_t)p[0]);      /* quad_perm [1,1,1,1] */
+        row[3] = dpp_move<0x55>((uint32_t)p[1]);
+    } else {
+        row[0] = dpp_move<0x00>(v);
+        row[1] = dpp_move<0x55>(v);
+        row[2] = dpp_move<0xAA>(v);
+        row[3] = dpp_move<0xFF>(v);
+    }
 }
 
 /* One strip: TPW adjacent patches of one patch row, channel C. */
@@ -232,7 +283,7 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
     /* this lane's 4 pixels: columns 4 xl .. 4 xl + 3 of the patch, nvalid of them exist */
     const uint32_t xpix = 4 * xl;
     const uint32_t nvalid = pw > xpix ? min(4u, pw - xpix) : 0u;
-    const uint8_t* src = d.rgb + (size_t)y0 * d.row_stride + ((size_t)x0 + xpix) * 3;   /* walks down the rows */
+    const uint8_t* src = d.rgb + (size_t)y0 * d.row_stride;   /* start of the image row, walks down; scalar */
 
     /* registers of two 16-bit fields: E = pixels (0, 2), O = pixels (1, 3) */
     const uint32_t validE = (nvalid > 0 ? 0x0000FFFFu : 0u) | (nvalid > 2 ? 0xFFFF0000u : 0u);
@@ -244,46 +295,57 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
 
     /* The residual byte r is looked at as t = r ^ K, K = 0 in the first row (raw,
      * unsigned) and 0x80 after it (signed byte + 128), so that the unsigned minimum of t
-     * is the row minimum of Section 4.2; u = t ^ 0xFF turns the maximum into a minimum
-     * too.  Fields of pixels that do not exist read 0xFFFF in both. */
-    uint32_t kminE = ~validE, kminO = ~validO;                          /* K = 0 */
-    uint32_t kmaxE = ~validE | keepE, kmaxO = ~validO | keepO;          /* K ^ 0xFF = 0xFF */
-    uint32_t krow = 0;
+     * is the row minimum of Section 4.2; what is kept is u = t ^ 0xFF, whose maximum gives
+     * the row minimum.  Fields of pixels that do not exist read 0xFFFF: neither the unsigned
+     * minimum nor the signed maximum takes them. */
+    uint32_t kE = ~validE | keepE, kO = ~validO | keepO;                /* K ^ 0xFF = 0xFF */
+    const uint32_t nowhere = ~(validE | validO);    /* fields that neither register has a pixel for */
+    const uint32_t my_row = reduced_row<LPT>(lane);                     /* see patch_min_of_rows */
+    uint32_t krow = my_row == 0 ? 0u : 0x80u;                           /* K of that row in the first period */
 
     uint64_t row_stride = d.row_stride;
     asm volatile("" : "+s"(row_stride));    /* kept in registers, not reloaded every row */
     /* The lane's 12 bytes of a row.  A lane at the right edge of the image owns fewer than
      * 4 pixels and must not read past the row: it reads the 12 bytes that END at its last
-     * pixel and shifts them down (what then sits above the valid bytes is masked later).
-     * Only waves with such a lane take that path; images narrower than 4 pixels go byte by
-     * byte. */
-    const bool ragged_wave = __builtin_amdgcn_ballot_w64(nvalid != 0 && nvalid != 4) != 0;
+     * pixel and shifts them down when it takes them (what then sits above the valid bytes is
+     * masked later).  Only waves with such a lane shift.  A lane without pixels reads the start
+     * of the row, so that no load is conditional.  Images narrower than 4 pixels go byte by
+     * byte; there all pixels are lane 0's. */
     const bool wide = d.width >= 4;
-    const uint32_t back = nvalid ? 3 * (4 - nvalid) : 0;              /* bytes to step back: 0, 3, 6, 9 */
-    auto load_row = [&](const uint8_t* p) -> u32x3 {
-        u32x3 v = {0, 0, 0};
-        if (!ragged_wave) {
-            if (nvalid == 4) v = *reinterpret_cast<global_const_u32x3_any*>((uintptr_t)p);
-        } else if (wide) {
-            if (nvalid) {
-                const u32x3 q = *reinterpret_cast<global_const_u32x3_any*>((uintptr_t)(p - back));
-                const uint32_t words = back >> 2, bits = (back & 3u) * 8;
-                const uint32_t a0 = words == 0 ? q.x : (words == 1 ? q.y : q.z);
-                const uint32_t a1 = words == 0 ? q.y : (words == 1 ? q.z : 0u);
-                const uint32_t a2 = words == 0 ? q.z : 0u;
-                v.x = __builtin_amdgcn_alignbit(a1, a0, bits);
-                v.y = __builtin_amdgcn_alignbit(a2, a1, bits);
-                v.z = a2 >> bits;
-            }
-        } else if (nvalid) {
-            uint32_t b[9];
+    const bool ragged_wave = wide && __builtin_amdgcn_ballot_w64(nvalid != 0 && nvalid != 4) != 0;
+    const uint32_t back = wide && nvalid ? 3 * (4 - nvalid) : 0;              /* bytes to step back: 0, 3, 6, 9 */
+    const uint32_t lane_at = nvalid ? (x0 + xpix) * 3 - back : 0u;            /* below 3 * 2^24 */
+    const uint32_t row_bytes = d.width * 3;
+    /* rows first .. first + P - 1 of the patch from `row` on; rows that do not exist (of the
+     * last period) repeat the last one */
+    u32x3 ahead[P];
+    auto load_rows = [&](const uint8_t* row, uint32_t exist) {
+        typedef __attribute__((address_space(1))) const uint8_t global_const_u8;
 #pragma unroll
-            for (int i = 0; i < 9; ++i) b[i] = (uint32_t)((uint32_t)i < 3 * nvalid ? p[i] : 0);
-            v.x = b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
-            v.y = b[4] | (b[5] << 8) | (b[6] << 16) | (b[7] << 24);
-            v.z = b[8];
+        for (int i = 0; i < P; ++i) {
+            global_const_u8* base = reinterpret_cast<global_const_u8*>((uintptr_t)(row + min((uint32_t)i, exist - 1) * row_stride));
+            if (wide) {
+                uint32_t at = lane_at;
+                L3_KEEP_VGPR(at);      /* stays the load's 32-bit offset */
+                ahead[i] = *reinterpret_cast<global_const_u32x3_any*>(base + at);
+            } else {
+                uint32_t b[9];
+#pragma unroll
+                for (uint32_t k = 0; k < 9; ++k) b[k] = base[min(k, row_bytes - 1)];
+                ahead[i].x = b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
+                ahead[i].y = b[4] | (b[5] << 8) | (b[6] << 16) | (b[7] << 24);
+                ahead[i].z = b[8];
+            }
         }
-        return v;
+    };
+    auto shift_down = [&](u32x3& v) {
+        const uint32_t words = back >> 2, bits = (back & 3u) * 8;
+        const uint32_t a0 = words == 0 ? v.x : (words == 1 ? v.y : v.z);
+        const uint32_t a1 = words == 0 ? v.y : (words == 1 ? v.z : 0u);
+        const uint32_t a2 = words == 0 ? v.z : 0u;
+        v.x = __builtin_amdgcn_alignbit(a1, a0, bits);
+        v.y = __builtin_amdgcn_alignbit(a2, a1, bits);
+        v.z = a2 >> bits;
     };
 
     uint32_t* const ring = ring_words + g * G::RING_WORDS;
@@ -309,9 +371,11 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
 
     uint32_t rowpos = 0;       /* bit position of the next row record in the patch stream */
     uint32_t flushed = 0;      /* granules already in the slot */
-    /* writes granules [flushed, upto) of the stream to the slot and clears them in the ring */
-    auto flush = [&](uint32_t upto) {
+    /* writes granules [flushed, end) of the stream to the slot and clears them in the ring, at
+     * most one per lane of the patch */
+    auto flush = [&](uint32_t end) {
         wave_lds_fence();
+        const uint32_t upto = min(end, flushed + LPT);
         const uint32_t gi = flushed + xl;
         if (active && gi < upto) {
             const uint32_t at = (gi * 16) & (RING - 1);
@@ -329,13 +393,10 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
         wave_lds_fence();
     };
 
-    uint32_t up[2] = {0, 0};   /* the original row above; zeros above the first row predict 0 */
+    uint32_t up[2] = {0, 0};   /* the original row above the period; zeros above the first row predict 0 */
 
-    /* One row: filter, row minimum and maximum, the lane's deltas into the ring.  Returns
-     * the row's 12-bit record; its place is the value of rowpos on entry. */
-    auto do_row = [&](const u32x3 raw) -> uint32_t {
-        /* channel C of pixel i is byte 3 i + C of the lane's 12 bytes */
-        uint32_t cur[2];
+    /* channel C of pixel i is byte 3 i + C of the lane's 12 bytes */
+    auto take_channel = [&](const u32x3 raw, uint32_t (&cur)[2]) {
         if (C == 0) {
             cur[0] = __builtin_amdgcn_perm(raw.y, raw.x, 0x0C060C00u);   /* bytes 0, 6 */
             cur[1] = __builtin_amdgcn_perm(raw.z, raw.x, 0x0C050C03u);   /* bytes 3, 9 */
@@ -346,59 +407,53 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
             cur[0] = __builtin_amdgcn_perm(raw.z, raw.x, 0x0C040C02u);   /* bytes 2, 8 */
             cur[1] = __builtin_amdgcn_perm(raw.z, raw.y, 0x0C070C01u);   /* bytes 5, 11 */
         }
+    };
 
-        /* Section 4.2 stage 1 on the original row above */
-        const uint32_t from_left = dpp_from_lower_lane(up[1]);
-        const uint32_t from_right = dpp_from_upper_lane(up[0]);
+    /* Section 4.2 stage 1 on the original row above; leaves u and the lane's own part of the
+     * row's extremes: (minimum of u, ~(maximum of u)), so that both go on as minima. */
+    auto filter_row = [&](const uint32_t (&above)[2], const uint32_t (&cur)[2], uint32_t& uE, uint32_t& uO) -> uint32_t {
+        const uint32_t from_left = dpp_from_lower_lane(above[1]);
+        const uint32_t from_right = dpp_from_upper_lane(above[0]);
         uint32_t TL[2], TR[2], pred[2];
-        TL[0] = __builtin_amdgcn_alignbit(up[1], from_left, 16);
-        TR[0] = up[1];
-        TL[1] = up[0];
-        TR[1] = __builtin_amdgcn_alignbit(from_right, up[0], 16);
-        predict_pairs<2>(TL, TR, up, border, pred);
+        TL[0] = __builtin_amdgcn_alignbit(above[1], from_left, 16);
+        TR[0] = above[1];
+        TL[1] = above[0];
+        TR[1] = __builtin_amdgcn_alignbit(from_right, above[0], 16);
+        predict_pairs<2>(TL, TR, above, border, pred);
         const uint32_t rE = __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, cur[0]) -
                                                                  __builtin_bit_cast(u16x2, pred[0])));
         const uint32_t rO = __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, cur[1]) -
                                                                  __builtin_bit_cast(u16x2, pred[1])));
-        /* (r & keep) ^ k */
-        const uint32_t tE = __builtin_amdgcn_bitop3_b32(rE, keepE, kminE, 0x6A);
-        const uint32_t tO = __builtin_amdgcn_bitop3_b32(rO, keepO, kminO, 0x6A);
-        const uint32_t uE = __builtin_amdgcn_bitop3_b32(rE, keepE, kmaxE, 0x6A);
-        const uint32_t uO = __builtin_amdgcn_bitop3_b32(rO, keepO, kmaxO, 0x6A);
-
-        /* stage 2, steps 1-2: row minimum and maximum over the patch */
-        const uint32_t a = pk_min_u16(tE, tO), b = pk_min_u16(uE, uO);
-        uint32_t mm = pk_min_u16(__builtin_amdgcn_perm(b, a, 0x05040100u),    /* (a.lo, b.lo) */
-                                 __builtin_amdgcn_perm(b, a, 0x07060302u));   /* (a.hi, b.hi) */
-        mm = patch_min_u16x2<LPT>(mm);
-        const uint32_t tmin = mm & 0xFFFFu, umin = mm >> 16;     /* min t, 255 - max t */
-        const uint32_t range = (255u - (tmin + umin)) & 0xFFu;   /* masked: lanes without a patch hold no minimum */
-        const uint32_t w = 31u - (uint32_t)__builtin_clz(2u * range + 1u);
-        const uint32_t rec = w | (((tmin ^ krow) & 0xFFu) << 4);
-
-        /* steps 3-4: deltas t - tmin = (255 - tmin) - u, 0 where no pixel exists; the
-         * lane's four deltas as one field of 4 w bits */
-        const uint32_t top1 = (tmin ^ 0xFFu) & 0xFFu, top = top1 | (top1 << 16);
-        const uint32_t dE = pk_sub_u16_sat(top, uE), dO = pk_sub_u16_sat(top, uO);
-        const uint32_t pair = dE | (dO << w);                   /* (d0 | d1 << w, d2 | d3 << w) */
-        const uint32_t group = (pair & 0xFFFFu) | ((pair >> 16) << (2 * w));
-        if (active) put(group, rowpos + 12 + xpix * w);
-        rowpos += 12 + pw * w;
-        up[0] = cur[0];
-        up[1] = cur[1];
-        return rec;
+        uE = __builtin_amdgcn_bitop3_b32(rE, keepE, kE, 0x6A);           /* (r & keep) ^ k */
+        uO = __builtin_amdgcn_bitop3_b32(rO, keepO, kO, 0x6A);
+        const uint32_t a = pk_min_u16(uE, uO);
+        const uint32_t b = ~pk_max_i16(uE, uO) | nowhere;
+        return pk_min_u16(__builtin_amdgcn_perm(b, a, 0x05040100u),      /* (a.lo, b.lo) */
+                          __builtin_amdgcn_perm(b, a, 0x07060302u));     /* (a.hi, b.hi) */
     };
 
-    /* Periods of P rows.  The rows of the next period are already travelling from memory
-     * while this one is worked on; the granules the previous period completed are written
-     * out right after those loads were issued, so that neither is waited for before a
-     * whole period of arithmetic has passed. */
-    u32x3 ahead[P];
-#pragma unroll
-    for (int i = 0; i < P; ++i) {
-        const u32x3 zero = {0, 0, 0};
-        ahead[i] = (uint32_t)i < ph ? load_row(src + i * row_stride) : zero;
-    }
+    /* Steps 3-4 of stage 2 for one row, given its largest u in the low half and its width in
+     * the high half: deltas t - tmin = umax - u, 0 where no pixel exists; the lane's four deltas
+     * as one field of 4 w bits into the ring.  Moves rowpos to the next record. */
+    auto pack_row = [&](uint32_t extremes, uint32_t uE, uint32_t uO) {
+        const uint32_t w = extremes >> 16;
+        const uint32_t dE = pk_sub_u16_sat_from_low(extremes, uE), dO = pk_sub_u16_sat_from_low(extremes, uO);
+        const uint32_t pair = dE | (dO << w);                   /* (d0 | d1 << w, d2 | d3 << w) */
+        const uint32_t group = (pair & 0xFFFFu) | ((pair >> 16) << (2 * w));
+        put(group, rowpos + 12 + xpix * w);      /* lanes without pixels add zeros to their own ring */
+        rowpos += 12 + pw * w;
+    };
+
+    /* Periods of P rows.  A row's range takes a reduction over the patch's lanes and then a few
+     * scalar-like steps; done row by row every lane works those out for itself (101 vector
+     * instructions a row in all, which is what bounds this kernel), done for four rows at once
+     * the steps are shared (see patch_min_of_rows; about 75).  A call with 32 images of
+     * 2048x1024: 198 -> 173 us, with one of 1920x1080: 40.7 -> 34.9 us.  The rows of the next period are asked for as soon as this one's
+     * channel bytes are taken out of their registers; the granules the previous period
+     * completed are written out right behind those loads, so that neither is waited for
+     * before a whole period of arithmetic has passed. */
+    static_assert(P == 4, "patch_min_of_rows takes four rows");
+    load_rows(src, ph);
     /* issue priorities as in the decoder: lowered by quarters of the rows, an older
      * workgroup of a CU a little sooner; workgroups ahead of the launch's last round keep
      * the top priority */
@@ -408,6 +463,7 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
     const uint32_t drop_at[3] = {wg < last_round_from ? 0x7FFFFFFFu : (ph * (8u + age_rank) + 31u) / 32u,
                                  (ph * (16u + age_rank) + 31u) / 32u, (ph * (24u + age_rank) + 31u) / 32u};
     uint32_t next_drop = drop_at[0], stage = 0;
+    const bool writes_record = active && (LPT == 32 ? (xl & 14u) == 0 : xl < 4);
     __builtin_amdgcn_s_setprio(3);
     for (uint32_t r = 0; r < ph; r += P) {
         const uint32_t rows = min((uint32_t)P, ph - r);
@@ -418,39 +474,57 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
             else if (stage == 2) __builtin_amdgcn_s_setprio(1);
             else __builtin_amdgcn_s_setprio(0);
         }
-        u32x3 raw[P];
+        uint32_t cur[P][2];
+        if (ragged_wave) {
 #pragma unroll
-        for (int i = 0; i < P; ++i) raw[i] = ahead[i];
-        src += P * row_stride;
-        if (r + P < ph) {
-#pragma unroll
-            for (int i = 0; i < P; ++i)
-                if (r + P + i < ph) ahead[i] = load_row(src + i * row_stride);
+            for (int i = 0; i < P; ++i) shift_down(ahead[i]);
         }
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            take_channel(ahead[i], cur[i]);
+            L3_KEEP_VGPR(cur[i][0]);
+            L3_KEEP_VGPR(cur[i][1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        src += P * row_stride;
+        if (r + P < ph) load_rows(src, ph - (r + P));
         if (r > 0) flush(rowpos >> 7);
 
-        uint32_t rec[P], at[P];
-        at[0] = rowpos;
-        rec[0] = do_row(raw[0]);
+        uint32_t uE[P], uO[P], lane_part[P], extremes[P];
+        lane_part[0] = filter_row(up, cur[0], uE[0], uO[0]);
         if (r == 0) {            /* rows after the first are looked at as signed bytes */
-            krow = 0x80u;
-            kminE = ~validE | (keepE & 0x00800080u);
-            kminO = ~validO | (keepO & 0x00800080u);
-            kmaxE = ~validE | (keepE & 0x007F007Fu);
-            kmaxO = ~validO | (keepO & 0x007F007Fu);
+            kE = ~validE | (keepE & 0x007F007Fu);
+            kO = ~validO | (keepO & 0x007F007Fu);
         }
-        at[1] = rowpos;
-        rec[1] = rows > 1 ? do_row(raw[1]) : 0u;
-        at[2] = rowpos;
-        rec[2] = rows > 2 ? do_row(raw[2]) : 0u;
-        /* the records of the period: lane i of the patch writes the one of row i */
-        static_assert(P == 3 && LPT >= P, "one lane per record of a period");
-        const uint32_t my_rec = xl == 0 ? rec[0] : (xl == 1 ? rec[1] : rec[2]);
-        const uint32_t my_at = xl == 0 ? at[0] : (xl == 1 ? at[1] : at[2]);
-        if (active && xl < rows) put(my_rec, my_at);
+#pragma unroll
+        for (int i = 1; i < P; ++i) lane_part[i] = filter_row(cur[i - 1], cur[i], uE[i], uO[i]);
+        up[0] = cur[P - 1][0];
+        up[1] = cur[P - 1][1];
+
+        /* stage 2, steps 1-2, for all rows at once: every lane works on row my_row */
+        const uint32_t m = patch_min_of_rows<LPT>(lane_part, my_row);
+        const uint32_t umin = m & 0xFFFFu, tmin = (m >> 16) & 0xFFu, umax = tmin ^ 0xFFu;
+        const uint32_t range = (umax - umin) & 0xFFu;        /* masked: lanes without a patch hold no minimum */
+        const uint32_t my_w = 31u - (uint32_t)__builtin_clz(2u * range + 1u);
+        const uint32_t my_rec = my_w | ((tmin ^ krow) << 4);
+        krow = 0x80u;
+        /* a row that does not exist packs nothing: no u is below 0, and its width is 0 */
+        const bool exists = my_row < rows;
+        rows_to_all_lanes<LPT>(exists ? umax | (my_w << 16) : 0u, extremes);
+
+        uint32_t my_at = rowpos;
+        pack_row(extremes[0], uE[0], uO[0]);
+#pragma unroll
+        for (int i = 1; i < P; ++i) {
+            my_at = my_row == (uint32_t)i ? rowpos : my_at;
+            pack_row(extremes[i], uE[i], uO[i]);
+        }
+        if (writes_record && exists) put(my_rec, my_at);
     }
+    rowpos -= 12 * ((P - ph % P) % P);           /* the records of rows that do not exist */
     const uint32_t bytes = (rowpos + 7) / 8;
-    flush((bytes + 15) / 16);
+#pragma unroll
+    for (int i = 0; i < G::FINAL_ROUNDS; ++i) flush((bytes + 15) / 16);
     if (active && xl == 0) sizes[d.sizes_base + k] = bytes;
 }
 
