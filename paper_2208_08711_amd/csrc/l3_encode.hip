@@ -9,7 +9,7 @@
  * base, minimal width, deltas packed).  Section 4.3: patches concatenated, their
  * offsets recorded in three arrays behind a 13-byte header.
  *
- * Patch sizes 32, 64 and 128 (the ones the paper's rule picks) take three kernels:
+ * Patch sizes 32, 64 and 128 (the ones the paper's rule picks) take two or three kernels:
  *   strip    a workgroup of three waves (one per channel) owns a strip of adjacent
  *            patches, 4 pixels per lane as two packed pairs of 16-bit fields: per
  *            four rows it filters, reduces their min and max over the patch's lanes, packs
@@ -18,7 +18,8 @@
  *            patch's byte size goes to a table;
  *   layout   one workgroup per image: exclusive prefix sum of the patch sizes ->
  *            header, offset arrays, file length (this is where a scan belongs: the
- *            addends are all known);
+ *            addends are all known); only for images of very many patches, otherwise the
+ *            next kernel does this too;
  *   compact  copies every slot to its place in the file.
  * Any other patch size up to 128 takes the plain route: measure (one wave per patch
  * and channel walks the rows for the sizes), layout, pack (walks them again and
@@ -30,6 +31,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <new>
+#include <type_traits>
 
 #include "l3_ctx.h"
 #include "l3_gfx950.h"
@@ -181,6 +183,7 @@ __host__ __device__ constexpr uint32_t strip_slot_bytes(uint32_t n) {
 
 typedef __attribute__((address_space(1))) const u32x3_any global_const_u32x3_any;
 typedef __attribute__((address_space(1))) u32x4 global_u32x4;
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
 
 /* max((low half of a) - b, 0) in both 16-bit halves */
 __device__ __forceinline__ uint32_t pk_sub_u16_sat_from_low(uint32_t a, uint32_t b) {
@@ -558,41 +561,155 @@ __global__ __launch_bounds__(192) void l3_encode_strip_kernel_args(const EncodeP
     strip_block<N>(pack.d[blockIdx.y], sizes, slots);
 }
 
-/* Copies one slot of the strip route to its place in the file (one workgroup per slot). */
-template <int THREADS>
+/* The fixed part of the file's header and what the caller is told about the file. */
+__device__ __forceinline__ void write_header(const L3EncodeDesc& d, uint64_t need, uint64_t header,
+                                             uint64_t* __restrict__ file_len, uint32_t* __restrict__ status) {
+    file_len[d.status_index] = need;
+    uint32_t st = 0;
+    if (need > d.file_cap) st |= 1u;                       /* output capacity too small: nothing packed */
+    if (need - header > 0xFFFFFFFFull) st |= 2u;           /* data section beyond 32-bit offsets */
+    if (status) status[d.status_index] = st;
+    if (header <= d.file_cap) {
+        uint8_t* f = d.file;
+        f[0] = 0x4C; f[1] = 0x33; f[2] = 0x00; f[3] = 0x01;
+        for (int b = 0; b < 4; ++b) {
+            f[4 + b] = (uint8_t)(d.width >> (8 * b));
+            f[8 + b] = (uint8_t)(d.height >> (8 * b));
+        }
+        f[12] = (uint8_t)d.patch;
+    }
+}
+
+/* How a workgroup of the compaction shares its slots: a slot of a 128-pixel patch (up to 16.6 KB)
+ * takes all four waves, one of a 64-pixel patch one wave, and of the 32-pixel ones (0.8 KB
+ * on photographs, less than one granule per lane) a wave takes four, so that its loads travel
+ * together. */
+template <int N>
+struct CompactGeom {
+    static constexpr int WAVE_SLOTS = N == 32 ? 4 : 1;                      /* slots a wave works on */
+    static constexpr int LANES = N == 128 ? 256 : 64;                       /* threads on a slot */
+    static constexpr int SLOTS = N == 128 ? 1 : 4 * WAVE_SLOTS;             /* slots of a workgroup */
+    static_assert(SLOTS <= 16, "offsets inside a workgroup are a scan over one 16-lane row");
+};
+
+/* Images of at most this many patches (all channels) are laid out by the compaction itself. */
+constexpr uint32_t kOwnLayoutPatches = 4096;
+
+/* Copies the slots of the strip route to their places in the file.
+ * OWN_LAYOUT: every workgroup works out where its slots go: it adds up all patch sizes of the
+ * image and those ahead of its own (a few loads per thread, out of the L2), instead of waiting
+ * for a kernel of one workgroup per image that does so once for all (5 to 9 us, of which a call
+ * with one image has nothing to hide behind).  The work of that grows with the square of
+ * the number of patches: beyond kOwnLayoutPatches the layout kernel runs first and the
+ * offsets are read from the header. */
+template <int N, bool OWN_LAYOUT>
 __device__ __forceinline__ void compact_block(const L3EncodeDesc& d, const uint32_t* __restrict__ sizes,
                                               const uint8_t* __restrict__ slots,
-                                              const uint64_t* __restrict__ file_len) {
-    const uint32_t patches = d.tiles_x * d.tiles_y;
-    const uint32_t k = blockIdx.x;
-    if ((d.patch != 32 && d.patch != 64 && d.patch != 128) || k >= 3 * patches) return;
-    const uint64_t need = file_len[d.status_index];
-    if (need > d.file_cap || need - (13 + 12ull * patches) > 0xFFFFFFFFull) return;
-    const uint32_t bytes = sizes[d.sizes_base + k];
-    const uint32_t offset = *reinterpret_cast<const global_u32_unaligned*>((uintptr_t)(d.file + 13 + 4 * (size_t)k));
-    const uint8_t* from = slots + d.slots_base + (uint64_t)k * strip_slot_bytes(d.patch);
-    uint8_t* to = d.file + 13 + 12 * (size_t)patches + offset;
-    typedef __attribute__((address_space(1))) u32x4 global_u32x4_any __attribute__((aligned(1)));
-    const uint32_t whole = bytes / 16;
-    for (uint32_t i = threadIdx.x; i < whole; i += THREADS)
-        *reinterpret_cast<global_u32x4_any*>((uintptr_t)(to + 16 * (size_t)i)) =
-            *reinterpret_cast<const global_const_u32x4*>((uintptr_t)(from + 16 * (size_t)i));
-    const uint32_t tail = bytes - 16 * whole;
-    if (threadIdx.x < tail) to[16 * (size_t)whole + threadIdx.x] = from[16 * (size_t)whole + threadIdx.x];
+                                              uint64_t* __restrict__ file_len, uint32_t* __restrict__ status) {
+    using G = CompactGeom<N>;
+    const uint32_t patches = d.tiles_x * d.tiles_y, total = 3 * patches;
+    const uint32_t first = blockIdx.x * G::SLOTS;
+    if (d.patch != N || first >= total) return;
+    const uint64_t header = 13 + 12ull * patches;
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t* const image_sizes = sizes + d.sizes_base;
+    uint8_t* const table = d.file + 13;                   /* the three offset arrays */
+
+    /* lane j of every wave: size and offset of the workgroup's slot j */
+    const uint32_t k = first + lane;
+    const bool mine = lane < (uint32_t)G::SLOTS && k < total;
+    const uint32_t size = mine ? image_sizes[k] : 0u;
+    uint32_t offset = 0;
+    uint64_t need;
+    if (OWN_LAYOUT) {
+        uint32_t all = 0, ahead = 0;                      /* at most 4096 * 16.6 KB */
+        for (uint32_t i = threadIdx.x; i < total; i += 256) {
+            const uint32_t s = image_sizes[i];
+            all += s;
+            ahead += i < first ? s : 0u;
+        }
+#pragma unroll
+        for (int step = 32; step >= 1; step >>= 1) {
+            all += (uint32_t)__shfl_xor((int)all, step);
+            ahead += (uint32_t)__shfl_xor((int)ahead, step);
+        }
+        __shared__ uint32_t parts[4][2];
+        if (lane == 0) {
+            parts[wave][0] = all;
+            parts[wave][1] = ahead;
+        }
+        __syncthreads();
+        all = parts[0][0] + parts[1][0] + parts[2][0] + parts[3][0];
+        ahead = parts[0][1] + parts[1][1] + parts[2][1] + parts[3][1];
+        uint32_t upto = size;                             /* inclusive scan of the first 16 lanes */
+        if (G::SLOTS > 1) {
+#pragma unroll
+            for (int step = 1; step < 16; step <<= 1) {
+                const uint32_t from = (uint32_t)__shfl_up((int)upto, step);
+                upto += lane >= (uint32_t)step ? from : 0u;
+            }
+        }
+        offset = ahead + upto - size;
+        need = header + all;
+        if (wave == 0 && mine && header <= d.file_cap)
+            *reinterpret_cast<global_u32_unaligned*>((uintptr_t)(table + 4 * (size_t)k)) = offset;
+        if (first == 0 && threadIdx.x == 0) write_header(d, need, header, file_len, status);
+    } else {
+        need = file_len[d.status_index];
+    }
+    if (need > d.file_cap || need - header > 0xFFFFFFFFull) return;
+    if (!OWN_LAYOUT && mine)
+        offset = *reinterpret_cast<const global_u32_unaligned*>((uintptr_t)(table + 4 * (size_t)k));
+
+    /* Bound by memory: 32 images of 2048x1024 move 330 MB in 57 us, 256 photographs of 39 million
+     * pixels 180 MB in 40 us (the layout kernel and this one took 57 and 54 us before, with one
+     * 64-thread workgroup per slot of the photographs).  Measured slower: aligned stores with the
+     * slot read at any alignment instead (64 us with four granules per lane in flight), that
+     * many in flight otherwise (60 us), non-temporal stores (a call with 32 images in turn with
+     * others 176.5 instead of 171.6 us), non-temporal slot stores in the strip kernel (62 us here). */
+    typedef __attribute__((address_space(1))) u32x4_any global_u32x4_any;
+    const uint32_t me = N == 128 ? threadIdx.x : lane;
+    const uint8_t* from[G::WAVE_SLOTS];
+    uint8_t* to[G::WAVE_SLOTS];
+    uint32_t whole[G::WAVE_SLOTS], tail[G::WAVE_SLOTS];
+    u32x4 v[G::WAVE_SLOTS];
+    uint8_t last[G::WAVE_SLOTS];
+#pragma unroll
+    for (int j = 0; j < G::WAVE_SLOTS; ++j) {
+        const uint32_t nth = N == 128 ? 0u : wave * G::WAVE_SLOTS + j;
+        const uint32_t bytes = (uint32_t)__builtin_amdgcn_readlane((int)size, (int)nth);
+        from[j] = slots + d.slots_base + (uint64_t)(first + nth) * strip_slot_bytes(N);
+        to[j] = d.file + header + (uint32_t)__builtin_amdgcn_readlane((int)offset, (int)nth);
+        whole[j] = bytes / 16;
+        tail[j] = bytes & 15u;
+        if (me < whole[j]) v[j] = *reinterpret_cast<const global_const_u32x4*>((uintptr_t)(from[j] + 16 * me));
+        if (me < tail[j]) last[j] = from[j][16 * whole[j] + me];
+    }
+#pragma unroll
+    for (int j = 0; j < G::WAVE_SLOTS; ++j) {
+        if (me < whole[j])
+            *reinterpret_cast<global_u32x4_any*>((uintptr_t)(to[j] + 16 * me)) = v[j];
+        for (uint32_t i = me + G::LANES; i < whole[j]; i += G::LANES)
+            *reinterpret_cast<global_u32x4_any*>((uintptr_t)(to[j] + 16 * i)) =
+                *reinterpret_cast<const global_const_u32x4*>((uintptr_t)(from[j] + 16 * i));
+        if (me < tail[j]) to[j][16 * whole[j] + me] = last[j];
+    }
 }
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void l3_encode_compact_kernel(const L3EncodeDesc* __restrict__ descs,
-                                                                    const uint32_t* __restrict__ sizes,
-                                                                    const uint8_t* __restrict__ slots,
-                                                                    const uint64_t* __restrict__ file_len) {
-    compact_block<THREADS>(descs[blockIdx.y], sizes, slots, file_len);
+template <int N, bool OWN_LAYOUT>
+__global__ __launch_bounds__(256) void l3_encode_compact_kernel(const L3EncodeDesc* __restrict__ descs,
+                                                                const uint32_t* __restrict__ sizes,
+                                                                const uint8_t* __restrict__ slots,
+                                                                uint64_t* __restrict__ file_len,
+                                                                uint32_t* __restrict__ status) {
+    compact_block<N, OWN_LAYOUT>(descs[blockIdx.y], sizes, slots, file_len, status);
 }
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void l3_encode_compact_kernel_args(const EncodePack pack,
-                                                                         const uint32_t* __restrict__ sizes,
-                                                                         const uint8_t* __restrict__ slots,
-                                                                         const uint64_t* __restrict__ file_len) {
-    compact_block<THREADS>(pack.d[blockIdx.y], sizes, slots, file_len);
+template <int N, bool OWN_LAYOUT>
+__global__ __launch_bounds__(256) void l3_encode_compact_kernel_args(const EncodePack pack,
+                                                                     const uint32_t* __restrict__ sizes,
+                                                                     const uint8_t* __restrict__ slots,
+                                                                     uint64_t* __restrict__ file_len,
+                                                                     uint32_t* __restrict__ status) {
+    compact_block<N, OWN_LAYOUT>(pack.d[blockIdx.y], sizes, slots, file_len, status);
 }
 
 /* ---- the plain route: any other N up to 128 -------------------------------- */
@@ -637,23 +754,7 @@ __device__ __forceinline__ void layout_block(const L3EncodeDesc& d, const uint32
         if (threadIdx.x == 255) carry += scan[255];
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        const uint64_t need = header + carry;
-        file_len[d.status_index] = need;
-        uint32_t st = 0;
-        if (need > d.file_cap) st |= 1u;                 /* output capacity too small: nothing packed */
-        if (carry > 0xFFFFFFFFull) st |= 2u;             /* data section beyond 32-bit offsets */
-        if (status) status[d.status_index] = st;
-        if (header_fits) {
-            uint8_t* f = d.file;
-            f[0] = 0x4C; f[1] = 0x33; f[2] = 0x00; f[3] = 0x01;
-            for (int b = 0; b < 4; ++b) {
-                f[4 + b] = (uint8_t)(d.width >> (8 * b));
-                f[8 + b] = (uint8_t)(d.height >> (8 * b));
-            }
-            f[12] = (uint8_t)d.patch;
-        }
-    }
+    if (threadIdx.x == 0) write_header(d, header + carry, header, file_len, status);
 }
 __global__ __launch_bounds__(256) void l3_encode_layout_kernel(const L3EncodeDesc* __restrict__ descs,
                                                                const uint32_t* __restrict__ sizes,
@@ -739,6 +840,7 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
     size_t total_patches = 0, slot_bytes = 0;
     uint32_t max_patches = 0, max_n = 1;
     uint32_t strip_units[3] = {0, 0, 0};   /* largest grid of the strip route per N = 32, 64, 128 */
+    uint32_t strip_slots[3] = {0, 0, 0};   /* most slots of an image, likewise */
     bool any_plain = false;
     for (int i = 0; i < n; ++i) {
         const l3_encode_item& it = items[i];
@@ -758,6 +860,7 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
             const uint32_t tpw = 256 / np, tiles_x = (it.width + np - 1) / np;
             const uint64_t units = (uint64_t)((tiles_x + tpw - 1) / tpw) * ((it.height + np - 1) / np);
             if (units > strip_units[cls]) strip_units[cls] = (uint32_t)units;
+            if (3 * p > strip_slots[cls]) strip_slots[cls] = (uint32_t)(3 * p);
             slot_bytes += (size_t)(3 * p) * strip_slot_bytes(np);
         } else {
             any_plain = true;
@@ -783,6 +886,7 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
         hipStreamWaitEvent(stream, st->done, 0) != hipSuccess)
         return L3_ERR_DEVICE;
     const bool by_args = n <= kArgDescs && !any_plain;
+    const bool own_layout = max_patches <= kOwnLayoutPatches && !any_plain;
     constexpr int kStage = 4;
     int stage = 0;
     if (!by_args) {
@@ -873,22 +977,28 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
         if (strip_units[2])
             hipLaunchKernelGGL(l3_encode_strip_kernel_args<128>, dim3(strip_units[2], m), dim3(192), 0, stream,
                                pack, st->d_sizes, st->d_slots);
-        hipLaunchKernelGGL(l3_encode_layout_kernel_args, dim3(m), dim3(256), 0, stream, pack, st->d_sizes,
-                           d_file_len, d_status);
-        /* a slot of a 128-pixel patch is up to 16.6 KB: four waves; smaller ones: one */
-        if (strip_units[2])
-            hipLaunchKernelGGL(l3_encode_compact_kernel_args<256>, dim3(max_patches, m), dim3(256), 0, stream,
-                               pack, st->d_sizes, st->d_slots, d_file_len);
-        else
-            hipLaunchKernelGGL(l3_encode_compact_kernel_args<64>, dim3(max_patches, m), dim3(64), 0, stream,
-                               pack, st->d_sizes, st->d_slots, d_file_len);
+        if (!own_layout)
+            hipLaunchKernelGGL(l3_encode_layout_kernel_args, dim3(m), dim3(256), 0, stream, pack, st->d_sizes,
+                               d_file_len, d_status);
+        const auto compact = [&](auto n_tag, uint32_t most) {
+            constexpr int N = decltype(n_tag)::value;
+            const dim3 grid((most + CompactGeom<N>::SLOTS - 1) / CompactGeom<N>::SLOTS, m);
+            if (most && own_layout)
+                hipLaunchKernelGGL((l3_encode_compact_kernel_args<N, true>), grid, dim3(256), 0, stream, pack,
+                                   st->d_sizes, st->d_slots, d_file_len, d_status);
+            else if (most)
+                hipLaunchKernelGGL((l3_encode_compact_kernel_args<N, false>), grid, dim3(256), 0, stream, pack,
+                                   st->d_sizes, st->d_slots, d_file_len, d_status);
+        };
+        compact(std::integral_constant<int, 32>(), strip_slots[0]);
+        compact(std::integral_constant<int, 64>(), strip_slots[1]);
+        compact(std::integral_constant<int, 128>(), strip_slots[2]);
     } else {
         if (hipMemcpyAsync(st->d_descs, table, (size_t)n * sizeof(L3EncodeDesc), hipMemcpyHostToDevice,
                            stream) != hipSuccess ||
             hipEventRecord(st->staged[stage], stream) != hipSuccess)
             return L3_ERR_DEVICE;
         st->staged_pending[stage] = true;
-        const bool any_strip = strip_units[0] || strip_units[1] || strip_units[2];
         const size_t lds_bytes = ((size_t)max_n * (12 + 8 * (size_t)max_n) + 31) / 32 * 4 + 8;
         for (int first = 0; first < n; first += 65535) {
             const uint32_t m = (uint32_t)(n - first < 65535 ? n - first : 65535);
@@ -906,17 +1016,25 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
                 hipLaunchKernelGGL(l3_encode_measure_kernel, dim3(max_patches, m), dim3(64), 0, stream, dd,
                                    st->d_sizes);
         }
-        hipLaunchKernelGGL(l3_encode_layout_kernel, dim3((uint32_t)n), dim3(256), 0, stream, st->d_descs,
-                           st->d_sizes, d_file_len, d_status);
+        if (!own_layout)
+            hipLaunchKernelGGL(l3_encode_layout_kernel, dim3((uint32_t)n), dim3(256), 0, stream, st->d_descs,
+                               st->d_sizes, d_file_len, d_status);
         for (int first = 0; first < n; first += 65535) {
             const uint32_t m = (uint32_t)(n - first < 65535 ? n - first : 65535);
             const L3EncodeDesc* dd = st->d_descs + first;
-            if (any_strip && strip_units[2])
-                hipLaunchKernelGGL(l3_encode_compact_kernel<256>, dim3(max_patches, m), dim3(256), 0, stream,
-                                   dd, st->d_sizes, st->d_slots, d_file_len);
-            else if (any_strip)
-                hipLaunchKernelGGL(l3_encode_compact_kernel<64>, dim3(max_patches, m), dim3(64), 0, stream,
-                                   dd, st->d_sizes, st->d_slots, d_file_len);
+            const auto compact = [&](auto n_tag, uint32_t most) {
+                constexpr int N = decltype(n_tag)::value;
+                const dim3 grid((most + CompactGeom<N>::SLOTS - 1) / CompactGeom<N>::SLOTS, m);
+                if (most && own_layout)
+                    hipLaunchKernelGGL((l3_encode_compact_kernel<N, true>), grid, dim3(256), 0, stream, dd,
+                                       st->d_sizes, st->d_slots, d_file_len, d_status);
+                else if (most)
+                    hipLaunchKernelGGL((l3_encode_compact_kernel<N, false>), grid, dim3(256), 0, stream, dd,
+                                       st->d_sizes, st->d_slots, d_file_len, d_status);
+            };
+            compact(std::integral_constant<int, 32>(), strip_slots[0]);
+            compact(std::integral_constant<int, 64>(), strip_slots[1]);
+            compact(std::integral_constant<int, 128>(), strip_slots[2]);
             if (any_plain)
                 hipLaunchKernelGGL(l3_encode_pack_kernel, dim3(max_patches, m), dim3(64), lds_bytes, stream,
                                    dd, st->d_sizes, d_file_len);

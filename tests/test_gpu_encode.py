@@ -253,3 +253,23 @@ def test_three_pixel_rows_over_a_value_grid_encode_like_the_oracle(l3, ctx):
         want = oracle.encode(im, 32)
         assert lens[i] == len(want), i
         assert got[i, :len(want)].tobytes() == want, i
+
+
+@pytest.mark.parametrize("tiles", [(35, 39), (36, 38), (1, 1), (5, 1), (11, 1), (16, 1)])
+def test_files_are_laid_out_alike_on_both_sides_of_the_limit(l3, ctx, tiles):
+    """Up to 4096 patches (3 x 35 x 39 = 4095) the copying kernel works the offsets out itself, above
+    (3 x 36 x 38 = 4104) a kernel ahead of it does; a workgroup of the copy takes 16 patches."""
+    im = synth.cosine_field(1970, tiles[0] * 32 - 5, tiles[1] * 32 - 3)
+    check(l3, ctx, [im], patch=32)
+    h, w = im.shape[:2]
+    want = oracle.encode(im, 32)
+    buf = torch.full((len(want),), 0xAB, dtype=torch.uint8, device="cuda")
+    lens = torch.zeros(1, dtype=torch.int64, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    dev = torch.from_numpy(im.reshape(h, 3 * w).copy()).cuda()
+    l3.encode_batch(ctx, [_Shape(dev, h, w)], [buf[:len(want) - 1]], lens, patch=32, status=status)
+    torch.cuda.synchronize()
+    assert int(status[0]) == 1 and int(lens[0]) == len(want)
+    header = 13 + 12 * tiles[0] * tiles[1]
+    assert (buf.cpu().numpy()[header:] == 0xAB).all()              # no stream is packed
+    assert buf.cpu().numpy()[:header].tobytes() == want[:header]
