@@ -4,8 +4,10 @@ Same names as the C entry points (without the l3_ prefix); argument marshalling
 only.  torch is used for device memory and streams, nothing else.  There is no
 CPU fallback: if libl3.so is missing, every call raises.
 """
+import array
 import ctypes
 import os
+import sys
 
 import numpy as np
 
@@ -45,6 +47,14 @@ class _EncodeItem(ctypes.Structure):
     _fields_ = [("d_rgb", ctypes.c_void_p), ("row_stride", ctypes.c_size_t),
                 ("width", ctypes.c_uint32), ("height", ctypes.c_uint32), ("patch", ctypes.c_uint8),
                 ("d_file", ctypes.c_void_p), ("file_cap", ctypes.c_size_t)]
+
+
+# encode_batch fills the array word by word (a data set is written hundreds of images a call, and
+# setting ctypes fields one by one took 0.8 us an image, longer than the kernels; this takes
+# half): this is the layout it relies on
+assert (ctypes.sizeof(_EncodeItem) == 48 and _EncodeItem.width.offset == 16 and _EncodeItem.height.offset == 20 and
+        _EncodeItem.patch.offset == 24 and _EncodeItem.d_file.offset == 32 and sys.byteorder == "little")
+_MASK32, _MASK64 = (1 << 32) - 1, (1 << 64) - 1
 
 
 class _Crop(ctypes.Structure):
@@ -314,15 +324,15 @@ def encode_batch(ctx, images, files, file_len, patch=0, status=None, stream=None
     given); files: list of uint8 device tensors that receive the L3 files; file_len: int64 (or
     uint64) device tensor of len(images) words; patch: one N for all or a list."""
     n = len(images)
-    arr = (_EncodeItem * max(n, 1))()
+    patches = patch if isinstance(patch, (list, tuple)) else (patch,) * n
+    words = array.array("Q")        # the l3_encode_item array, see _EncodeItem: 6 words of 8 bytes each
     for i in range(n):
-        h, w = int(images[i].shape[0]), int(images[i].shape[1])
-        arr[i].d_rgb = images[i].data_ptr()
-        arr[i].row_stride = row_strides[i] if row_strides is not None else 3 * w
-        arr[i].width, arr[i].height = w, h
-        arr[i].patch = patch[i] if isinstance(patch, (list, tuple)) else patch
-        arr[i].d_file = files[i].data_ptr()
-        arr[i].file_cap = files[i].numel()
+        shape, out = images[i].shape, files[i]
+        h, w = int(shape[0]), int(shape[1])
+        stride = 3 * w if row_strides is None else row_strides[i]
+        words.extend((images[i].data_ptr(), stride & _MASK64,
+                      (w & _MASK32) | (h & _MASK32) << 32, patches[i] & 0xFF, out.data_ptr(), out.numel()))
+    arr = (_EncodeItem * n).from_buffer(words) if n else (_EncodeItem * 1)()
     _check(_load().l3_encode_batch(ctx.handle, arr, n, ctypes.c_void_p(file_len.data_ptr()),
                                    ctypes.c_void_p(status.data_ptr() if status is not None else None),
                                    _stream_ptr(stream)), "l3_encode_batch")
