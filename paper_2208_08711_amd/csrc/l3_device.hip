@@ -94,11 +94,14 @@ struct Geom {
  * addressed by their 32-bit LDS byte address. */
 typedef LdsPair RingWords;
 template <int RING>
-__device__ __forceinline__ uint32_t ring_where(uint32_t ring_lds, uint32_t bit) {
+__device__ __forceinline__ uint32_t ring_word_bits() {
     static_assert((RING & (RING - 1)) == 0, "ring size is a power of two");
-    uint32_t word = __builtin_amdgcn_ubfe(bit, 5, __builtin_ctz(RING / 4));
-    L3_OPAQUE_VGPR(word);            /* keep bfe + shift-add: two instructions, not three */
-    return (word << 2) + ring_lds;
+    uint32_t bits = __builtin_ctz(RING / 4);
+    L3_KEEP_SGPR(bits);     /* unknown to the compiler: a bit-field extract and a shift-add below, not three instructions */
+    return bits;
+}
+__device__ __forceinline__ uint32_t ring_where(uint32_t ring_lds, uint32_t bit, uint32_t word_bits) {
+    return (__builtin_amdgcn_ubfe(bit, 5, word_bits) << 2) + ring_lds;
 }
 __device__ __forceinline__ RingWords ring_fetch(uint32_t where) {
     return lds_read_pair(where);   /* the second word may be the mirror word behind the ring */
@@ -270,12 +273,11 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
      * register beside it and the top-left neighbours of an odd register the even one;
      * the other neighbours take one alignbit, the two outermost a lane shift. */
     const uint32_t xpix = xl * PPL;                         /* first pixel column of this lane */
-    uint32_t border[NP];
+    /* the predictor's limits: see predict_pairs_biased */
+    uint32_t least[NP], most[NP];
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
-        const uint32_t xa = xpix + 4 * (j / 2) + (j & 1), xb = xa + 2;
-        border[j] = ((xa == 0 || xa + 1 == pw) ? 0x0000FFFFu : 0u) |
-                    ((xb == 0 || xb + 1 == pw) ? 0xFFFF0000u : 0u);
+        predict_limits(xpix + 4 * (j / 2) + (j & 1), pw, least[j], most[j]);
     }
 
     /* what the arithmetic of a row needs from its base-delta record */
@@ -288,23 +290,29 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
      * where this lane's deltas are (4w <= 32 contiguous bits per word of 4 pixels) and
      * advances bitpos to the next record.  A width above 8 (damaged stream) is not
      * clamped: ring indices are masked and global loads are bounded by the file, so it
-     * can only produce wrong pixels. */
+     * can only produce wrong pixels.
+     * Every lane does this for every row, so its length counts: the base goes into both
+     * halves with one packed shift, with four bits of the first delta above it that the masks
+     * of the sum take off.  (Measured slower: the distances w * pixels + 12 as one
+     * v_dot2_u32_u16 each instead of an addition shared by two multiply-adds, one instruction
+     * less: one full-HD image 20.1 -> 20.7 us, 16 windows of 768x768 53.9 -> 54.6 us.) */
+    const uint32_t word_bits = ring_word_bits<RING>();
+    uint32_t four = 0x00040004u;
+    L3_KEEP_SGPR(four);
     auto open_row = [&](RingWords hw) {
         const uint32_t hdr = ring_align(hw, bitpos);
-        const uint32_t wr = hdr & 15u;
-        const uint32_t base = __builtin_amdgcn_ubfe(hdr, 4, 8);
+        w = hdr & 15u;
+        base2 = low_b16_lshr_twice(four, hdr);
         const uint32_t dbit = bitpos + 12;
-        bitpos = dbit + pw * wr;
-        xbit[0] = dbit + xpix * wr;
+        bitpos = dbit + pw * w;
+        xbit[0] = dbit + xpix * w;
 #pragma unroll
-        for (int k = 1; k < NW; ++k) xbit[k] = xbit[k - 1] + 4 * wr;
+        for (int k = 1; k < NW; ++k) xbit[k] = xbit[k - 1] + 4 * w;
 #pragma unroll
-        for (int k = 0; k < NW; ++k) xwhere[k] = ring_where<RING>(ring_lds, xbit[k]);
-        hwhere = ring_where<RING>(ring_lds, bitpos);
-        w = wr;
-        w2 = wr + wr;
-        K = 0xFFFFFFFFu << wr;
-        base2 = base | (base << 16);
+        for (int k = 0; k < NW; ++k) xwhere[k] = ring_where(ring_lds, xbit[k], word_bits);
+        hwhere = ring_where(ring_lds, bitpos, word_bits);
+        w2 = w + w;
+        K = 0xFFFFFFFFu << w;
     };
 
     /* What the write-out needs from the descriptor, pinned in registers: left to
@@ -337,6 +345,13 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
         word_off[pass] = (MODE == L3_MODE_HWC ? 3u : 1u) * word_x[pass] +
                          (ty - ty_base) * (uint32_t)N * (uint32_t)out_row_stride;
     }
+    /* no lane of the wave has a word that is cut off or not there: one scalar branch then
+     * stands for the tests of every row's write-out (with planar rows stored as they are decoded,
+     * two vector and ten scalar instructions a row) */
+    bool partial = false;
+#pragma unroll
+    for (int pass = 0; pass < NW; ++pass) partial |= word_valid[pass] != 4;
+    const bool wave_whole = !wave_any(partial);
     /* tensor mode: whether the word's 4 pixels all lie inside the window, and the byte offset
      * of its 4 elements in a row of the window (mirrored or not): the same for every row */
     bool tensor_whole[NW];
@@ -371,11 +386,11 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
                 /* row start: scalar arithmetic; the lane's 32-bit column offset goes into the
                  * store's offset register (kept opaque here so that it is not widened and
                  * added with vector instructions ahead of time) */
-                uint32_t column = word_off[pass];
-                L3_KEEP_VGPR(column);
+                L3_KEEP_VGPR(word_off[pass]);
+                const uint32_t column = word_off[pass];
                 global_u8* row = reinterpret_cast<global_u8*>((uintptr_t)(out_base + (uint64_t)y * out_row_stride));
                 const uint32_t o0 = pr, o1 = pg, o2 = pb;
-                if (nvalid == 4) {
+                if (wave_whole || nvalid == 4) {
                     const u32x3 v = {o0, o1, o2};
                     __builtin_nontemporal_store(v, reinterpret_cast<global_u32x3_any*>(row + column));
                 } else if (nvalid) {
@@ -399,9 +414,9 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
                     const uint32_t word = ch == 0 ? pr : (ch == 1 ? pg : pb);
                     global_u8* row = reinterpret_cast<global_u8*>(
                         (uintptr_t)(out_base + (uint64_t)ch * out_plane_stride + (uint64_t)y * out_row_stride));
-                    uint32_t column = word_off[pass];
-                    L3_KEEP_VGPR(column);
-                    if (nvalid == 4) {
+                    L3_KEEP_VGPR(word_off[pass]);
+                    const uint32_t column = word_off[pass];
+                    if (wave_whole || nvalid == 4) {
                         __builtin_nontemporal_store(word, reinterpret_cast<global_u32_any*>(row + column));
                     } else if (nvalid) {
                         global_u8* b = row + column;
@@ -477,8 +492,11 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
 
     uint32_t prev[NP];
 #pragma unroll
-    for (int j = 0; j < NP; ++j) prev[j] = 0;   /* an all-zero row above predicts 0: row 0 is raw */
-    open_row(ring_fetch(ring_where<RING>(ring_lds, bitpos)));
+    for (int j = 0; j < NP; ++j) prev[j] = kPixelBias;   /* an all-zero row above predicts 0: row 0 is raw */
+    uint32_t pixel_bits = 0x00FF00FFu, pixel_bias = kPixelBias;
+    L3_KEEP_VGPR(pixel_bits);      /* one of the two constants of an instruction may be scalar */
+    L3_KEEP_SGPR(pixel_bias);
+    open_row(ring_fetch(ring_where(ring_lds, bitpos, word_bits)));
 
     /* One row: no branch inside.  The deltas of the row and the record of the next
      * row travel from LDS while part 1 is computed; after the last row the record
@@ -506,12 +524,11 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
             TL[2 * k + 1] = E;
             TR[2 * k + 1] = __builtin_amdgcn_alignbit(k < NW - 1 ? prev[2 * k + 2] : from_right, E, 16);
         }
-        predict_pairs<NP>(TL, TR, prev, border, pred);
+        predict_pairs_biased<NP>(TL, TR, prev, least, most, pred);
         __builtin_amdgcn_sched_barrier(0);
 
         /* base-delta: value = base + delta; part 2 of the filter: pixel = prediction
          * + value (both mod 256, one mask at the end) */
-        wmax = max(wmax, w);
         uint32_t word[NW];
 #pragma unroll
         for (int k = 0; k < NW; ++k) {
@@ -525,8 +542,8 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
             const uint32_t Y = f01 | (f23 << 16);
             const uint32_t B = pk_lshr_b16_by_low(w, Y);
             const uint32_t A = pk_mad_u16_by_low(B, K, Y);   /* before the 32-bit sums: Y's halves are full */
-            prev[2 * k] = (A + pred[2 * k] + base2) & 0x00FF00FFu;
-            prev[2 * k + 1] = (B + pred[2 * k + 1] + base2) & 0x00FF00FFu;
+            prev[2 * k] = ((A + pred[2 * k] + base2) & pixel_bits) | pixel_bias;
+            prev[2 * k + 1] = ((B + pred[2 * k + 1] + base2) & pixel_bits) | pixel_bias;
             if (MODE != L3_MODE_HWC)
                 word[k] = __builtin_amdgcn_perm(prev[2 * k + 1], prev[2 * k], 0x06020400u);   /* p0 p1 p2 p3 */
         }
@@ -544,12 +561,11 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
         } else if (DIRECT) {
             global_u8* row = reinterpret_cast<global_u8*>(
                 (uintptr_t)(out_base + (uint64_t)c * out_plane_stride + (uint64_t)y * out_row_stride));
-            uint32_t column = word_off[0];
-            L3_KEEP_VGPR(column);
-            if (word_valid[0] == 4) {
-                __builtin_nontemporal_store(word[0], reinterpret_cast<global_u32_any*>(row + column));
+            L3_KEEP_VGPR(word_off[0]);
+            if (wave_whole || word_valid[0] == 4) {
+                __builtin_nontemporal_store(word[0], reinterpret_cast<global_u32_any*>(row + word_off[0]));
             } else if (word_valid[0]) {
-                global_u8* b = row + column;
+                global_u8* b = row + word_off[0];
 #pragma unroll
                 for (int k = 0; k < 3; ++k)
                     if ((uint32_t)k < word_valid[0]) b[k] = (uint8_t)(word[0] >> (8 * k));
@@ -612,12 +628,18 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
                              ? reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(&parked[buf][0][0][0]) +
                                                            lane * (12 * NW) + c)
                              : &parked[buf][0][c][lane * NW];
+        const uint32_t w_first = w;
         do_row(park, y0 + r);
         if (!DIRECT && LATE_BARRIER && r > 0) {
             __syncthreads();
             flush(prev_buf, r - P, P);
         }
-        if (rows > 1) do_row(park + 3 * QW, y0 + r + 1);
+        if (rows > 1) {
+            wmax = max3_u32(wmax, w_first, w);   /* the widest width: rows 0 and 1 in one instruction */
+            do_row(park + 3 * QW, y0 + r + 1);
+        } else {
+            wmax = max(wmax, w_first);
+        }
         if (rows > 2) {
             if (r + P < ph) {
                 /* top the ring up for rows r+3 .. r+5; bitpos is the record of row r+3.  `fill`
@@ -656,6 +678,7 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
                 }
                 wave_lds_fence();
             }
+            wmax = max(wmax, w);
             do_row(park + 2 * 3 * QW, y0 + r + 2);
         }
         prev_buf = buf;

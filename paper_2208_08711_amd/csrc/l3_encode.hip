@@ -185,11 +185,10 @@ typedef __attribute__((address_space(1))) const u32x3_any global_const_u32x3_any
 typedef __attribute__((address_space(1))) u32x4 global_u32x4;
 typedef u32x4 u32x4_any __attribute__((aligned(1)));
 
-/* max((low half of a) - b, 0) in both 16-bit halves */
+/* max((low half of a) - b, 0) in both 16-bit halves: v_pk_sub_u16 with clamp */
 __device__ __forceinline__ uint32_t pk_sub_u16_sat_from_low(uint32_t a, uint32_t b) {
-    uint32_t d;
-    asm("v_pk_sub_u16 %0, %1, %2 op_sel_hi:[0,1] clamp" : "=v"(d) : "v"(a), "v"(b));
-    return d;
+    const unsigned short low = (unsigned short)a;
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat((u16x2){low, low}, __builtin_bit_cast(u16x2, b)));
 }
 __device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a),
@@ -291,9 +290,9 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
     /* registers of two 16-bit fields: E = pixels (0, 2), O = pixels (1, 3) */
     const uint32_t validE = (nvalid > 0 ? 0x0000FFFFu : 0u) | (nvalid > 2 ? 0xFFFF0000u : 0u);
     const uint32_t validO = (nvalid > 1 ? 0x0000FFFFu : 0u) | (nvalid > 3 ? 0xFFFF0000u : 0u);
-    uint32_t border[2];
-    border[0] = ((xpix == 0 || xpix + 1 == pw) ? 0x0000FFFFu : 0u) | ((xpix + 3 == pw) ? 0xFFFF0000u : 0u);
-    border[1] = ((xpix + 2 == pw) ? 0x0000FFFFu : 0u) | ((xpix + 4 == pw) ? 0xFFFF0000u : 0u);
+    uint32_t least[2], most[2];              /* the predictor's limits: see predict_pairs_biased */
+    predict_limits(xpix, pw, least[0], most[0]);
+    predict_limits(xpix + 1, pw, least[1], most[1]);
     const uint32_t keepE = validE & 0x00FF00FFu, keepO = validO & 0x00FF00FFu;
 
     /* The residual byte r is looked at as t = r ^ K, K = 0 in the first row (raw,
@@ -396,9 +395,13 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
         wave_lds_fence();
     };
 
-    uint32_t up[2] = {0, 0};   /* the original row above the period; zeros above the first row predict 0 */
+    /* the original row above the period; zeros above the first row predict 0 */
+    uint32_t up[2] = {kPixelBias, kPixelBias};
+    uint32_t pixel_bias = kPixelBias;
+    L3_KEEP_SGPR(pixel_bias);
 
-    /* channel C of pixel i is byte 3 i + C of the lane's 12 bytes */
+    /* channel C of pixel i is byte 3 i + C of the lane's 12 bytes; biased as the predictor takes
+     * it (the bias goes again with the subtraction of the prediction) */
     auto take_channel = [&](const u32x3 raw, uint32_t (&cur)[2]) {
         if (C == 0) {
             cur[0] = __builtin_amdgcn_perm(raw.y, raw.x, 0x0C060C00u);   /* bytes 0, 6 */
@@ -410,6 +413,8 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
             cur[0] = __builtin_amdgcn_perm(raw.z, raw.x, 0x0C040C02u);   /* bytes 2, 8 */
             cur[1] = __builtin_amdgcn_perm(raw.z, raw.y, 0x0C070C01u);   /* bytes 5, 11 */
         }
+        cur[0] |= pixel_bias;
+        cur[1] |= pixel_bias;
     };
 
     /* Section 4.2 stage 1 on the original row above; leaves u and the lane's own part of the
@@ -422,7 +427,7 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
         TR[0] = above[1];
         TL[1] = above[0];
         TR[1] = __builtin_amdgcn_alignbit(from_right, above[0], 16);
-        predict_pairs<2>(TL, TR, above, border, pred);
+        predict_pairs_biased<2>(TL, TR, above, least, most, pred);
         const uint32_t rE = __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, cur[0]) -
                                                                  __builtin_bit_cast(u16x2, pred[0])));
         const uint32_t rO = __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, cur[1]) -

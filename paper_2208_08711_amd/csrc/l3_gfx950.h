@@ -17,6 +17,8 @@ namespace {
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef u32x3 u32x3_any __attribute__((aligned(1)));      /* any byte alignment */
@@ -41,22 +43,62 @@ __device__ __forceinline__ uint32_t dpp_from_upper_lane(uint32_t v) {   /* lane 
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130 /* wave_shl:1 */, 0xF, 0xF, true);
 }
 
-__device__ __forceinline__ uint32_t pk_mad_i16(uint32_t a, uint32_t b, uint32_t c) {
-    uint32_t d;
-    asm("v_pk_mad_i16 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
-    return d;
+/* What follows is written with builtins where these become the instruction named, and not as
+ * inline assembly: behind that the compiler puts a wait state (s_nop) ahead of every use. */
+
+/* Both 16-bit halves of v shifted right by the low half of `by` (modulo 16): v_pk_lshrrev_b16. */
+__device__ __forceinline__ uint32_t pk_lshr_b16_by_low(uint32_t by, uint32_t v) {
+    const unsigned short s = (unsigned short)(by & 15u);
+    return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, v) >> (u16x2){s, s}));
+}
+/* a * (low half of b) + c in both 16-bit halves, modulo 2^16: v_pk_mad_u16. */
+__device__ __forceinline__ uint32_t pk_mad_u16_by_low(uint32_t a, uint32_t b, uint32_t c) {
+    const unsigned short f = (unsigned short)b;
+    return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, a) * (u16x2){f, f} + __builtin_bit_cast(u16x2, c)));
+}
+/* Both 16-bit halves: the low half of v shifted right by the halves of `by` (below 16; a value
+ * that the compiler does not know, or it shifts before it copies): v_pk_lshrrev_b16. */
+__device__ __forceinline__ uint32_t low_b16_lshr_twice(uint32_t by, uint32_t v) {
+    const unsigned short low = (unsigned short)v;
+    return __builtin_bit_cast(uint32_t, (u16x2)((u16x2){low, low} >> __builtin_bit_cast(u16x2, by)));
 }
 
-/* Both 16-bit halves of v shifted right by the low half of `by`. */
-__device__ __forceinline__ uint32_t pk_lshr_b16_by_low(uint32_t by, uint32_t v) {
-    uint32_t d;
-    asm("v_pk_lshrrev_b16 %0, %1, %2 op_sel_hi:[0,1]" : "=v"(d) : "v"(by), "v"(v));
-    return d;
+/* Packed 16-bit floats, used as exact integers.  Smallest and largest of three
+ * (v_pk_minimum3_f16, v_pk_maximum3_f16): */
+__device__ __forceinline__ uint32_t pk_min3_f16(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_minimum(
+        __builtin_elementwise_minimum(__builtin_bit_cast(f16x2, a), __builtin_bit_cast(f16x2, b)), __builtin_bit_cast(f16x2, c)));
 }
-/* a * (low half of b) + c in both 16-bit halves, modulo 2^16. */
-__device__ __forceinline__ uint32_t pk_mad_u16_by_low(uint32_t a, uint32_t b, uint32_t c) {
+__device__ __forceinline__ uint32_t pk_max3_f16(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_maximum(
+        __builtin_elementwise_maximum(__builtin_bit_cast(f16x2, a), __builtin_bit_cast(f16x2, b)), __builtin_bit_cast(f16x2, c)));
+}
+__device__ __forceinline__ uint32_t pk_add_f16(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, (f16x2)(__builtin_bit_cast(f16x2, a) + __builtin_bit_cast(f16x2, b)));
+}
+__device__ __forceinline__ uint32_t pk_sub_f16(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, (f16x2)(__builtin_bit_cast(f16x2, a) - __builtin_bit_cast(f16x2, b)));
+}
+/* c + a * b and c - a * b, rounded once (v_pk_fma_f16) */
+__device__ __forceinline__ uint32_t pk_fma_f16(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(f16x2, a), __builtin_bit_cast(f16x2, b),
+                                                                  __builtin_bit_cast(f16x2, c)));
+}
+__device__ __forceinline__ uint32_t pk_fnma_f16(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(-__builtin_bit_cast(f16x2, a), __builtin_bit_cast(f16x2, b),
+                                                                  __builtin_bit_cast(f16x2, c)));
+}
+/* 2a - b, held between 0 and 1 (one v_pk_fma_f16 with clamp): of whole numbers, 1 where 2a > b
+ * and 0 elsewhere */
+__device__ __forceinline__ uint32_t pk_twice_exceeds_f16(uint32_t a, uint32_t b) {
+    const f16x2 zero = {0, 0}, one = {1, 1}, two = {2, 2};
+    const f16x2 d = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, a), two, -__builtin_bit_cast(f16x2, b));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_elementwise_max(d, zero), one));
+}
+/* One instruction also where the compiler would keep the inner maximum for another path. */
+__device__ __forceinline__ uint32_t max3_u32(uint32_t a, uint32_t b, uint32_t c) {
     uint32_t d;
-    asm("v_pk_mad_u16 %0, %1, %2, %3 op_sel_hi:[1,0,1]" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    asm("v_max3_u32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
     return d;
 }
 

@@ -11,59 +11,62 @@
 
 namespace {
 
-/* Section 4.2, custom Paeth filter, on NP registers of two pixels at once (16-bit
- * fields holding 0..255).  Value-wise the nearest of TL, TR, T to TL + TR - T is:
- * with lo = min(TL,TR), hi = max(TL,TR), dl = T - lo, dh = hi - T (signed):
- * lo if dl >= 2*dh, else hi if dh >= 2*dl, else T.  The stated tie order
- * (TL, TR, T) only ever chooses between equal values, except T against a
- * neighbour, where the neighbour wins: that is the ">=" above.
- * `border` has all ones in the fields whose pixel sits in the first or last
- * column of its patch, where the prediction is T.  The registers are worked on
- * in lockstep so that dependent packed instructions are not adjacent. */
+/* Section 4.2, custom Paeth filter, on NP registers of two pixels at once.  Value-wise the
+ * nearest of TL, TR, T to TL + TR - T is: with lo = min(TL,TR), hi = max(TL,TR), dl = T - lo,
+ * dh = hi - T: lo if dl >= 2 dh, else hi if dh >= 2 dl, else T.  The stated tie order
+ * (TL, TR, T) only ever chooses between equal values, except T against a neighbour, where
+ * the neighbour wins: that is the ">=".
+ * The decoder and the encoder are bound by the number of their vector instructions; this takes 9
+ * a register (11 with integer masks: a multiply-add and a shift for each, three selects).
+ * A field holds the pixel as a 16-bit float from 1024 to 1279: bits 0x6400 | pixel, so that nothing
+ * is converted.  All values are whole numbers of at most 11 bits, which 16-bit floats hold
+ * exactly.  n_lo = (2 dh > dl) and n_hi = (2 dl > dh) are one multiply-add each, clamped to
+ * 0..1, and the prediction is lo + dh + n_lo * dl - n_hi * dh: T where both hold, hi where
+ * n_hi does not (then n_lo holds or dl is 0), lo where n_lo does not (then n_hi holds or dh is
+ * 0).  In the first and last column of a patch, where the prediction is T, a third operand of the
+ * minimum and of the maximum makes lo = 0 and hi = 1919: then dl = T is 1024..1279, dh = 1919 - T
+ * is 640..895, both n hold and the sum is T, whatever the outer neighbours hold (0, or another
+ * patch's pixel).  The registers are worked on in lockstep so that dependent instructions are
+ * not adjacent.
+ * Measured with the shorter record walk of the decoder's open_row, before and after on one card:
+ * 32 images of 2048x1024 88.4 -> 85.0 us a call, 32 of 1920x1080 planar 85.1 -> 80.4, 256 photographs
+ * 61.7 -> 59.6.  Written as inline assembly it cost the small calls what it gained (4 images of
+ * 2048x1024, one wave per SIMD: 36.0 us against 35.6 before): behind that the compiler puts wait
+ * states.  With builtins, and the write-out's tests taken once, 34.2, 84.2, 76.9 and 59.5 us. */
+constexpr uint32_t kPixelBias = 0x64006400u;          /* 1024 in both fields: a pixel of value 0 */
+constexpr uint32_t kPredictLow = 0x0000u;             /* 0, border fields' third operand of the minimum */
+constexpr uint32_t kPredictHigh = 0x677Fu;            /* 1919, of the maximum */
+constexpr uint32_t kPredictNoLimitLow = 0x67FFu;      /* 2047 and 0: all other fields */
+constexpr uint32_t kPredictNoLimitHigh = 0x0000u;
+/* The third operands for a register that holds pixels x and x + 2 of a patch of pw columns. */
+__device__ __forceinline__ void predict_limits(uint32_t x, uint32_t pw, uint32_t& least, uint32_t& most) {
+    const bool edge_lo = x == 0 || x + 1 == pw, edge_hi = x + 3 == pw;
+    least = (edge_lo ? kPredictLow : kPredictNoLimitLow) | ((edge_hi ? kPredictLow : kPredictNoLimitLow) << 16);
+    most = (edge_lo ? kPredictHigh : kPredictNoLimitHigh) | ((edge_hi ? kPredictHigh : kPredictNoLimitHigh) << 16);
+}
 template <int NP>
-__device__ __forceinline__ void predict_pairs(const uint32_t (&TL)[NP], const uint32_t (&TR)[NP],
-                                              const uint32_t (&T)[NP], const uint32_t (&border)[NP],
-                                              uint32_t (&pred)[NP]) {
-    uint32_t L[NP], H[NP], dl[NP], dh[NP], not_lo[NP], not_hi[NP];
-    const uint32_t minus2 = 0xFFFEFFFEu;
+__device__ __forceinline__ void predict_pairs_biased(const uint32_t (&TL)[NP], const uint32_t (&TR)[NP],
+                                                     const uint32_t (&T)[NP], const uint32_t (&least)[NP],
+                                                     const uint32_t (&most)[NP], uint32_t (&pred)[NP]) {
+    uint32_t lo[NP], hi[NP], dl[NP], dh[NP], n_lo[NP], n_hi[NP];
 #pragma unroll
-    for (int j = 0; j < NP; ++j)
-        L[j] = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, TL[j]),
-                                                                      __builtin_bit_cast(u16x2, TR[j])));
+    for (int j = 0; j < NP; ++j) lo[j] = pk_min3_f16(TL[j], TR[j], least[j]);
 #pragma unroll
-    for (int j = 0; j < NP; ++j)
-        H[j] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, TL[j]),
-                                                                      __builtin_bit_cast(u16x2, TR[j])));
+    for (int j = 0; j < NP; ++j) hi[j] = pk_max3_f16(TL[j], TR[j], most[j]);
 #pragma unroll
-    for (int j = 0; j < NP; ++j)
-        dl[j] = __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, T[j]) -
-                                                     __builtin_bit_cast(u16x2, L[j])));
+    for (int j = 0; j < NP; ++j) dl[j] = pk_sub_f16(T[j], lo[j]);
 #pragma unroll
-    for (int j = 0; j < NP; ++j)
-        dh[j] = __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, H[j]) -
-                                                     __builtin_bit_cast(u16x2, T[j])));
+    for (int j = 0; j < NP; ++j) dh[j] = pk_sub_f16(hi[j], T[j]);
 #pragma unroll
-    for (int j = 0; j < NP; ++j) not_lo[j] = pk_mad_i16(dh[j], minus2, dl[j]);   /* dl - 2 dh */
+    for (int j = 0; j < NP; ++j) n_lo[j] = pk_twice_exceeds_f16(dh[j], dl[j]);
 #pragma unroll
-    for (int j = 0; j < NP; ++j) not_hi[j] = pk_mad_i16(dl[j], minus2, dh[j]);   /* dh - 2 dl */
+    for (int j = 0; j < NP; ++j) n_hi[j] = pk_twice_exceeds_f16(dl[j], dh[j]);
 #pragma unroll
-    for (int j = 0; j < NP; ++j)
-        not_lo[j] = __builtin_bit_cast(uint32_t, (s16x2)(__builtin_bit_cast(s16x2, not_lo[j]) >> 15));
+    for (int j = 0; j < NP; ++j) pred[j] = pk_add_f16(lo[j], dh[j]);
 #pragma unroll
-    for (int j = 0; j < NP; ++j)
-        not_hi[j] = __builtin_bit_cast(uint32_t, (s16x2)(__builtin_bit_cast(s16x2, not_hi[j]) >> 15));
+    for (int j = 0; j < NP; ++j) pred[j] = pk_fma_f16(n_lo[j], dl[j], pred[j]);
 #pragma unroll
-    for (int j = 0; j < NP; ++j) {   /* keep the masks packed */
-        L3_OPAQUE_VGPR(not_lo[j]);
-        L3_OPAQUE_VGPR(not_hi[j]);
-    }
-    /* bitop3 0xCA: first ? second : third */
-#pragma unroll
-    for (int j = 0; j < NP; ++j) pred[j] = __builtin_amdgcn_bitop3_b32(not_hi[j], T[j], H[j], 0xCA);
-#pragma unroll
-    for (int j = 0; j < NP; ++j) pred[j] = __builtin_amdgcn_bitop3_b32(not_lo[j], pred[j], L[j], 0xCA);
-#pragma unroll
-    for (int j = 0; j < NP; ++j) pred[j] = __builtin_amdgcn_bitop3_b32(border[j], T[j], pred[j], 0xCA);
+    for (int j = 0; j < NP; ++j) pred[j] = pk_fnma_f16(n_hi[j], dh[j], pred[j]);
 }
 
 /* Which (image, unit) a workgroup takes.  The grid is one-dimensional, a multiple of 8

@@ -727,6 +727,31 @@ class Emu:
     def i_v_pk_max_u16(self, w, ins, a, m): self._pk(w, ins, a, m, lambda x, y: np.maximum(x, y), 2)
     def i_v_pk_lshrrev_b16(self, w, ins, a, m): self._pk(w, ins, a, m, lambda s, x: x >> (s & U32(15)), 2)
 
+    # packed 16-bit floats: in double, rounded once
+    def _pkf(self, w, ins, a, m, fn, nsrc):
+        def signs(key):
+            return [int(t) for t in m[key].strip("[]").split(",")] if key in m else [0] * nsrc
+        lo_sel, hi_sel = self._opsel(m, nsrc)
+        out = []
+        for sel, neg in ((lo_sel, signs("neg_lo")), (hi_sel, signs("neg_hi"))):
+            args = []
+            for k in range(nsrc):
+                if a[1 + k] == "2.0":                      # the constant sits in the low half
+                    v = np.full(LANES, 2.0 if sel[k] == 0 else 0.0)
+                else:
+                    v = self._halves(self.rv(w, a[1 + k]))[sel[k]].astype(np.uint16).view(np.float16).astype(np.float64)
+                args.append(-v if neg[k] else v)
+            v = fn(*args)
+            if "clamp" in m:
+                v = np.clip(v, 0.0, 1.0)
+            out.append(v.astype(np.float16).view(np.uint16).astype(U32))
+        self.wv(w, a[0], out[0] | (out[1] << U32(16)))
+
+    def i_v_pk_add_f16(self, w, ins, a, m): self._pkf(w, ins, a, m, lambda x, y: x + y, 2)
+    def i_v_pk_fma_f16(self, w, ins, a, m): self._pkf(w, ins, a, m, lambda x, y, z: x * y + z, 3)
+    def i_v_pk_minimum3_f16(self, w, ins, a, m): self._pkf(w, ins, a, m, lambda x, y, z: np.minimum(np.minimum(x, y), z), 3)
+    def i_v_pk_maximum3_f16(self, w, ins, a, m): self._pkf(w, ins, a, m, lambda x, y, z: np.maximum(np.maximum(x, y), z), 3)
+
     def i_v_pk_ashrrev_i16(self, w, ins, a, m):
         def sar(s, x):
             sx = np.where(x & U32(0x8000), x | U32(0xFFFF0000), x).view(np.int32)

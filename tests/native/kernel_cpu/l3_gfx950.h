@@ -11,6 +11,8 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <cmath>
+#include <cstdlib>
 
 namespace {
 
@@ -62,12 +64,6 @@ inline bool wave_any(bool mine) {
     return any != 0;
 }
 
-/* v_pk_mad_i16: a * b + c in both 16-bit halves, modulo 2^16 */
-inline uint32_t pk_mad_i16(uint32_t a, uint32_t b, uint32_t c) {
-    const uint32_t lo = ((a & 0xFFFFu) * (b & 0xFFFFu) + (c & 0xFFFFu)) & 0xFFFFu;
-    const uint32_t hi = ((a >> 16) * (b >> 16) + (c >> 16)) & 0xFFFFu;
-    return lo | (hi << 16);
-}
 /* v_pk_lshrrev_b16 with op_sel_hi [0,1]: both halves of v shifted right by the low four
  * bits of the low half of `by` */
 inline uint32_t pk_lshr_b16_by_low(uint32_t by, uint32_t v) {
@@ -80,6 +76,60 @@ inline uint32_t pk_mad_u16_by_low(uint32_t a, uint32_t b, uint32_t c) {
     const uint32_t lo = ((a & 0xFFFFu) * m + (c & 0xFFFFu)) & 0xFFFFu;
     const uint32_t hi = ((a >> 16) * m + (c >> 16)) & 0xFFFFu;
     return lo | (hi << 16);
+}
+/* both halves: the low half of v shifted right by the halves of `by` */
+inline uint32_t low_b16_lshr_twice(uint32_t by, uint32_t v) {
+    return ((v & 0xFFFFu) >> (by & 15u)) | (((v & 0xFFFFu) >> (by >> 16 & 15u)) << 16);
+}
+/* packed 16-bit floats: worked out in double, where every step below is exact, and rounded once
+ * (to nearest, ties to even) */
+inline double l3cpu_half_value(uint32_t h) {
+    const int e = (int)((h >> 10) & 31u), m = (int)(h & 0x3FFu);
+    if (e == 31) std::abort();                              /* infinities and NaN do not occur */
+    const double v = e ? std::ldexp(1024 + m, e - 25) : std::ldexp(m, -24);
+    return h & 0x8000u ? -v : v;
+}
+inline uint32_t l3cpu_half_bits(double v) {
+    const uint32_t sign = std::signbit(v) ? 0x8000u : 0u;
+    const double a = std::fabs(v);
+    int e = a == 0 ? -14 : std::ilogb(a);
+    if (e < -14) e = -14;
+    uint32_t m = (uint32_t)std::nearbyint(std::ldexp(a, 10 - e));   /* 1024 .. 2048, or a subnormal */
+    if (e > 15) std::abort();
+    return sign | (m < 1024 ? m : ((uint32_t)(e + 14) << 10) + m);
+}
+template <class F>
+inline uint32_t l3cpu_pk_f16(uint32_t a, uint32_t b, uint32_t c, F f) {
+    uint32_t out = 0;
+    for (int s = 0; s < 32; s += 16)
+        out |= l3cpu_half_bits(f(l3cpu_half_value(a >> s & 0xFFFFu), l3cpu_half_value(b >> s & 0xFFFFu),
+                                 l3cpu_half_value(c >> s & 0xFFFFu))) << s;
+    return out;
+}
+inline uint32_t pk_min3_f16(uint32_t a, uint32_t b, uint32_t c) {
+    return l3cpu_pk_f16(a, b, c, [](double x, double y, double z) { return std::fmin(std::fmin(x, y), z); });
+}
+inline uint32_t pk_max3_f16(uint32_t a, uint32_t b, uint32_t c) {
+    return l3cpu_pk_f16(a, b, c, [](double x, double y, double z) { return std::fmax(std::fmax(x, y), z); });
+}
+inline uint32_t pk_add_f16(uint32_t a, uint32_t b) {
+    return l3cpu_pk_f16(a, b, 0, [](double x, double y, double) { return x + y; });
+}
+inline uint32_t pk_sub_f16(uint32_t a, uint32_t b) {
+    return l3cpu_pk_f16(a, b, 0, [](double x, double y, double) { return x - y; });
+}
+inline uint32_t pk_fma_f16(uint32_t a, uint32_t b, uint32_t c) {
+    return l3cpu_pk_f16(a, b, c, [](double x, double y, double z) { return x * y + z; });
+}
+inline uint32_t pk_fnma_f16(uint32_t a, uint32_t b, uint32_t c) {
+    return l3cpu_pk_f16(a, b, c, [](double x, double y, double z) { return z - x * y; });
+}
+inline uint32_t pk_twice_exceeds_f16(uint32_t a, uint32_t b) {
+    return l3cpu_pk_f16(a, b, 0, [](double x, double y, double) { return std::fmin(std::fmax(2 * x - y, 0.0), 1.0); });
+}
+inline uint32_t max3_u32(uint32_t a, uint32_t b, uint32_t c) {
+    const uint32_t ab = a > b ? a : b;
+    return ab > c ? ab : c;
 }
 
 /* v_bfe_u32: offset and width taken modulo 32 */
