@@ -137,6 +137,21 @@ def test_rows_of_every_width(l3, ctx):
         check(l3, ctx, [img], patch=patch)
 
 
+@pytest.mark.parametrize("patch", [32, 64, 128])
+def test_first_row_of_every_width(l3, ctx, patch):
+    """The first record of a stream is followed by deltas of 0 to 8 bits (the words that the lanes
+    put into the ring begin up to 4 bits ahead of the stream), behind it one row or enough rows
+    of the other widths that the ring is used again."""
+    rng = np.random.default_rng(patch)
+    images = []
+    for width in range(9):
+        for h in (1, 70):
+            img = rng.integers(0, 256, size=(h, 2 * patch + 5, 3)).astype(np.uint8)
+            img[0] = 90 + rng.integers(0, 1 << width, size=img[0].shape) % 166 if width < 8 else img[0]
+            images.append(img)
+    check(l3, ctx, images, patch=patch)
+
+
 def test_both_routes_in_one_call(l3, ctx):
     images = [synth.cosine_field(2300 + k, 260 + 3 * k, 140 + k) for k in range(6)]
     check(l3, ctx, images, patch=[128, 7, 32, 100, 64, 33])
