@@ -693,7 +693,24 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
     if (wmax > 8) flags |= L3_STATUS_BAD_WIDTH;
     /* bitpos is one (non-existent) row past the end: step back over it */
     if (bitpos - 12 - pw * w > endbit) flags |= L3_STATUS_OVERRUN;
-    if (flags && active && status) atomicOr(&status[d.status_index], flags);
+    if (!active) flags = 0;
+    if (d.units == 1) {
+        /* An image that is one workgroup's (up to 8, 4 or 2 patches) has no other writer of its
+         * status word: it is stored whole, and a call with only such images needs no kernel
+         * ahead of this one that clears them (one of 64x64: 11.7 -> 9.7 us a call).  The waves' words meet
+         * in their own rings, which nothing reads any more. */
+        if (!status) return;
+        uint32_t word = 0;
+#pragma unroll
+        for (uint32_t bit = L3_STATUS_BAD_WIDTH; bit <= L3_STATUS_BAD_OFFSET; bit <<= 1)
+            word |= wave_any((flags & bit) != 0) ? bit : 0u;
+        wave_lds_fence();
+        if (lane == 0) rings[c][0][0] = word;
+        __syncthreads();
+        if (threadIdx.x == 0) status[d.status_index] = word | rings[1][0][0] | rings[2][0][0];
+    } else if (flags && status) {
+        atomicOr(&status[d.status_index], flags);
+    }
 }
 
 /* How old a workgroup of the launch's last round is among the workgroups of its CU, 0 (oldest)
@@ -1013,7 +1030,8 @@ l3_status run_batch(l3_ctx* ctx, const l3_item* items, const l3_crop* crops, int
         hipLaunchKernelGGL(l3_prepare_kernel, dim3((threads + 255) / 256), dim3(256), 0, stream,
                            reinterpret_cast<const uint64_t*>(ctx->h_stage[slot]),
                            reinterpret_cast<uint64_t*>(d_descs), words, d_status, (uint32_t)n);
-    } else if (d_status) {
+    } else if (d_status && (max_units[0] > 1 || max_units[1] > 1 || max_units[2] > 1)) {
+        /* the words of images of one workgroup are stored whole by it */
         hipLaunchKernelGGL(l3_fill_u32_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, d_status,
                            (uint32_t)n, 0u);
     }

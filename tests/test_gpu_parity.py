@@ -286,6 +286,35 @@ def test_damaged_streams_are_flagged_and_contained(l3, ctx):
     assert not diff.any()
 
 
+@pytest.mark.parametrize("patch", [32, 64, 128])
+@pytest.mark.parametrize("layout", ["hwc", "chw"])
+@pytest.mark.parametrize("with_larger", [False, True])
+def test_status_words_of_images_of_one_workgroup(l3, ctx, patch, layout, with_larger):
+    """An image of up to 256 / N patches is one workgroup's, which stores the status word whole
+    (the words start out as 0x55 here); in one call with larger ones, and on its own, where
+    nothing clears the words first.  Flags of every channel arrive, from any lane group."""
+    at_most = 256 // patch
+    sizes = [(5, 3), (patch, patch), (at_most * patch, 7), (at_most * patch, patch)] * 3
+    images = [synth.cosine_field(400 + k, w, h) for k, (w, h) in enumerate(sizes)]
+    if with_larger:
+        images.insert(5, synth.cosine_field(450, 3 * at_most * patch, 2 * patch))
+    files = [bytearray(oracle.encode(im, patch)) for im in images]
+    damaged = {}
+    for k, channel in ((3, 0), (len(files) - 5, 1), (len(files) - 1, 2)):   # full rows of patches
+        count = at_most
+        entry = 13 + 4 * (channel * count + count - 1)                     # that channel's last patch
+        start = 13 + 12 * count + int.from_bytes(files[k][entry:entry + 4], "little")
+        files[k][start] = (files[k][start] & 0xF0) | 0x0D                  # width 13 in its first record
+        damaged[k] = 1
+    got, status = gpu_decode(l3, ctx, [bytes(f) for f in files], layout, pad_cols=3)
+    for k, im in enumerate(images):
+        if k in damaged:
+            assert status[k] & 1, (k, im.shape, status)
+        else:
+            assert status[k] == 0, (k, im.shape, status)
+            assert np.array_equal(got[k], im), (k, im.shape)
+
+
 def test_host_errors_enqueue_nothing(l3, ctx):
     im = synth.cosine_field(71, 100, 80)
     f = oracle.encode(im, 16)                                  # N = 16: not a GPU patch size
