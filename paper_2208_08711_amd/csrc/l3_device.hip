@@ -173,13 +173,6 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
      * N = 128 and slower for N = 64 and 32 (three times as many store instructions for
      * the same bytes), so only N = 128 takes it. */
     constexpr bool DIRECT = MODE == L3_MODE_CHW && PPL == 4 && N == 128;
-    /* Where the write-out behind that barrier comes: at once, or behind the ring top-up, whose
-     * wait for the next chunk then finds the stores a whole period old instead of two rows (loads
-     * and stores share one counter); the parked rows stay until the next barrier.  256 windows
-     * of 224x224 at N = 32: 32.7 us a call at once, 31.6 behind.  Elsewhere at once: at N = 128,
-     * 16 windows of 768x768 53.9 against 56.1, 4 images 33.4 against 34.5, 32 images 83.2
-     * against 82.3; chosen by the size of the launch, the branch costs the small ones 4 %. */
-    constexpr bool FLUSH_LATE = MODE == L3_MODE_TENSOR && N == 32;
     constexpr int PARKS = LATE_BARRIER ? 3 : 2;
     __shared__ __attribute__((aligned(8))) uint32_t parked[PARKS][P][3][QW]; /* [buffer][row of period][channel][word] */
     __shared__ uint16_t s_lut[MODE == L3_MODE_TENSOR ? 768 : 2];
@@ -627,7 +620,7 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
         if (!DIRECT && !LATE_BARRIER && r > 0) {
             /* all three channels of the previous period are parked: write them out */
             __syncthreads();
-            if (!FLUSH_LATE) flush(prev_buf, r - P, P);
+            flush(prev_buf, r - P, P);
         }
         /* interleaved mode: this lane's 12 NW bytes of the row, channel c first at byte c;
          * planar modes: this lane's NW words of channel c */
@@ -685,11 +678,8 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
                 }
                 wave_lds_fence();
             }
-            if (FLUSH_LATE && r > 0) flush(prev_buf, r - P, P);
             wmax = max(wmax, w);
             do_row(park + 2 * 3 * QW, y0 + r + 2);
-        } else if (FLUSH_LATE && r > 0) {
-            flush(prev_buf, r - P, P);
         }
         prev_buf = buf;
         buf = buf == PARKS - 1 ? 0u : buf + 1u;

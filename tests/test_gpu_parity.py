@@ -413,27 +413,6 @@ def test_two_contexts_two_streams_and_one_context_on_alternating_streams(l3, ctx
         other.close()
 
 
-@pytest.mark.parametrize("patch", [32, 64, 128])
-@pytest.mark.parametrize("rows", [1, 2, 3, 4, 5, 6, 31, 32, 33])
-def test_fused_windows_of_few_rows(l3, ctx, patch, rows):
-    """The write-out of a period comes in different places by mode and patch size; windows that
-    end with the first, second and third row of a period, of one period or of many."""
-    images = [synth.cosine_field(700 + k, 80 + 9 * k, rows + k) for k in range(3)]
-    files = [oracle.encode(im, patch) for im in images]
-    infos = [l3.peek_header(f) for f in files]
-    dfiles, keep = upload_files(files)
-    crops = [(k, k // 2, k & 1) for k in range(3)]
-    out = torch.full((3, 3, rows, 70), -1, dtype=torch.int16, device="cuda")
-    status = torch.full((3,), 0x55, dtype=torch.int32, device="cuda")
-    l3.decode_crop_normalize_batch(ctx, dfiles, infos, crops, 70, rows, synth.IMAGENET_MEAN, synth.IMAGENET_STD, out,
-                                   dtype=0, status=status)
-    torch.cuda.synchronize()
-    assert (status.cpu().numpy() == 0).all()
-    for k, (im, (x0, y0, flip)) in enumerate(zip(images, crops)):
-        want = oracle.crop_normalize(im, x0, y0, flip, 70, rows, synth.IMAGENET_MEAN, synth.IMAGENET_STD, 0)
-        assert np.array_equal(out[k].cpu().numpy().view(np.uint16), want), (k, rows)
-
-
 # ---------------------------------------------------------------------------
 # fused crop + flip + normalise (configs[4])
 
