@@ -6,6 +6,7 @@ CPU fallback: if libl3.so is missing, every call raises.
 """
 import array
 import ctypes
+import operator
 import os
 import sys
 
@@ -324,12 +325,17 @@ def encode_batch(ctx, images, files, file_len, patch=0, status=None, stream=None
     given); files: list of uint8 device tensors that receive the L3 files; file_len: int64 (or
     uint64) device tensor of len(images) words; patch: one N for all or a list."""
     n = len(images)
-    patches = patch if isinstance(patch, (list, tuple)) else (patch,) * n
+    # integers of any kind (numpy's, a tensor's elements) as Python's own, which the masks below take
+    if isinstance(patch, (list, tuple)):
+        patches = [operator.index(patch[i]) for i in range(n)]
+    else:
+        patches = (operator.index(patch),) * n if n else ()
+    strides = None if row_strides is None else [operator.index(row_strides[i]) for i in range(n)]
     words = array.array("Q")        # the l3_encode_item array, see _EncodeItem: 6 words of 8 bytes each
     for i in range(n):
         shape, out = images[i].shape, files[i]
         h, w = int(shape[0]), int(shape[1])
-        stride = 3 * w if row_strides is None else row_strides[i]
+        stride = 3 * w if strides is None else strides[i]
         words.extend((images[i].data_ptr(), stride & _MASK64,
                       (w & _MASK32) | (h & _MASK32) << 32, patches[i] & 0xFF, out.data_ptr(), out.numel()))
     arr = (_EncodeItem * n).from_buffer(words) if n else (_EncodeItem * 1)()

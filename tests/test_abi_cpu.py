@@ -159,6 +159,58 @@ def test_context_needs_a_gpu_and_says_so():
     assert e.value.code == 7
 
 
+class _Buffer:
+    """What the binding needs of a tensor: shape, address and size."""
+
+    def __init__(self, shape, address, size=1):
+        self.shape, self._address, self._size = shape, address, size
+
+    def data_ptr(self):
+        return self._address
+
+    def numel(self):
+        return self._size
+
+
+@pytest.mark.parametrize("kind", ["list", "numpy array", "list of numpy scalars", "tensor"])
+def test_encode_batch_hands_over_strides_and_patch_sizes_of_every_integer_kind(monkeypatch, kind):
+    """row_strides and patch as Python integers, numpy integers or a tensor arrive in the C array
+    unchanged (modulo their field's width), a fraction is refused."""
+    import torch
+    from paper_2208_08711_amd import binding
+    seen = []
+
+    class Library:
+        def l3_encode_batch(self, ctx, items, n, *rest):
+            seen.extend((it.d_rgb, it.row_stride, it.width, it.height, it.patch, it.d_file, it.file_cap)
+                        for it in items[:n])
+            return 0
+
+    class Context:
+        handle = None
+
+    monkeypatch.setattr(binding, "_load", lambda: Library())
+    monkeypatch.setattr(binding, "_stream_ptr", lambda stream: None)
+    convert = {"list": list, "numpy array": np.array, "tensor": torch.tensor,
+               "list of numpy scalars": lambda v: [np.int64(x) for x in v]}[kind]
+    strides = [20, 1 << 40, -1]
+    patches = {"list": [32, 64, 128], "list of numpy scalars": [np.uint8(32), np.int64(64), np.int16(128)],
+               "numpy array": np.int64(32), "tensor": torch.tensor(32)}[kind]
+    images = [_Buffer((4 + k, 6, 3), 4096 * (k + 1)) for k in range(3)]
+    files = [_Buffer((100,), 1 << 40, 100 + k) for k in range(3)]
+    lens = _Buffer((3,), 8)
+    binding.encode_batch(Context(), images, files, lens, patch=patches, row_strides=convert(strides))
+    sizes = [32, 64, 128] if isinstance(patches, list) else [32, 32, 32]
+    assert seen == [(4096 * (k + 1), strides[k] % (1 << 64), 6, 4 + k, sizes[k], 1 << 40, 100 + k) for k in range(3)]
+    del seen[:]
+    binding.encode_batch(Context(), images, files, lens)
+    assert [s[1] for s in seen] == [18, 18, 18] and [s[4] for s in seen] == [0, 0, 0]
+    for refused in ({"patch": 32.0}, {"patch": None}, {"row_strides": [18.0, 18, 18]}, {"row_strides": [None, 18, 18]}):
+        with pytest.raises(TypeError):
+            binding.encode_batch(Context(), images, files, lens, **refused)
+    binding.encode_batch(Context(), [], [], lens, patch=[], row_strides=[])
+
+
 def test_header_is_plain_c99(tmp_path):
     """include/l3.h and include/l3_ablation.h compile as C99 with every warning on (no GPU, no
     HIP header needed): the ABI has no C++ in it."""
