@@ -18,8 +18,8 @@
  *            patch's byte size goes to a table;
  *   layout   one workgroup per image: exclusive prefix sum of the patch sizes ->
  *            header, offset arrays, file length (this is where a scan belongs: the
- *            addends are all known); only for images of very many patches, otherwise the
- *            next kernel does this too;
+ *            addends are all known); only in calls with very many patches or with an image on
+ *            the plain route, otherwise the next kernel does this too;
  *   compact  copies every slot to its place in the file.
  * Any other patch size up to 128 takes the plain route: measure (one wave per patch
  * and channel walks the rows for the sizes), layout, pack (walks them again and
@@ -608,16 +608,39 @@ struct CompactGeom {
     static_assert(SLOTS <= 16, "offsets inside a workgroup are a scan over one 16-lane row");
 };
 
-/* Images of at most this many patches (all channels) are laid out by the compaction itself. */
+constexpr uint32_t compact_slots(uint32_t n) {
+    return n == 32 ? CompactGeom<32>::SLOTS : (n == 64 ? CompactGeom<64>::SLOTS : CompactGeom<128>::SLOTS);
+}
+
+/* Which calls lay their files out in the compaction itself (OWN_LAYOUT below).  A workgroup then reads
+ * all patch sizes of its image, so what is read grows with the square of the patches and with
+ * the number of images; the layout kernel's time grows with the largest image only (2.5 us, and
+ * 3.5 us for every 1000 of its patches).  The reads come out of the L2 at 10 TB/s at N = 128, 13 at
+ * N = 64 and, where a workgroup copies 16 slots behind them, 40 at N = 32.  So they are counted 4, 3
+ * and 1 times by patch size, and taken where ten million of them a microsecond are done sooner
+ * than the layout kernel.  A call with the layout kernel against one without, on one card:
+ *   N = 128   32 images of 384 patches (all channels) 202.5 / 200.5 us, 1 of 4095 92.6 / 77.6, 2 of 4095
+ *             153.6 / 143.8, 4 of 2700 196 / 197, 16 of 1587 407.6 / 410.5, 16 of 4095 977 / 1074
+ *   N = 64    8 of 4095 156.1 / 146.2, 32 of 1587 223.1 / 223.7, 16 of 4095 287.8 / 291.7, 64 1004 / 1076
+ *   N = 32    256 of 540 180.7 / 178.1, 64 of 4095 307.4 / 304.2, 128 555.7 / 555.7, 256 1057 / 1070
+ * and on another, images of whole patches: N = 128, 3 of 4095 188.7 / 197.0; N = 64, 16 258.4 / 262.4; N = 32, 165
+ * 620.4 / 631.6.
+ * Images of more than kOwnLayoutPatches patches keep the layout kernel (one of 12288 32-pixel patches
+ * would take 36.5 instead of 82.6 us without, so that bound could lie higher). */
 constexpr uint32_t kOwnLayoutPatches = 4096;
+constexpr uint64_t own_layout_reads(uint32_t n, uint64_t patches) {      /* counted as above */
+    return (n == 32 ? 1 : n == 64 ? 3 : 4) * patches * ((patches + compact_slots(n) - 1) / compact_slots(n));
+}
+constexpr bool own_layout_pays(uint32_t max_patches, uint64_t reads) {
+    return max_patches <= kOwnLayoutPatches && reads <= 36000ull * (max_patches + 700);
+}
 
 /* Copies the slots of the strip route to their places in the file.
  * OWN_LAYOUT: every workgroup works out where its slots go: it adds up all patch sizes of the
  * image and those ahead of its own (a few loads per thread, out of the L2), instead of waiting
  * for a kernel of one workgroup per image that does so once for all (5 to 9 us, of which a call
- * with one image has nothing to hide behind).  The work of that grows with the square of
- * the number of patches: beyond kOwnLayoutPatches the layout kernel runs first and the
- * offsets are read from the header. */
+ * with one image has nothing to hide behind).  Otherwise the layout kernel runs first and the
+ * offsets are read from the header.  The rule is own_layout_pays. */
 template <int N, bool OWN_LAYOUT>
 __device__ __forceinline__ void compact_block(const L3EncodeDesc& d, const uint32_t* __restrict__ sizes,
                                               const uint8_t* __restrict__ slots,
@@ -857,6 +880,7 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
     uint32_t max_patches = 0, max_n = 1;
     uint32_t strip_units[3] = {0, 0, 0};   /* largest grid of the strip route per N = 32, 64, 128 */
     uint32_t strip_slots[3] = {0, 0, 0};   /* most slots of an image, likewise */
+    uint64_t layout_reads = 0;             /* see own_layout_pays */
     bool any_plain = false;
     for (int i = 0; i < n; ++i) {
         const l3_encode_item& it = items[i];
@@ -877,6 +901,8 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
             const uint64_t units = (uint64_t)((tiles_x + tpw - 1) / tpw) * ((it.height + np - 1) / np);
             if (units > strip_units[cls]) strip_units[cls] = (uint32_t)units;
             if (3 * p > strip_slots[cls]) strip_slots[cls] = (uint32_t)(3 * p);
+            if (3 * p <= kOwnLayoutPatches)
+                layout_reads += own_layout_reads(np, 3 * p);
             slot_bytes += (size_t)(3 * p) * strip_slot_bytes(np);
         } else {
             any_plain = true;
@@ -902,7 +928,7 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
         hipStreamWaitEvent(stream, st->done, 0) != hipSuccess)
         return L3_ERR_DEVICE;
     const bool by_args = n <= kArgDescs && !any_plain;
-    const bool own_layout = max_patches <= kOwnLayoutPatches && !any_plain;
+    const bool own_layout = own_layout_pays(max_patches, layout_reads) && !any_plain;
     constexpr int kStage = 4;
     int stage = 0;
     if (!by_args) {

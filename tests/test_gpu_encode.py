@@ -288,3 +288,25 @@ def test_files_are_laid_out_alike_on_both_sides_of_the_limit(l3, ctx, tiles):
     header = 13 + 12 * tiles[0] * tiles[1]
     assert (buf.cpu().numpy()[header:] == 0xAB).all()              # no stream is packed
     assert buf.cpu().numpy()[:header].tobytes() == want[:header]
+
+
+@pytest.mark.parametrize("patch,at_most", [(128, 2), (64, 13), (32, 164)])
+def test_files_are_laid_out_alike_on_both_sides_of_the_limit_on_a_call(l3, ctx, patch, at_most):
+    """A call's images of 4095 patches each are laid out by the copying kernel up to `at_most` of
+    them (4 x 4095 x 4095 x 2, 3 x 4095 x 1024 x 13 and 4095 x 256 x 164 counted reads, of 172.6
+    million) and by the kernel ahead of it from one more on."""
+    w, h = 35 * patch - 3, 39 * patch - 5
+    im = np.random.default_rng(patch).integers(0, 24, size=(h, w, 3)).astype(np.uint8)
+    want = oracle.encode(im, patch)
+    expected = torch.from_numpy(np.frombuffer(want, dtype=np.uint8).copy()).cuda()
+    dev = torch.from_numpy(im).cuda()
+    room = torch.empty((at_most + 1, (len(want) + 15) // 16 * 16 + 16), dtype=torch.uint8, device="cuda")
+    for n in (at_most, at_most + 1):
+        room.fill_(0xAB)
+        lens = torch.zeros(n, dtype=torch.int64, device="cuda")
+        status = torch.full((n,), 7, dtype=torch.int32, device="cuda")
+        l3.encode_batch(ctx, [dev] * n, [room[k, :len(want)] for k in range(n)], lens, patch=patch, status=status)
+        torch.cuda.synchronize()
+        assert (lens == len(want)).all() and (status == 0).all()
+        assert (room[:n, :len(want)] == expected).all(), n
+        assert (room[:n, len(want):] == 0xAB).all() and (room[n:] == 0xAB).all(), n
