@@ -562,13 +562,21 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
             global_u8* row = reinterpret_cast<global_u8*>(
                 (uintptr_t)(out_base + (uint64_t)c * out_plane_stride + (uint64_t)y * out_row_stride));
             L3_KEEP_VGPR(word_off[0]);
-            if (wave_whole || word_valid[0] == 4) {
+            /* two separate arms (not "whole wave or whole word"): with those joined a wave with a
+             * cut-off word jumps twice out of line in every row, and calls of such waves were
+             * slower than without the scalar branch (300 images of 130x97 41.2 us, 40.3 without the
+             * branch, 36.5 so; 200 of 258x128 43.8, 42.7, 40.2; whole waves are the same) */
+            if (wave_whole) {
                 __builtin_nontemporal_store(word[0], reinterpret_cast<global_u32_any*>(row + word_off[0]));
-            } else if (word_valid[0]) {
-                global_u8* b = row + word_off[0];
+            } else {
+                if (word_valid[0] == 4)
+                    __builtin_nontemporal_store(word[0], reinterpret_cast<global_u32_any*>(row + word_off[0]));
+                if (word_valid[0] - 1 < 3) {
+                    global_u8* b = row + word_off[0];
 #pragma unroll
-                for (int k = 0; k < 3; ++k)
-                    if ((uint32_t)k < word_valid[0]) b[k] = (uint8_t)(word[0] >> (8 * k));
+                    for (int k = 0; k < 3; ++k)
+                        if ((uint32_t)k < word_valid[0]) b[k] = (uint8_t)(word[0] >> (8 * k));
+                }
             }
         } else {
 #pragma unroll
