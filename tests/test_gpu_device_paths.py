@@ -124,6 +124,76 @@ def test_damaged_streams_fused_path(l3, ctx, patch):
         assert np.array_equal(got[i], want)
 
 
+@pytest.mark.parametrize("patch", [32, 64, 128])
+@pytest.mark.parametrize("mode", ["hwc", "chw", "fused"])
+@pytest.mark.parametrize("with_larger", [False, True])
+@pytest.mark.parametrize("repeat", [1, 8])
+def test_every_flag_of_images_of_one_workgroup(l3, ctx, patch, mode, with_larger, repeat):
+    """Images that are one workgroup's (one row of at most 256 / N patches; in the fused call, of
+    the window): it stores their status word whole, over what was there, with the flags of all
+    three channels' waves.  Each flag from another channel, two of them together, and all; next
+    to clean images; on their own (nothing clears the words then) and beside an image of
+    several workgroups; up to 32 and more descriptors in the kernel arguments."""
+    count = 256 // patch                                       # patches per channel
+    w, h = count * patch, patch
+    im = [synth.cosine_field(8500 + k, w, h) for k in range(6)]
+    whole = [oracle.encode(x, patch) for x in im]
+    header = 13 + 12 * count
+
+    def entry(k, channel, tile):                               # place and value of an offset
+        at = 13 + 4 * (channel * count + tile)
+        return at, int.from_bytes(whole[k][at:at + 4], "little")
+
+    def wide(k, channel):                                      # width 12 in the first record of the last patch
+        start = header + entry(k, channel, count - 1)[1]
+        bad[k][start] = (bad[k][start] & 0xF0) | 0x0C
+
+    def lost(k, channel, tile):                                # offset beyond the data; the stream is empty then
+        at = entry(k, channel, tile)[0]
+        bad[k][at:at + 4] = (0xFFFFFFF0).to_bytes(4, "little")
+
+    bad = [bytearray(f) for f in whole]
+    wide(1, 1)
+    bad[2] = bad[2][:-2]                                       # channel 2: every record there, the last row cut short
+    lost(3, 0, 0)
+    wide(4, 2)
+    lost(4, 0, count - 1)
+    # image: (flags that are set, flags that may be).  A patch with a wrong width may also run
+    # past its end, one without a stream does and decodes what it finds.
+    expected = {0: (0, 0), 1: (1, 3), 2: (2, 2), 3: (6, 7), 4: (7, 7), 5: (0, 0)}
+    infos = [l3.peek_header(f) for f in whole]
+    infos[2] = l3.peek_header(bytes(bad[2]))
+    order = list(range(6)) * repeat
+    files, infos = [bytes(bad[k]) for k in order], [infos[k] for k in order]
+    crop_w, crop_h = w - 3, h - 2
+    crops = [(k % 4, 2, k & 1) for k in order]                 # down to the last row of the patches
+    if with_larger:
+        big = synth.cosine_field(8600, 2 * w, h)
+        files.insert(3, oracle.encode(big, patch))
+        infos.insert(3, l3.peek_header(files[3]))
+        crops.insert(3, (patch // 2, 0, 0))                    # touches one patch more than a workgroup has
+        order.insert(3, -1)
+    dfiles, keep = upload_files(files)
+    if mode == "fused":
+        n = len(files)
+        status = torch.full((n,), 0x5A50, dtype=torch.int32, device="cuda")
+        out = torch.full((n, 3, crop_h, crop_w), -1, dtype=torch.int16, device="cuda")
+        l3.decode_crop_normalize_batch(ctx, dfiles, infos, crops, crop_w, crop_h, synth.IMAGENET_MEAN,
+                                       synth.IMAGENET_STD, out, status=status)
+        torch.cuda.synchronize()
+        status, got = status.cpu().numpy(), out.cpu().numpy().view(np.uint16)
+    else:
+        got, status = _decode(l3, ctx, dfiles, infos, mode)
+    for i, k in enumerate(order):
+        must, may = expected.get(k, (0, 0))
+        assert status[i] & must == must and status[i] & ~may == 0, (i, k, status)
+        if may == 0:
+            want = big if k < 0 else im[k]
+            if mode == "fused":
+                want = oracle.crop_normalize(want, *crops[i], crop_w, crop_h, synth.IMAGENET_MEAN, synth.IMAGENET_STD, 0)
+            assert np.array_equal(got[i], want), (i, k)
+
+
 def test_every_neighbour_triple_through_the_kernel(l3, ctx):
     """All 2^24 combinations of (top-left, top, top-right) as the row above an interior pixel.
     Even rows carry the triples, 42 per 128-pixel patch row, centred on interior columns; odd
