@@ -55,8 +55,6 @@ struct L3EncodeDesc {
     uint64_t slots_base;     /* strip route: byte offset of this image's first slot in the workspace */
 };
 
-typedef __attribute__((address_space(1))) uint32_t global_u32_unaligned __attribute__((aligned(1)));
-
 __device__ __forceinline__ int nearest_upper(int tl, int t, int tr) {
     /* distances to TL + TR - T: |TR - T| for TL, |TL - T| for TR, |TL + TR - 2T| for T;
      * ties: TL, then TR, then T */
@@ -180,10 +178,6 @@ struct StripGeom {
 __host__ __device__ constexpr uint32_t strip_slot_bytes(uint32_t n) {
     return n == 32 ? StripGeom<32>::SLOT : n == 64 ? StripGeom<64>::SLOT : StripGeom<128>::SLOT;
 }
-
-typedef __attribute__((address_space(1))) const u32x3_any global_const_u32x3_any;
-typedef __attribute__((address_space(1))) u32x4 global_u32x4;
-typedef u32x4 u32x4_any __attribute__((aligned(1)));
 
 /* max((low half of a) - b, 0) in both 16-bit halves: v_pk_sub_u16 with clamp */
 __device__ __forceinline__ uint32_t pk_sub_u16_sat_from_low(uint32_t a, uint32_t b) {
@@ -310,7 +304,7 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
     uint32_t krow = my_row == 0 ? 0u : 0x80u;                           /* K of that row in the first period */
 
     uint64_t row_stride = d.row_stride;
-    asm volatile("" : "+s"(row_stride));    /* kept in registers, not reloaded every row */
+    L3_KEEP_SGPR(row_stride);               /* kept in registers, not reloaded every row */
     /* The lane's 12 bytes of a row.  A lane at the right edge of the image owns fewer than
      * 4 pixels and must not read past the row: it reads the 12 bytes that END at its last
      * pixel and shifts them down when it takes them (what then sits above the valid bytes is
@@ -326,14 +320,13 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
      * last period) repeat the last one */
     u32x3 ahead[P];
     auto load_rows = [&](const uint8_t* row, uint32_t exist) {
-        typedef __attribute__((address_space(1))) const uint8_t global_const_u8;
 #pragma unroll
         for (int i = 0; i < P; ++i) {
             global_const_u8* base = reinterpret_cast<global_const_u8*>((uintptr_t)(row + min((uint32_t)i, exist - 1) * row_stride));
             if (wide) {
                 uint32_t at = lane_at;
                 L3_KEEP_VGPR(at);      /* stays the load's 32-bit offset */
-                ahead[i] = *reinterpret_cast<global_const_u32x3_any*>(base + at);
+                ahead[i] = load_u32x3(base + at);
             } else {
                 uint32_t b[9];
 #pragma unroll
@@ -355,8 +348,7 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
     };
 
     uint32_t* const ring = ring_words + g * G::RING_WORDS;
-    const uint32_t ring_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)ring;
-    typedef __attribute__((address_space(3))) uint32_t lds_u32;
+    const uint32_t ring_lds = lds_address_of(ring);
     {
         u32x4 zero = {0, 0, 0, 0};
         for (uint32_t i = xl; i < G::RING_WORDS / 4; i += LPT) reinterpret_cast<u32x4*>(ring)[i] = zero;
@@ -372,9 +364,7 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
         const uint32_t w0 = __builtin_amdgcn_ubfe(pos, 5, word_bits);
         const uint32_t lo = value << (pos & 31u);
         const uint32_t hi = (value >> 1) >> (~pos & 31u);
-        lds_u32* cell = reinterpret_cast<lds_u32*>(ring_lds + 4 * w0);
-        __hip_atomic_fetch_or(cell, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-        __hip_atomic_fetch_or(cell + 1, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        lds_or_pair(ring_lds + 4 * w0, lo, hi);
     };
 
     uint32_t rowpos = 0;       /* bit position of the next row record in the patch stream */
@@ -691,14 +681,14 @@ __device__ __forceinline__ void compact_block(const L3EncodeDesc& d, const uint3
         offset = ahead + upto - size;
         need = header + all;
         if (wave == 0 && mine && header <= d.file_cap)
-            *reinterpret_cast<global_u32_unaligned*>((uintptr_t)(table + 4 * (size_t)k)) = offset;
+            *reinterpret_cast<global_u32_any*>((uintptr_t)(table + 4 * (size_t)k)) = offset;
         if (first == 0 && threadIdx.x == 0) write_header(d, need, header, file_len, status);
     } else {
         need = file_len[d.status_index];
     }
     if (need > d.file_cap || need - header > 0xFFFFFFFFull) return;
     if (!OWN_LAYOUT && mine)
-        offset = *reinterpret_cast<const global_u32_unaligned*>((uintptr_t)(table + 4 * (size_t)k));
+        offset = *reinterpret_cast<global_const_u32_any*>((uintptr_t)(table + 4 * (size_t)k));
 
     /* Bound by memory: 32 images of 2048x1024 move 330 MB in 57 us, 256 photographs of 39 million
      * pixels 180 MB in 40 us (the layout kernel and this one took 57 and 54 us before, with one
@@ -706,7 +696,6 @@ __device__ __forceinline__ void compact_block(const L3EncodeDesc& d, const uint3
      * slot read at any alignment instead (64 us with four granules per lane in flight), that
      * many in flight otherwise (60 us), non-temporal stores (a call with 32 images in turn with
      * others 176.5 instead of 171.6 us), non-temporal slot stores in the strip kernel (62 us here). */
-    typedef __attribute__((address_space(1))) u32x4_any global_u32x4_any;
     const uint32_t me = N == 128 ? threadIdx.x : lane;
     const uint8_t* from[G::WAVE_SLOTS];
     uint8_t* to[G::WAVE_SLOTS];
@@ -721,7 +710,7 @@ __device__ __forceinline__ void compact_block(const L3EncodeDesc& d, const uint3
         to[j] = d.file + header + (uint32_t)__builtin_amdgcn_readlane((int)offset, (int)nth);
         whole[j] = bytes / 16;
         tail[j] = bytes & 15u;
-        if (me < whole[j]) v[j] = *reinterpret_cast<const global_const_u32x4*>((uintptr_t)(from[j] + 16 * me));
+        if (me < whole[j]) v[j] = *reinterpret_cast<global_const_u32x4*>((uintptr_t)(from[j] + 16 * me));
         if (me < tail[j]) last[j] = from[j][16 * whole[j] + me];
     }
 #pragma unroll
@@ -730,7 +719,7 @@ __device__ __forceinline__ void compact_block(const L3EncodeDesc& d, const uint3
             *reinterpret_cast<global_u32x4_any*>((uintptr_t)(to[j] + 16 * me)) = v[j];
         for (uint32_t i = me + G::LANES; i < whole[j]; i += G::LANES)
             *reinterpret_cast<global_u32x4_any*>((uintptr_t)(to[j] + 16 * i)) =
-                *reinterpret_cast<const global_const_u32x4*>((uintptr_t)(from[j] + 16 * i));
+                *reinterpret_cast<global_const_u32x4*>((uintptr_t)(from[j] + 16 * i));
         if (me < tail[j]) to[j][16 * whole[j] + me] = last[j];
     }
 }
@@ -788,7 +777,7 @@ __device__ __forceinline__ void layout_block(const L3EncodeDesc& d, const uint32
         }
         const uint64_t offset = carry + scan[threadIdx.x] - mine;
         if (k < total && header_fits && offset <= 0xFFFFFFFFull)
-            *reinterpret_cast<global_u32_unaligned*>((uintptr_t)(d.file + 13 + 4 * (size_t)k)) = (uint32_t)offset;
+            *reinterpret_cast<global_u32_any*>((uintptr_t)(d.file + 13 + 4 * (size_t)k)) = (uint32_t)offset;
         __syncthreads();
         if (threadIdx.x == 255) carry += scan[255];
         __syncthreads();
@@ -818,7 +807,7 @@ __global__ __launch_bounds__(64) void l3_encode_pack_kernel(const L3EncodeDesc* 
     const uint64_t need = file_len[d.status_index];
     if (need > d.file_cap || need - (13 + 12ull * patches) > 0xFFFFFFFFull) return;
 
-    extern __shared__ uint32_t bits[];   /* sized by the host for the largest patch of the launch */
+    L3_DYNAMIC_LDS(uint32_t, bits);      /* sized by the host for the largest patch of the launch */
     const uint32_t bytes = sizes[d.sizes_base + k];
     const uint32_t words = (bytes + 3) / 4 + 1;
     for (uint32_t i = threadIdx.x; i < words; i += 64) bits[i] = 0;
@@ -827,11 +816,11 @@ __global__ __launch_bounds__(64) void l3_encode_pack_kernel(const L3EncodeDesc* 
     (void)walk_patch<true>(d, c, i % d.tiles_x, i / d.tiles_x, bits);
     __syncthreads();
 
-    const uint32_t offset = *reinterpret_cast<const global_u32_unaligned*>((uintptr_t)(d.file + 13 + 4 * (size_t)k));
+    const uint32_t offset = *reinterpret_cast<global_const_u32_any*>((uintptr_t)(d.file + 13 + 4 * (size_t)k));
     uint8_t* dst = d.file + 13 + 12 * (size_t)patches + offset;
     const uint32_t whole = bytes / 4;
     for (uint32_t w = threadIdx.x; w < whole; w += 64)
-        *reinterpret_cast<global_u32_unaligned*>((uintptr_t)(dst + 4 * (size_t)w)) = bits[w];
+        *reinterpret_cast<global_u32_any*>((uintptr_t)(dst + 4 * (size_t)w)) = bits[w];
     const uint32_t tail = bytes - 4 * whole;
     if (threadIdx.x < tail) dst[4 * (size_t)whole + threadIdx.x] = (uint8_t)(bits[whole] >> (8 * threadIdx.x));
 }

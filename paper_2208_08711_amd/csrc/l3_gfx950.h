@@ -1,9 +1,9 @@
 /*
  * gfx950 primitives of the L3 kernels: vector and address-space types, lane shifts, packed
  * 16-bit operations, LDS addressing by 32-bit address, register pinning.  Everything in the
- * decoder that names the target sits here or is an amdgcn builtin; its own logic
- * (l3_kernel_parts.h, l3_device.hip) is written on top of these names.  (A host build of the
- * decode kernels for the sanitizers replaces this file alone: tests/native/kernel_cpu.)
+ * decoder and the encoder that names the target sits here or is an amdgcn builtin; their own
+ * logic (l3_kernel_parts.h, l3_device.hip, l3_encode.hip) is written on top of these names.  (A host
+ * build of the kernels for the sanitizers replaces this file alone: tests/native/kernel_cpu.)
  * Device code only; every translation unit gets its own copy.
  */
 #ifndef L3_GFX950_H
@@ -31,10 +31,18 @@ typedef __attribute__((address_space(1))) const u32_any global_const_u32_any;
 typedef __attribute__((address_space(1))) u32x3_any global_u32x3_any;
 typedef __attribute__((address_space(1))) u32_any global_u32_any;
 typedef __attribute__((address_space(1))) u32x2_any global_u32x2_any;
+typedef __attribute__((address_space(1))) const u32x3_any global_const_u32x3_any;
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+typedef __attribute__((address_space(1))) u32x4 global_u32x4;
+typedef __attribute__((address_space(1))) u32x4_any global_u32x4_any;
+typedef __attribute__((address_space(1))) const uint8_t global_const_u8;
 typedef __attribute__((address_space(1))) uint8_t global_u8;
 typedef __attribute__((address_space(1))) uint16_t global_u16;
 typedef uint16_t u16_any __attribute__((aligned(1)));
 typedef __attribute__((address_space(1))) u16_any global_u16_any;
+
+/* 12 bytes at any alignment, and no more */
+__device__ __forceinline__ u32x3 load_u32x3(global_const_u8* p) { return *reinterpret_cast<global_const_u32x3_any*>(p); }
 
 __device__ __forceinline__ uint32_t dpp_from_lower_lane(uint32_t v) {   /* lane i <- lane i-1, lane 0 <- 0 */
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138 /* wave_shr:1 */, 0xF, 0xF, true);
@@ -137,13 +145,22 @@ __device__ __forceinline__ void lds_write_u32x4(uint32_t where, u32x4 v) {
     *reinterpret_cast<__attribute__((address_space(3))) u32x4*>(where) = v;
 }
 
+/* ORs lo and hi into the two consecutive words at LDS address `where`, each atomically among the wave's lanes */
+__device__ __forceinline__ void lds_or_pair(uint32_t where, uint32_t lo, uint32_t hi) {
+    __attribute__((address_space(3))) uint32_t* cell = reinterpret_cast<__attribute__((address_space(3))) uint32_t*>(where);
+    __hip_atomic_fetch_or(cell, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __hip_atomic_fetch_or(cell + 1, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
+/* LDS of the size that the launch gives */
+#define L3_DYNAMIC_LDS(type, name) extern __shared__ type name[]
+
 /* ---- keeping a value where it is ------------------------------------------ */
 
 /* The value becomes opaque to the optimiser and stays in a vector (scalar) register: used
  * where the compiler would otherwise widen, rematerialise or reload it at a bad place. */
 #define L3_KEEP_VGPR(x) asm volatile("" : "+v"(x))
 #define L3_KEEP_SGPR(x) asm volatile("" : "+s"(x))
-#define L3_OPAQUE_VGPR(x) asm("" : "+v"(x))     /* the same, free to move or vanish with its value */
 
 __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

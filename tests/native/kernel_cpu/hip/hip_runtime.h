@@ -1,8 +1,8 @@
 /*
  * A stand-in for <hip/hip_runtime.h> that runs HIP kernels on host threads, one thread per
- * GPU thread, one workgroup at a time.  It exists so that the decode kernels' own source
- * can be compiled for the host and run under AddressSanitizer, UBSan and ThreadSanitizer
- * (tests/test_kernel_cpu_build.py): "device" memory is host memory, so every access a
+ * GPU thread, one workgroup at a time.  It exists so that the decode and encode kernels' own
+ * source can be compiled for the host and run under AddressSanitizer, UBSan and ThreadSanitizer
+ * (tests/test_kernel_cpu_build.py, tests/test_encoder_cpu_build.py): "device" memory is host memory, so every access a
  * kernel makes outside a buffer is reported, and LDS is ordinary static memory, so every
  * unsynchronised pair of accesses is.  Only what those kernels and their host code use is
  * here.  Test infrastructure; nothing in the library includes it.
@@ -78,8 +78,14 @@ inline const uint32_t* exchange(uint32_t v) {
     return wg->exchange[wave()][p];
 }
 
+/* LDS whose size the launch gives: a heap block of exactly that size */
+inline void*& dynamic_lds() {
+    static void* p = nullptr;
+    return p;
+}
+
 /* Runs `body` once per thread of every workgroup of the grid. */
-inline void launch(dim3 grid, dim3 block, const std::function<void()>& body) {
+inline void launch(dim3 grid, dim3 block, const std::function<void()>& body, size_t lds_bytes = 0) {
     const unsigned threads = block.x * block.y * block.z;
     if (threads % kWave != 0 || threads / kWave > 16 || block.y != 1 || block.z != 1) std::abort();
     grid_dim() = grid;
@@ -92,6 +98,7 @@ inline void launch(dim3 grid, dim3 block, const std::function<void()>& body) {
                 pthread_barrier_init(&wg.all, nullptr, threads);
                 for (unsigned w = 0; w < threads / kWave; ++w) pthread_barrier_init(&wg.wave[w], nullptr, kWave);
                 workgroup() = &wg;
+                dynamic_lds() = lds_bytes ? std::malloc(lds_bytes) : nullptr;
                 std::vector<std::thread> pool;
                 pool.reserve(threads);
                 for (unsigned t = 0; t < threads; ++t)
@@ -105,6 +112,7 @@ inline void launch(dim3 grid, dim3 block, const std::function<void()>& body) {
                 for (unsigned w = 0; w < threads / kWave; ++w) pthread_barrier_destroy(&wg.wave[w]);
                 pthread_barrier_destroy(&wg.all);
                 workgroup() = nullptr;
+                std::free(dynamic_lds());
             }
 }
 
@@ -149,6 +157,19 @@ inline uint32_t __float_as_uint(float f) {
 }
 inline uint32_t min(uint32_t a, uint32_t b) { return a < b ? a : b; }
 inline uint32_t max(uint32_t a, uint32_t b) { return a > b ? a : b; }
+inline int min(int a, int b) { return a < b ? a : b; }
+inline int max(int a, int b) { return a > b ? a : b; }
+/* a lane outside the wave: the lane's own value */
+inline int __shfl(int v, int from) { return (int)l3cpu::exchange((uint32_t)v)[from & 63]; }
+inline int __shfl_xor(int v, int mask) { return (int)l3cpu::exchange((uint32_t)v)[l3cpu::lane() ^ (unsigned)mask]; }
+inline int __shfl_up(int v, unsigned by) {
+    const unsigned l = l3cpu::lane();
+    return (int)l3cpu::exchange((uint32_t)v)[l >= by ? l - by : l];
+}
+inline int __shfl_down(int v, unsigned by) {
+    const unsigned l = l3cpu::lane();
+    return (int)l3cpu::exchange((uint32_t)v)[l + by < 64 ? l + by : l];
+}
 
 /* ---- runtime -------------------------------------------------------------- */
 
@@ -182,6 +203,12 @@ inline hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
 inline hipError_t hipEventDestroy(hipEvent_t e) { std::free(e); return hipSuccess; }
 inline hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }   /* launches are synchronous */
 inline hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+enum hipMemcpyKind { hipMemcpyHostToDevice = 1 };
+inline hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind, hipStream_t) {
+    std::memcpy(dst, src, n);
+    return hipSuccess;
+}
 inline hipError_t hipGetLastError() { return hipSuccess; }
 #define HIP_SYMBOL(x) l3cpu::symbol(&(x), sizeof(x))
 inline hipError_t hipGetSymbolAddress(void** p, const void* symbol) {
@@ -198,6 +225,6 @@ inline hipError_t hipLaunchKernel(const void* kernel, dim3 grid, dim3 block, voi
     return hipSuccess;
 }
 #define hipLaunchKernelGGL(kernel, grid, block, shared_bytes, stream, ...) \
-    l3cpu::launch((grid), (block), [&] { kernel(__VA_ARGS__); })
+    l3cpu::launch((grid), (block), [&] { kernel(__VA_ARGS__); }, (shared_bytes))
 
 #endif

@@ -1,9 +1,9 @@
 /*
  * Host twin of paper_2208_08711_amd/csrc/l3_gfx950.h: the same names, written for host
- * threads (hip/hip_runtime.h beside this file), so that the decode kernels' own logic runs
- * under the sanitizers.  Each primitive states what the GPU instruction does; the kernels'
- * parity with the oracle on the CPU (tests/test_kernel_cpu_build.py) and on the GPU checks
- * that the two agree.  Included ahead of the kernel source, whose own include of the
+ * threads (hip/hip_runtime.h beside this file), so that the decode and encode kernels' own logic
+ * runs under the sanitizers.  Each primitive states what the GPU instruction does; the kernels'
+ * parity with the oracle on the CPU (tests/test_kernel_cpu_build.py,
+ * tests/test_encoder_cpu_build.py) and on the GPU checks that the two agree.  Included ahead of the kernel source, whose own include of the
  * product header then finds the guard set.  Test infrastructure.
  */
 #ifndef L3_GFX950_H
@@ -32,6 +32,10 @@ typedef const u32_any global_const_u32_any;
 typedef u32x3_any global_u32x3_any;
 typedef u32_any global_u32_any;
 typedef u32x2_any global_u32x2_any;
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+typedef u32x4 global_u32x4;
+typedef u32x4_any global_u32x4_any;
+typedef const uint8_t global_const_u8;
 typedef uint8_t global_u8;
 typedef uint16_t global_u16;
 typedef uint16_t u16_any __attribute__((aligned(1)));
@@ -44,6 +48,12 @@ inline void l3cpu_store(V v, void* p) { std::memcpy(p, &v, sizeof v); }   /* at 
 inline void l3cpu_store(u32x3 v, void* p) { std::memcpy(p, &v, 12); }
 #define __builtin_nontemporal_store(v, p) l3cpu_store((v), (p))
 
+inline u32x3 load_u32x3(const uint8_t* p) {
+    u32x3 v;
+    std::memcpy(&v, p, 12);
+    return v;
+}
+
 /* wave_shr:1 / wave_shl:1 with bound_ctrl: the neighbour lane's value, 0 at the wave's end */
 inline uint32_t dpp_from_lower_lane(uint32_t v) {
     const uint32_t* all = l3cpu::exchange(v);
@@ -54,6 +64,35 @@ inline uint32_t dpp_from_upper_lane(uint32_t v) {
     const uint32_t* all = l3cpu::exchange(v);
     const unsigned l = l3cpu::lane();
     return l < 63 ? all[l + 1] : 0u;
+}
+/* v_mov_b32_dpp: the lane's value from the lane that `ctrl` names (the controls used here); a lane
+ * of a 16-lane row or a 4-lane bank that its mask leaves out keeps `old` */
+inline int l3cpu_update_dpp(int old, int src, int ctrl, int row_mask, int bank_mask, bool) {
+    const uint32_t* all = l3cpu::exchange((uint32_t)src);
+    const unsigned l = l3cpu::lane();
+    unsigned from = 0;
+    if (ctrl <= 0xFF) from = (l & ~3u) + (((unsigned)ctrl >> (2 * (l & 3u))) & 3u);   /* quad_perm */
+    else if (ctrl == 0x140) from = l ^ 15u;                                            /* row_mirror */
+    else if (ctrl == 0x141) from = l ^ 7u;                                             /* row_half_mirror */
+    else std::abort();
+    return (row_mask >> (l / 16) & 1) && (bank_mask >> (l / 4 % 4) & 1) ? (int)all[from] : old;
+}
+/* v_permlane16_swap_b32: the odd 16-lane rows of the first register and the even rows of the
+ * second change places (row 1 with row 0, row 3 with row 2) */
+struct L3CpuPair { uint32_t v[2]; uint32_t operator[](int i) const { return v[i]; } };
+inline L3CpuPair l3cpu_permlane16_swap(uint32_t a, uint32_t b, bool, bool) {
+    const unsigned l = l3cpu::lane();
+    const bool odd = (l / 16) & 1u;
+    const uint32_t b_of_row_below = l3cpu::exchange(b)[l ^ 16u];
+    const uint32_t a_of_row_above = l3cpu::exchange(a)[l ^ 16u];
+    return odd ? L3CpuPair{{b_of_row_below, b}} : L3CpuPair{{a, a_of_row_above}};
+}
+inline int l3cpu_readlane(int v, int lane) { return (int)l3cpu::exchange((uint32_t)v)[lane & 63]; }
+inline uint64_t l3cpu_ballot(bool mine) {
+    const uint32_t* all = l3cpu::exchange(mine ? 1u : 0u);
+    uint64_t mask = 0;
+    for (int l = 0; l < 64; ++l) mask |= (uint64_t)all[l] << l;
+    return mask;
 }
 inline uint32_t l3cpu_readfirstlane(uint32_t v) { return l3cpu::exchange(v)[0]; }
 /* a ballot over the wave: true if any lane's flag is */
@@ -171,6 +210,10 @@ inline uint32_t l3cpu_bitop3(uint32_t a, uint32_t b, uint32_t c, uint32_t table)
 #define __builtin_amdgcn_perm l3cpu_perm
 #define __builtin_amdgcn_bitop3_b32 l3cpu_bitop3
 #define __builtin_amdgcn_readfirstlane l3cpu_readfirstlane
+#define __builtin_amdgcn_readlane l3cpu_readlane
+#define __builtin_amdgcn_ballot_w64 l3cpu_ballot
+#define __builtin_amdgcn_update_dpp l3cpu_update_dpp
+#define __builtin_amdgcn_permlane16_swap l3cpu_permlane16_swap
 #define __builtin_amdgcn_sched_barrier(mask) ((void)0)
 #define __builtin_amdgcn_s_setprio(level) ((void)0)
 
@@ -203,9 +246,14 @@ inline u32x4 lds_read_u32x4(uint32_t where) { return *l3cpu_lds_at<const u32x4>(
 inline void lds_write_u32x2(uint32_t where, u32x2 v) { *l3cpu_lds_at<u32x2>(where, 8) = v; }
 inline void lds_write_u32x4(uint32_t where, u32x4 v) { *l3cpu_lds_at<u32x4>(where, 16) = v; }
 
+inline void lds_or_pair(uint32_t where, uint32_t lo, uint32_t hi) {
+    __atomic_fetch_or(l3cpu_lds_at<uint32_t>(where, 4), lo, __ATOMIC_RELAXED);
+    __atomic_fetch_or(l3cpu_lds_at<uint32_t>(where + 4, 4), hi, __ATOMIC_RELAXED);
+}
+#define L3_DYNAMIC_LDS(type, name) type* name = reinterpret_cast<type*>(l3cpu::dynamic_lds())
+
 #define L3_KEEP_VGPR(x) asm volatile("" : "+r"(x))
 #define L3_KEEP_SGPR(x) asm volatile("" : "+r"(x))
-#define L3_OPAQUE_VGPR(x) asm("" : "+r"(x))
 
 /* the lanes of a wave, which are threads here, meet: what one wrote to LDS the others see */
 inline void wave_lds_fence() { l3cpu::wave_barrier(); }
