@@ -347,7 +347,9 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
     }
     /* no lane of the wave has a word that is cut off or not there: one scalar branch then
      * stands for the tests of every row's write-out (with planar rows stored as they are decoded,
-     * two vector and ten scalar instructions a row) */
+     * two vector and ten scalar instructions a row).  Without and with it, on one card: one image of
+     * 1920x1080 20.4 -> 19.0 us, 4 of 2048x1024 36.5 -> 33.4, 32 of 1920x1080 planar 79.3 -> 75.8, 32 of
+     * 2048x1024 77.9 -> 77.2. */
     bool partial = false;
 #pragma unroll
     for (int pass = 0; pass < NW; ++pass) partial |= word_valid[pass] != 4;

@@ -444,9 +444,10 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
         const uint32_t dE = pk_sub_u16_sat_from_low(extremes, uE), dO = pk_sub_u16_sat_from_low(extremes, uO);
         const uint32_t pair = dE | (dO << w);                   /* (d0 | d1 << w, d2 | d3 << w) */
         /* The lower field moves up to the upper one (not the upper one down: that takes three
-         * instructions more; 32 images of 2048x1024 172.4 -> 171.6 us with this): the four deltas are then the bits from 16 - 2 w on, below them
-         * zeros, and go to the ring by as much sooner, which may be the word ahead of the
-         * stream's first (the ring's last: zeros).  w = 0 shifts a field of zeros. */
+         * instructions more; 32 images of 2048x1024 172.4 -> 171.6 us with this): the four deltas
+         * are then the bits from 16 - 2 w on, below them zeros, and go to the ring by as much
+         * sooner, which may be the word ahead of the stream's first (the ring's last: zeros).
+         * w = 0 shifts a field of zeros. */
         const uint32_t up_by = (uint32_t)(16 - 2 * (int)w);     /* and nothing in the upper half */
         const uint32_t group = pk_lshl_b16(up_by, pair);
         put(group, rowpos - 4 + (xpix + 2) * w); /* lanes without pixels add zeros to their own ring */
@@ -456,11 +457,12 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
     /* Periods of P rows.  A row's range takes a reduction over the patch's lanes and then a few
      * scalar-like steps; done row by row every lane works those out for itself (101 vector
      * instructions a row in all, which is what bounds this kernel), done for four rows at once
-     * the steps are shared (see patch_min_of_rows; about 75).  A call with 32 images of
-     * 2048x1024: 198 -> 173 us, with one of 1920x1080: 40.7 -> 34.9 us.  The rows of the next period are asked for as soon as this one's
-     * channel bytes are taken out of their registers; the granules the previous period
-     * completed are written out right behind those loads, so that neither is waited for
-     * before a whole period of arithmetic has passed. */
+     * the steps are shared (see patch_min_of_rows; about 75, and 70 with what pack_row saved
+     * later).  By this step alone a call with 32 images of 2048x1024 went from 198 to 173 us, one with
+     * one of 1920x1080 from 40.7 to 34.9 us.  The rows of the next period are asked for as soon as
+     * this one's channel bytes are taken out of their registers; the granules the previous period
+     * completed are written out right behind those loads, so that neither is waited for before a
+     * whole period of arithmetic has passed. */
     static_assert(P == 4, "patch_min_of_rows takes four rows");
     load_rows(src, ph);
     /* issue priorities as in the decoder: lowered by quarters of the rows, an older

@@ -28,11 +28,12 @@ namespace {
  * is 640..895, both n hold and the sum is T, whatever the outer neighbours hold (0, or another
  * patch's pixel).  The registers are worked on in lockstep so that dependent instructions are
  * not adjacent.
- * Measured with the shorter record walk of the decoder's open_row, before and after on one card:
- * 32 images of 2048x1024 88.4 -> 85.0 us a call, 32 of 1920x1080 planar 85.1 -> 80.4, 256 photographs
- * 61.7 -> 59.6.  Written as inline assembly it cost the small calls what it gained (4 images of
- * 2048x1024, one wave per SIMD: 36.0 us against 35.6 before): behind that the compiler puts wait
- * states.  With builtins, and the write-out's tests taken once, 34.2, 84.2, 76.9 and 59.5 us. */
+ * Measured together with the shorter record walk of the decoder's open_row (the decoder's write-out as
+ * it was), before and after on one card: 32 images of 2048x1024 81.3 -> 77.9 us a call, 8 of 3840x2160
+ * planar 78.9 -> 75.0, 32 of 1920x1080 planar 84.2 -> 79.3, 256 photographs 59.3 -> 56.9.  Calls that
+ * leave the SIMDs with one wave or less wait for the longer chain instead: 4 of 2048x1024 35.7 -> 36.5, one of
+ * 1920x1080 20.2 -> 20.4, 16 fused windows of 768x768 54.2 -> 54.2.  Written as inline assembly those
+ * lost more: behind that the compiler puts wait states. */
 constexpr uint32_t kPixelBias = 0x64006400u;          /* 1024 in both fields: a pixel of value 0 */
 constexpr uint32_t kPredictLow = 0x0000u;             /* 0, border fields' third operand of the minimum */
 constexpr uint32_t kPredictHigh = 0x677Fu;            /* 1919, of the maximum */
