@@ -600,10 +600,6 @@ struct CompactGeom {
     static_assert(SLOTS <= 16, "offsets inside a workgroup are a scan over one 16-lane row");
 };
 
-constexpr uint32_t compact_slots(uint32_t n) {
-    return n == 32 ? CompactGeom<32>::SLOTS : (n == 64 ? CompactGeom<64>::SLOTS : CompactGeom<128>::SLOTS);
-}
-
 /* Which calls lay their files out in the compaction itself (OWN_LAYOUT below).  A workgroup then reads
  * all patch sizes of its image, so what is read grows with the square of the patches and with
  * the number of images; the layout kernel's time grows with the largest image only (2.5 us, and
@@ -620,8 +616,11 @@ constexpr uint32_t compact_slots(uint32_t n) {
  * Images of more than kOwnLayoutPatches patches keep the layout kernel (one of 12288 32-pixel patches
  * would take 36.5 instead of 82.6 us without, so that bound could lie higher). */
 constexpr uint32_t kOwnLayoutPatches = 4096;
-constexpr uint64_t own_layout_reads(uint32_t n, uint64_t patches) {      /* counted as above */
-    return (n == 32 ? 1 : n == 64 ? 3 : 4) * patches * ((patches + compact_slots(n) - 1) / compact_slots(n));
+/* counted as above, for one image; 32-bit and without a division: a batch is planned image by image */
+constexpr uint32_t own_layout_reads(uint32_t n, uint32_t patches) {
+    constexpr uint32_t s32 = CompactGeom<32>::SLOTS, s64 = CompactGeom<64>::SLOTS;
+    static_assert(CompactGeom<128>::SLOTS == 1 && 4ull * kOwnLayoutPatches * kOwnLayoutPatches <= 0xFFFFFFFFull, "");
+    return n == 32 ? patches * ((patches + s32 - 1) / s32) : n == 64 ? 3 * patches * ((patches + s64 - 1) / s64) : 4 * patches * patches;
 }
 constexpr bool own_layout_pays(uint32_t max_patches, uint64_t reads) {
     return max_patches <= kOwnLayoutPatches && reads <= 36000ull * (max_patches + 700);
@@ -892,8 +891,7 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
             const uint64_t units = (uint64_t)((tiles_x + tpw - 1) / tpw) * ((it.height + np - 1) / np);
             if (units > strip_units[cls]) strip_units[cls] = (uint32_t)units;
             if (3 * p > strip_slots[cls]) strip_slots[cls] = (uint32_t)(3 * p);
-            if (3 * p <= kOwnLayoutPatches)
-                layout_reads += own_layout_reads(np, 3 * p);
+            if (3 * p <= kOwnLayoutPatches) layout_reads += own_layout_reads(np, (uint32_t)(3 * p));
             slot_bytes += (size_t)(3 * p) * strip_slot_bytes(np);
         } else {
             any_plain = true;
