@@ -151,6 +151,301 @@ __device__ __forceinline__ uint16_t normalised_bits(uint32_t v, float mean, floa
 
 /* ---- the decode kernel ---------------------------------------------------- */
 
+/* Which patch a lane group of a work unit decodes. */
+struct UnitPlace {
+    uint32_t tx, ty;         /* the patch */
+    uint32_t ty_base;        /* patch row of the unit's first group, the same for the whole workgroup */
+    uint32_t strip_x0;       /* per-row order: first column of the unit's strip */
+    bool active;             /* false: a group that only shadows another patch of its unit */
+    bool flat_order;
+};
+template <int N, int TPW, int MODE>
+__device__ __forceinline__ UnitPlace place_unit(const L3ImageDesc& d, const uint32_t unit, const uint32_t g) {
+    UnitPlace at;
+    at.strip_x0 = 0;
+    at.flat_order = MODE != L3_MODE_TENSOR && d.groups_x == 0;
+    if (at.flat_order) {
+        const bool upper = unit < d.flat_upper_units;
+        const uint32_t first = (upper ? unit : unit - d.flat_upper_units) * TPW;
+        const uint32_t count = upper ? d.tiles_x * d.flat_upper_rows : d.tiles_x;
+        const uint32_t row_off = upper ? 0u : d.flat_upper_rows;
+        const uint32_t fl = first + g;
+        at.active = fl < count;
+        const uint32_t flc = at.active ? fl : count - 1;
+        const uint32_t qrow = flc / d.tiles_x;
+        at.ty = row_off + qrow;
+        at.tx = flc - qrow * d.tiles_x;
+        at.ty_base = row_off + first / d.tiles_x;
+    } else {
+        const uint32_t trow = unit / d.groups_x, gx = unit - trow * d.groups_x;
+        const uint32_t txr = gx * TPW + g;
+        at.active = txr < d.tile_x_count;
+        at.tx = d.tile_x_first + (at.active ? txr : d.tile_x_count - 1);
+        at.ty = at.ty_base = d.tile_y_first + trow;
+        at.strip_x0 = (d.tile_x_first + gx * TPW) * N;
+    }
+    return at;
+}
+
+/* Where the stream of channel c of patch (tx, ty) lies: Section 4.3, offset array of channel c.
+ * Offsets that point outside the data section are flagged and held inside it. */
+struct StreamPlace {
+    const uint8_t* origin;   /* 16-byte aligned, at or up to 15 bytes before the stream's first byte */
+    uint32_t bitpos, endbit; /* first bit and end of the stream from there */
+    uint32_t limit;          /* the stream's granules end here; inside the file's last one */
+};
+__device__ __forceinline__ StreamPlace locate_stream(const L3ImageDesc& d, const uint32_t c, const uint32_t tx,
+                                                     const uint32_t ty, uint32_t& flags) {
+    const uint32_t patches = d.tiles_x * d.tiles_y;
+    const uint32_t data_len = (uint32_t)(d.file_len - d.header_bytes);
+    const uint32_t flat = c * patches + ty * d.tiles_x + tx;
+    const uint8_t* otab = d.file + 13 + 4 * (size_t)flat;
+    uint32_t off = load_u32_any_alignment(otab);
+    uint32_t end = flat + 1 < 3 * patches ? load_u32_any_alignment(otab + 4) : data_len;
+    if (off > data_len || end > data_len || end < off) {
+        flags |= L3_STATUS_BAD_OFFSET;
+        off = min(off, data_len);
+        end = min(max(end, off), data_len);
+    }
+    const uintptr_t a = (uintptr_t)(d.file + d.header_bytes + off);
+    const uintptr_t ab = a & ~(uintptr_t)15;
+    StreamPlace s;
+    s.bitpos = (uint32_t)(a - ab) * 8;
+    s.endbit = s.bitpos + (end - off) * 8;
+    s.origin = reinterpret_cast<const uint8_t*>(ab);
+    s.limit = ((s.endbit >> 3) + 15u) & ~15u;
+    return s;
+}
+
+/* Writes the decoded rows of a unit: what that needs from the descriptor and the lane's place is
+ * worked out once.  The scalars are pinned in registers: left to itself the compiler reloads them
+ * from the argument segment after every barrier, and the wave waits for the scalar load each
+ * period. */
+template <int N, int NW, int MODE>
+struct RowWriter {
+    static constexpr int QW = 64 * NW;
+    uint64_t out_base, out_row_stride, out_plane_stride;
+    uint32_t img_width;
+    int32_t win_x0, win_y0;
+    uint32_t win_flip;
+    const uint32_t crop_w, crop_h, lane;
+    const uint16_t* const s_lut;
+    uint32_t word_x[NW], word_valid[NW], word_off[NW];
+    bool wave_whole;
+    /* tensor mode: the first of this lane's four columns in the strip, and their byte offset in a row of
+     * the window; and of the one value the lane takes at the edges its byte in the parked row, its channel's
+     * part of the table and its place behind the start of the first channel's row; how many lanes do */
+    bool takes_four;
+    uint32_t strip_at, tensor_at, singles, single_at, single_lut;
+    uint64_t single_to;
+
+    __device__ __forceinline__ RowWriter(const L3ImageDesc& d, const UnitPlace& at, uint32_t xl, uint32_t lane_,
+                                         uint32_t crop_w_, uint32_t crop_h_, const uint16_t* s_lut_)
+        : crop_w(crop_w_), crop_h(crop_h_), lane(lane_), s_lut(s_lut_) {
+        out_base = (uint64_t)(uintptr_t)d.out;
+        out_row_stride = d.row_stride;
+        out_plane_stride = d.plane_stride;
+        img_width = d.width;
+        win_x0 = d.crop_x0;
+        win_y0 = d.crop_y0;
+        win_flip = d.flip;
+        L3_KEEP_SGPR(out_base);
+        L3_KEEP_SGPR(out_row_stride);
+        L3_KEEP_SGPR(out_plane_stride);
+        L3_KEEP_SGPR(img_width);
+        L3_KEEP_SGPR(win_x0);
+        L3_KEEP_SGPR(win_y0);
+        L3_KEEP_SGPR(win_flip);
+        /* lane l takes the 4-pixel words l, l + 64, ... of the wave's strip; how many of
+         * their pixels exist does not change from row to row */
+#pragma unroll
+        for (int pass = 0; pass < NW; ++pass) {
+            /* in flat order (NW = 1) the word is the lane's own four pixels; a group that
+             * only shadows the block's last patch writes nothing */
+            word_x[pass] = at.flat_order ? at.tx * N + 4 * xl : at.strip_x0 + 4 * (lane + 64 * pass);
+            word_valid[pass] = (word_x[pass] >= img_width || (at.flat_order && !at.active)) ? 0u : min(4u, img_width - word_x[pass]);
+            /* byte offset of the word from the start of the output row that the unit's
+             * first patch row writes: column bytes, plus the rows by which this group's
+             * patch row lies below it (flat order; the host checked that this fits 32 bits) */
+            word_off[pass] = (MODE == L3_MODE_HWC ? 3u : 1u) * word_x[pass] +
+                             (at.ty - at.ty_base) * (uint32_t)N * (uint32_t)out_row_stride;
+        }
+        /* no lane of the wave has a word that is cut off or not there: one scalar branch then
+         * stands for the tests of every row's write-out (with planar rows stored as they are decoded,
+         * two vector and ten scalar instructions a row).  Without and with it, on one card: one image of
+         * 1920x1080 20.4 -> 19.0 us, 4 of 2048x1024 36.5 -> 33.4, 32 of 1920x1080 planar 79.3 -> 75.8, 32 of
+         * 2048x1024 77.9 -> 77.2. */
+        bool partial = false;
+#pragma unroll
+        for (int pass = 0; pass < NW; ++pass) partial |= word_valid[pass] != 4;
+        wave_whole = !wave_any(partial);
+        if (MODE == L3_MODE_TENSOR) {
+            static_assert(MODE != L3_MODE_TENSOR || NW == 1, "a strip is 64 words");
+            /* A lane takes four columns whose elements start at a multiple of 8 bytes in a row of the
+             * window, not the four of its own word: no lane's columns lie across the window's edge.
+             * The strip's columns ahead of the first such four and behind the last, up to three
+             * each, are taken one a lane, all channels at once.  (Where the window's width is no multiple of
+             * four its rows start at any alignment, and the fours at the strip's first column.)  With the
+             * strip's own words those on the window's edges went element by element, for which a
+             * wave waited in every row with three of four windows: 256 windows of 224x224 32.9 -> 27.2 us a
+             * call, 16 of 768x768 54.1 -> 47.1, 16 of 401x300 at N = 128 48.0 -> 41.6, 8 of 1999x1501 59.9 -> 58.6;
+             * without the alignment 16 of 768x768 took 3 us more.  (20 of 1001x777 at N = 64 went from 41.0 to
+             * 41.4.) */
+            const int32_t before = win_x0 - (int32_t)at.strip_x0;       /* the window's first column, in the strip */
+            const int32_t from = max(before, 0);
+            const uint32_t count = (uint32_t)(min(before + (int32_t)crop_w, 256) - from);
+            const uint32_t head = crop_w % 4 ? 0u : min(count, (uint32_t)(before - from) & 3u);
+            const uint32_t fours = (count - head) / 4, tail = (count - head) & 3u;
+            takes_four = lane < fours;
+            strip_at = (uint32_t)from + head + 4 * lane;
+            const int32_t col = (int32_t)strip_at - before;             /* of the window */
+            tensor_at = 2u * (uint32_t)(win_flip ? (int32_t)crop_w - 4 - col : col);
+            /* lane = (channel, one of the head's and tail's columns) */
+            const uint32_t each = head + tail, ch = each ? lane / each : 0u, nth = each ? lane - ch * each : 0u;
+            const uint32_t single = (uint32_t)from + (nth < head ? nth : 4 * fours + nth);
+            const int32_t single_col = (int32_t)single - before;
+            singles = 3 * each;
+            single_at = ch * 4 * QW + single;
+            single_lut = ch * 256;
+            single_to = 2 * ((uint64_t)ch * crop_h * crop_w + (uint32_t)(win_flip ? (int32_t)crop_w - 1 - single_col : single_col));
+        }
+    }
+
+    /* Row y of the image, whose three channels are parked at `src`: lane l takes the 4-pixel words
+     * l, l + 64, ... of the strip, 12 contiguous output bytes each, contiguous over the lanes. */
+    __device__ __forceinline__ void write_row(const uint32_t* src, uint32_t y) {
+#pragma unroll
+        for (int pass = 0; pass < NW; ++pass) {
+            const uint32_t q = lane + 64 * pass;
+            const uint32_t nvalid = word_valid[pass];
+            /* interleaved mode: 12 bytes R0 G0 B0 R1 G1 B1 R2 G2 B2 R3 G3 B3 per word q;
+             * planar mode: one word of 4 pixels per channel */
+            uint32_t pr = 0, pg = 0, pb = 0;
+            if (MODE != L3_MODE_TENSOR) {
+                pr = MODE == L3_MODE_HWC ? src[3 * q] : src[q];
+                pg = MODE == L3_MODE_HWC ? src[3 * q + 1] : src[QW + q];
+                pb = MODE == L3_MODE_HWC ? src[3 * q + 2] : src[2 * QW + q];
+            }
+            if (MODE == L3_MODE_HWC) {
+                /* row start: scalar arithmetic; the lane's 32-bit column offset goes into the
+                 * store's offset register (kept opaque here so that it is not widened and
+                 * added with vector instructions ahead of time) */
+                L3_KEEP_VGPR(word_off[pass]);
+                const uint32_t column = word_off[pass];
+                global_u8* row = reinterpret_cast<global_u8*>((uintptr_t)(out_base + (uint64_t)y * out_row_stride));
+                const uint32_t o0 = pr, o1 = pg, o2 = pb;
+                if (wave_whole || nvalid == 4) {
+                    const u32x3 v = {o0, o1, o2};
+                    __builtin_nontemporal_store(v, reinterpret_cast<global_u32x3_any*>(row + column));
+                } else if (nvalid) {
+                    /* the last word of an image row: 3, 6 or 9 bytes in two stores */
+                    global_u8* b = row + column;
+                    if (nvalid == 3) {
+                        const u32x2 v = {o0, o1};
+                        *reinterpret_cast<global_u32x2_any*>(b) = v;
+                        b[8] = (uint8_t)o2;
+                    } else if (nvalid == 2) {
+                        *reinterpret_cast<global_u32_any*>(b) = o0;
+                        *reinterpret_cast<global_u16_any*>(b + 4) = (uint16_t)o1;
+                    } else {
+                        *reinterpret_cast<global_u16_any*>(b) = (uint16_t)o0;
+                        b[2] = (uint8_t)(o0 >> 16);
+                    }
+                }
+            } else if (MODE == L3_MODE_CHW) {
+#pragma unroll
+                for (int ch = 0; ch < 3; ++ch) {
+                    const uint32_t word = ch == 0 ? pr : (ch == 1 ? pg : pb);
+                    global_u8* row = reinterpret_cast<global_u8*>(
+                        (uintptr_t)(out_base + (uint64_t)ch * out_plane_stride + (uint64_t)y * out_row_stride));
+                    L3_KEEP_VGPR(word_off[pass]);
+                    const uint32_t column = word_off[pass];
+                    if (wave_whole || nvalid == 4) {
+                        __builtin_nontemporal_store(word, reinterpret_cast<global_u32_any*>(row + column));
+                    } else if (nvalid) {
+                        global_u8* b = row + column;
+#pragma unroll
+                        for (int k = 0; k < 3; ++k)
+                            if ((uint32_t)k < nvalid) b[k] = (uint8_t)(word >> (8 * k));
+                    }
+                }
+            } else {
+                /* tensor mode: window test, optional mirror, table of the 256 normalised values: four
+                 * elements (8 bytes) per channel at once, mirrored or not */
+                const int32_t row = (int32_t)y - win_y0;
+                if (row >= 0 && row < (int32_t)crop_h) {
+                    /* element (ch, row, 0) of this image; planes are crop_h * crop_w apart: the
+                     * planes' rows start at scalar addresses, the lane adds its byte offset */
+                    const size_t plane = (size_t)crop_h * crop_w;
+                    if (takes_four) {
+                        /* all twelve table reads first, so that they travel together */
+                        uint16_t e[3][4];
+#pragma unroll
+                        for (int ch = 0; ch < 3; ++ch) {
+                            const uint32_t* words = src + ch * QW + strip_at / 4;   /* and the word behind it: see SPAN */
+                            const uint32_t word = __builtin_amdgcn_alignbit(words[1], words[0], 8 * (strip_at & 3u));
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) e[ch][k] = s_lut[ch * 256 + ((word >> (8 * k)) & 0xFFu)];
+                        }
+                        u32x2 v[3];
+                        if (win_flip) {        /* the same for the whole image: elements 3 2 | 1 0 */
+#pragma unroll
+                            for (int ch = 0; ch < 3; ++ch) v[ch] = four(e[ch][3], e[ch][2], e[ch][1], e[ch][0]);
+                        } else {
+#pragma unroll
+                            for (int ch = 0; ch < 3; ++ch) v[ch] = four(e[ch][0], e[ch][1], e[ch][2], e[ch][3]);
+                        }
+#pragma unroll
+                        for (int ch = 0; ch < 3; ++ch)
+                            __builtin_nontemporal_store(v[ch], reinterpret_cast<global_u32x2_any*>(line_of(row, ch * plane) + offset_of(tensor_at)));
+                    }
+                    if (lane < singles) {
+                        const uint32_t value = reinterpret_cast<const uint8_t*>(src)[single_at];
+                        *reinterpret_cast<global_u16_any*>(line_of(row, 0) + single_to) = s_lut[single_lut + value];
+                    }
+                }
+            }
+        }
+    }
+    static __device__ __forceinline__ u32x2 four(uint16_t e0, uint16_t e1, uint16_t e2, uint16_t e3) {
+        const u16x2 lo = {e0, e1}, hi = {e2, e3};
+        return u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+    }
+    /* the start of a row of the window, `plane` elements behind the first channel's: a scalar */
+    __device__ __forceinline__ global_u8* line_of(int32_t row, size_t plane) const {
+        uint64_t line_at = out_base + 2 * ((uint64_t)row * crop_w + plane);
+        L3_KEEP_SGPR(line_at);
+        return reinterpret_cast<global_u8*>((uintptr_t)line_at);
+    }
+    static __device__ __forceinline__ uint32_t offset_of(uint32_t to) {
+        L3_KEEP_VGPR(to);      /* stays the store's 32-bit offset */
+        return to;
+    }
+
+    /* Planar output: the lane's word of channel c of row y, from the wave that decoded it. */
+    __device__ __forceinline__ void store_own(uint32_t c, uint32_t y, uint32_t word) {
+        global_u8* row = reinterpret_cast<global_u8*>(
+            (uintptr_t)(out_base + (uint64_t)c * out_plane_stride + (uint64_t)y * out_row_stride));
+        L3_KEEP_VGPR(word_off[0]);
+        /* two separate arms (not "whole wave or whole word"): with those joined a wave with a
+         * cut-off word jumps twice out of line in every row, and calls of such waves were
+         * slower than without the scalar branch (300 images of 130x97 41.2 us, 40.3 without the
+         * branch, 36.5 so; 200 of 258x128 43.8, 42.7, 40.2; whole waves are the same) */
+        if (wave_whole) {
+            __builtin_nontemporal_store(word, reinterpret_cast<global_u32_any*>(row + word_off[0]));
+        } else {
+            if (word_valid[0] == 4)
+                __builtin_nontemporal_store(word, reinterpret_cast<global_u32_any*>(row + word_off[0]));
+            if (word_valid[0] - 1 < 3) {
+                global_u8* b = row + word_off[0];
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    if ((uint32_t)k < word_valid[0]) b[k] = (uint8_t)(word >> (8 * k));
+            }
+        }
+    }
+};
+
 template <int N, int PPL, int MODE>
 __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t unit,
                                             uint32_t* __restrict__ status, uint32_t crop_w,
@@ -174,7 +469,10 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
      * the same bytes), so only N = 128 takes it. */
     constexpr bool DIRECT = MODE == L3_MODE_CHW && PPL == 4 && N == 128;
     constexpr int PARKS = LATE_BARRIER ? 3 : 2;
-    __shared__ __attribute__((aligned(8))) uint32_t parked[PARKS][P][3][QW]; /* [buffer][row of period][channel][word] */
+    /* [buffer][row of period][channel][word]; in tensor mode a lane reads the word behind its own too
+     * (four columns from any one on), behind the last row words that nothing writes */
+    constexpr int SPAN = P * 3 * QW + (MODE == L3_MODE_TENSOR ? 4 : 0);
+    __shared__ __attribute__((aligned(8))) uint32_t parked[PARKS][SPAN];
     __shared__ uint16_t s_lut[MODE == L3_MODE_TENSOR ? 768 : 2];
 
     const uint32_t lane = threadIdx.x & 63u;
@@ -190,61 +488,21 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
     }
 
     const uint32_t g = lane / LPT, xl = lane % LPT;
-    /* Which patch this lane group decodes: (tx, ty); ty_base is the patch row of the
-     * unit's first group, the same for the whole workgroup. */
-    uint32_t tx, ty, ty_base, strip_x0 = 0;
-    bool active;
-    const bool flat_order = MODE != L3_MODE_TENSOR && PPL == 4 && d.groups_x == 0;
-    if (flat_order) {
-        const bool upper = unit < d.flat_upper_units;
-        const uint32_t first = (upper ? unit : unit - d.flat_upper_units) * TPW;
-        const uint32_t count = upper ? d.tiles_x * d.flat_upper_rows : d.tiles_x;
-        const uint32_t row_off = upper ? 0u : d.flat_upper_rows;
-        const uint32_t fl = first + g;
-        active = fl < count;
-        const uint32_t flc = active ? fl : count - 1;
-        const uint32_t qrow = flc / d.tiles_x;
-        ty = row_off + qrow;
-        tx = flc - qrow * d.tiles_x;
-        ty_base = row_off + first / d.tiles_x;
-    } else {
-        const uint32_t trow = unit / d.groups_x, gx = unit - trow * d.groups_x;
-        const uint32_t txr = gx * TPW + g;
-        active = txr < d.tile_x_count;
-        tx = d.tile_x_first + (active ? txr : d.tile_x_count - 1);
-        ty = ty_base = d.tile_y_first + trow;
-        strip_x0 = (d.tile_x_first + gx * TPW) * N;   /* first column of the wave's strip */
-    }
-    const uint32_t x0 = tx * N, y0 = ty_base * N;     /* y0: first image row of the unit's first patch */
+    const UnitPlace at = place_unit<N, TPW, MODE>(d, unit, g);
+    const uint32_t x0 = at.tx * N, y0 = at.ty_base * N;     /* y0: first image row of the unit's first patch */
     const uint32_t pw = min((uint32_t)N, d.width - x0);
     uint32_t ph = min((uint32_t)N, d.height - y0);           /* same for the whole workgroup */
     if (MODE == L3_MODE_TENSOR)                              /* rows below the window are not needed */
         ph = min(ph, (uint32_t)d.crop_y0 + crop_h - y0);
-    const uint32_t patches = d.tiles_x * d.tiles_y;
-    const uint32_t data_len = (uint32_t)(d.file_len - d.header_bytes);
-
     /* locate this lane group's stream: Section 4.3, offset array of channel c */
     uint32_t flags = 0;
-    uint32_t bitpos, endbit, fill, limit;
-    const uint8_t* origin;
+    const StreamPlace stream = locate_stream(d, c, at.tx, at.ty, flags);
+    uint32_t bitpos = stream.bitpos, fill;
+    const uint32_t endbit = stream.endbit, limit = stream.limit;
+    const uint8_t* const origin = stream.origin;
     u32x4 pf[GPL];
     uint32_t* const ring = rings[c][g];
     {
-        const uint32_t flat = c * patches + ty * d.tiles_x + tx;
-        const uint8_t* otab = d.file + 13 + 4 * (size_t)flat;
-        uint32_t off = load_u32_any_alignment(otab);
-        uint32_t end = flat + 1 < 3 * patches ? load_u32_any_alignment(otab + 4) : data_len;
-        if (off > data_len || end > data_len || end < off) {
-            flags |= L3_STATUS_BAD_OFFSET;
-            off = min(off, data_len);
-            end = min(max(end, off), data_len);
-        }
-        const uintptr_t a = (uintptr_t)(d.file + d.header_bytes + off);
-        const uintptr_t ab = a & ~(uintptr_t)15;
-        bitpos = (uint32_t)(a - ab) * 8;
-        endbit = bitpos + (end - off) * 8;
-        origin = reinterpret_cast<const uint8_t*>(ab);
-        limit = ((endbit >> 3) + 15u) & ~15u;     /* the stream's granules end here; inside the file's last one */
         /* first chunk into the ring (covers the first period), second into registers */
 #pragma unroll
         for (int t = 0; t < GPL; ++t) pf[t] = load_granule(origin, (t * LPT + xl) * 16, limit);
@@ -315,181 +573,11 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
         K = 0xFFFFFFFFu << w;
     };
 
-    /* What the write-out needs from the descriptor, pinned in registers: left to
-     * itself the compiler reloads these from the argument segment after every
-     * barrier, and the wave waits for the scalar load each period. */
-    uint64_t out_base = (uint64_t)(uintptr_t)d.out, out_row_stride = d.row_stride,
-             out_plane_stride = d.plane_stride;
-    uint32_t img_width = d.width;
-    int32_t win_x0 = d.crop_x0, win_y0 = d.crop_y0;
-    uint32_t win_flip = d.flip;
-    L3_KEEP_SGPR(out_base);
-    L3_KEEP_SGPR(out_row_stride);
-    L3_KEEP_SGPR(out_plane_stride);
-    L3_KEEP_SGPR(img_width);
-    L3_KEEP_SGPR(win_x0);
-    L3_KEEP_SGPR(win_y0);
-    L3_KEEP_SGPR(win_flip);
-    /* lane l takes the 4-pixel words l, l + 64, ... of the wave's strip; how many of
-     * their pixels exist does not change from row to row */
-    uint32_t word_x[NW], word_valid[NW], word_off[NW];
-#pragma unroll
-    for (int pass = 0; pass < NW; ++pass) {
-        /* in flat order (NW = 1) the word is the lane's own four pixels; a group that
-         * only shadows the block's last patch writes nothing */
-        word_x[pass] = flat_order ? x0 + 4 * xl : strip_x0 + 4 * (lane + 64 * pass);
-        word_valid[pass] = (word_x[pass] >= img_width || (flat_order && !active)) ? 0u : min(4u, img_width - word_x[pass]);
-        /* byte offset of the word from the start of the output row that the unit's
-         * first patch row writes: column bytes, plus the rows by which this group's
-         * patch row lies below it (flat order; the host checked that this fits 32 bits) */
-        word_off[pass] = (MODE == L3_MODE_HWC ? 3u : 1u) * word_x[pass] +
-                         (ty - ty_base) * (uint32_t)N * (uint32_t)out_row_stride;
-    }
-    /* no lane of the wave has a word that is cut off or not there: one scalar branch then
-     * stands for the tests of every row's write-out (with planar rows stored as they are decoded,
-     * two vector and ten scalar instructions a row).  Without and with it, on one card: one image of
-     * 1920x1080 20.4 -> 19.0 us, 4 of 2048x1024 36.5 -> 33.4, 32 of 1920x1080 planar 79.3 -> 75.8, 32 of
-     * 2048x1024 77.9 -> 77.2. */
-    bool partial = false;
-#pragma unroll
-    for (int pass = 0; pass < NW; ++pass) partial |= word_valid[pass] != 4;
-    const bool wave_whole = !wave_any(partial);
-    /* tensor mode: whether the word's 4 pixels all lie inside the window, and the byte offset
-     * of its 4 elements in a row of the window (mirrored or not): the same for every row */
-    bool tensor_whole[NW];
-    uint32_t tensor_at[NW];
-#pragma unroll
-    for (int pass = 0; pass < NW; ++pass) {
-        const int32_t col0 = (int32_t)word_x[pass] - win_x0;
-        tensor_whole[pass] = MODE == L3_MODE_TENSOR && word_valid[pass] == 4 && col0 >= 0 &&
-                             col0 + 4 <= (int32_t)crop_w;
-        tensor_at[pass] = 2u * (uint32_t)(win_flip ? (int32_t)crop_w - 4 - col0 : col0);
-    }
-
+    RowWriter<N, NW, MODE> writer(d, at, xl, lane, crop_w, crop_h, s_lut);
     /* After the workgroup barrier: this wave writes row c of the period whose rows
-     * are parked in buffer `buf` (rows first .. first+count-1 of the patch).  Lane l
-     * takes the 4-pixel words l, l + 64, ... of the wave's strip: 12 contiguous
-     * output bytes each, contiguous over the lanes. */
+     * are parked in buffer `buf` (rows first .. first+count-1 of the patch). */
     auto flush = [&](uint32_t buf, uint32_t first, uint32_t count) {
-        if (c >= count) return;
-        const uint32_t y = y0 + first + c;
-#pragma unroll
-        for (int pass = 0; pass < NW; ++pass) {
-            const uint32_t q = lane + 64 * pass;
-            const uint32_t x = word_x[pass];                           /* image column of the word */
-            const uint32_t nvalid = word_valid[pass];
-            const uint32_t* src = &parked[buf][c][0][0];
-            /* interleaved mode: 12 bytes R0 G0 B0 R1 G1 B1 R2 G2 B2 R3 G3 B3 per word q;
-             * planar modes: one word of 4 pixels per channel */
-            const uint32_t pr = MODE == L3_MODE_HWC ? src[3 * q] : src[q];
-            const uint32_t pg = MODE == L3_MODE_HWC ? src[3 * q + 1] : src[QW + q];
-            const uint32_t pb = MODE == L3_MODE_HWC ? src[3 * q + 2] : src[2 * QW + q];
-            if (MODE == L3_MODE_HWC) {
-                /* row start: scalar arithmetic; the lane's 32-bit column offset goes into the
-                 * store's offset register (kept opaque here so that it is not widened and
-                 * added with vector instructions ahead of time) */
-                L3_KEEP_VGPR(word_off[pass]);
-                const uint32_t column = word_off[pass];
-                global_u8* row = reinterpret_cast<global_u8*>((uintptr_t)(out_base + (uint64_t)y * out_row_stride));
-                const uint32_t o0 = pr, o1 = pg, o2 = pb;
-                if (wave_whole || nvalid == 4) {
-                    const u32x3 v = {o0, o1, o2};
-                    __builtin_nontemporal_store(v, reinterpret_cast<global_u32x3_any*>(row + column));
-                } else if (nvalid) {
-                    /* the last word of an image row: 3, 6 or 9 bytes in two stores */
-                    global_u8* b = row + column;
-                    if (nvalid == 3) {
-                        const u32x2 v = {o0, o1};
-                        *reinterpret_cast<global_u32x2_any*>(b) = v;
-                        b[8] = (uint8_t)o2;
-                    } else if (nvalid == 2) {
-                        *reinterpret_cast<global_u32_any*>(b) = o0;
-                        *reinterpret_cast<global_u16_any*>(b + 4) = (uint16_t)o1;
-                    } else {
-                        *reinterpret_cast<global_u16_any*>(b) = (uint16_t)o0;
-                        b[2] = (uint8_t)(o0 >> 16);
-                    }
-                }
-            } else if (MODE == L3_MODE_CHW) {
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch) {
-                    const uint32_t word = ch == 0 ? pr : (ch == 1 ? pg : pb);
-                    global_u8* row = reinterpret_cast<global_u8*>(
-                        (uintptr_t)(out_base + (uint64_t)ch * out_plane_stride + (uint64_t)y * out_row_stride));
-                    L3_KEEP_VGPR(word_off[pass]);
-                    const uint32_t column = word_off[pass];
-                    if (wave_whole || nvalid == 4) {
-                        __builtin_nontemporal_store(word, reinterpret_cast<global_u32_any*>(row + column));
-                    } else if (nvalid) {
-                        global_u8* b = row + column;
-#pragma unroll
-                        for (int k = 0; k < 3; ++k)
-                            if ((uint32_t)k < nvalid) b[k] = (uint8_t)(word >> (8 * k));
-                    }
-                }
-            } else {
-                /* tensor mode: window test, optional mirror, table of the 256 normalised
-                 * values.  A word whose 4 pixels all lie inside the window is written as 4
-                 * elements (8 bytes) per channel at once, mirrored or not; words on the
-                 * window's edge go element by element. */
-                const int32_t row = (int32_t)y - win_y0;
-                if (row >= 0 && row < (int32_t)crop_h && nvalid) {
-                    /* all twelve table reads first, so that they travel together */
-                    uint16_t e[3][4];
-#pragma unroll
-                    for (int ch = 0; ch < 3; ++ch) {
-                        const uint32_t word = ch == 0 ? pr : (ch == 1 ? pg : pb);
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) e[ch][k] = s_lut[ch * 256 + ((word >> (8 * k)) & 0xFFu)];
-                    }
-                    /* element (ch, row, 0) of this image; planes are crop_h * crop_w apart: the
-                     * planes' rows start at scalar addresses, the lane adds its byte offset */
-                    const size_t plane = (size_t)crop_h * crop_w;
-                    if (tensor_whole[pass]) {
-                        if (win_flip) {        /* the same for the whole image: elements 3 2 | 1 0 */
-#pragma unroll
-                            for (int ch = 0; ch < 3; ++ch) {
-                                uint64_t line_at = out_base + 2 * ((uint64_t)row * crop_w + ch * plane);
-                                L3_KEEP_SGPR(line_at);
-                                global_u8* line = reinterpret_cast<global_u8*>((uintptr_t)line_at);
-                                uint32_t at = tensor_at[pass];
-                                L3_KEEP_VGPR(at);      /* stays the store's 32-bit offset */
-                                const u16x2 lo = {e[ch][3], e[ch][2]}, hi = {e[ch][1], e[ch][0]};
-                                const u32x2 v = {__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
-                                __builtin_nontemporal_store(v, reinterpret_cast<global_u32x2_any*>(line + at));
-                            }
-                        } else {
-#pragma unroll
-                            for (int ch = 0; ch < 3; ++ch) {
-                                uint64_t line_at = out_base + 2 * ((uint64_t)row * crop_w + ch * plane);
-                                L3_KEEP_SGPR(line_at);
-                                global_u8* line = reinterpret_cast<global_u8*>((uintptr_t)line_at);
-                                uint32_t at = tensor_at[pass];
-                                L3_KEEP_VGPR(at);      /* stays the store's 32-bit offset */
-                                const u16x2 lo = {e[ch][0], e[ch][1]}, hi = {e[ch][2], e[ch][3]};
-                                const u32x2 v = {__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
-                                __builtin_nontemporal_store(v, reinterpret_cast<global_u32x2_any*>(line + at));
-                            }
-                        }
-                    } else {
-                        const int32_t col0 = (int32_t)x - win_x0;   /* window column of pixel 0 */
-                        global_u16* line = reinterpret_cast<global_u16*>((uintptr_t)out_base) + (size_t)row * crop_w;
-#pragma unroll
-                        for (int ch = 0; ch < 3; ++ch) {
-                            global_u16* out16 = line + ch * plane;
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) {
-                                int32_t col = col0 + k;
-                                if ((uint32_t)k < nvalid && col >= 0 && col < (int32_t)crop_w) {
-                                    if (win_flip) col = (int32_t)crop_w - 1 - col;
-                                    out16[col] = e[ch][k];
-                                }
-                            }
-                        }
-                    }
-                }
-            }
-        }
+        if (c < count) writer.write_row(&parked[buf][c * 3 * QW], y0 + first + c);
     };
 
     uint32_t prev[NP];
@@ -561,25 +649,7 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
                 pb[12 * k + 9] = (uint8_t)(prev[2 * k + 1] >> 16);
             }
         } else if (DIRECT) {
-            global_u8* row = reinterpret_cast<global_u8*>(
-                (uintptr_t)(out_base + (uint64_t)c * out_plane_stride + (uint64_t)y * out_row_stride));
-            L3_KEEP_VGPR(word_off[0]);
-            /* two separate arms (not "whole wave or whole word"): with those joined a wave with a
-             * cut-off word jumps twice out of line in every row, and calls of such waves were
-             * slower than without the scalar branch (300 images of 130x97 41.2 us, 40.3 without the
-             * branch, 36.5 so; 200 of 258x128 43.8, 42.7, 40.2; whole waves are the same) */
-            if (wave_whole) {
-                __builtin_nontemporal_store(word[0], reinterpret_cast<global_u32_any*>(row + word_off[0]));
-            } else {
-                if (word_valid[0] == 4)
-                    __builtin_nontemporal_store(word[0], reinterpret_cast<global_u32_any*>(row + word_off[0]));
-                if (word_valid[0] - 1 < 3) {
-                    global_u8* b = row + word_off[0];
-#pragma unroll
-                    for (int k = 0; k < 3; ++k)
-                        if ((uint32_t)k < word_valid[0]) b[k] = (uint8_t)(word[0] >> (8 * k));
-                }
-            }
+            writer.store_own(c, y, word[0]);
         } else {
 #pragma unroll
             for (int k = 0; k < NW; ++k) park[k] = word[k];
@@ -635,9 +705,9 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
         /* interleaved mode: this lane's 12 NW bytes of the row, channel c first at byte c;
          * planar modes: this lane's NW words of channel c */
         uint32_t* park = MODE == L3_MODE_HWC
-                             ? reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(&parked[buf][0][0][0]) +
+                             ? reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(&parked[buf][0]) +
                                                            lane * (12 * NW) + c)
-                             : &parked[buf][0][c][lane * NW];
+                             : &parked[buf][c * QW + lane * NW];
         const uint32_t w_first = w;
         do_row(park, y0 + r);
         if (!DIRECT && LATE_BARRIER && r > 0) {
@@ -703,7 +773,7 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
     if (wmax > 8) flags |= L3_STATUS_BAD_WIDTH;
     /* bitpos is one (non-existent) row past the end: step back over it */
     if (bitpos - 12 - pw * w > endbit) flags |= L3_STATUS_OVERRUN;
-    if (!active) flags = 0;
+    if (!at.active) flags = 0;
     if (d.units == 1) {
         /* An image that is one workgroup's (up to 8, 4 or 2 patches) has no other writer of its
          * status word: it is stored whole, and a call with only such images needs no kernel
@@ -1080,13 +1150,15 @@ l3_status run_batch(l3_ctx* ctx, const l3_item* items, const l3_crop* crops, int
         /* the workgroups ahead of the launch's last round (see decode_unit's priorities) */
         const uint32_t last_round = ctx->resident_workgroups;
         const auto top_below = [last_round](uint32_t grid) { return grid > last_round ? grid - last_round : 0u; };
+        const KernelChoice choice = pick_kernel(kClasses[k], mode);
+        const uint32_t grid = in_args ? grid_for((uint64_t)count) : 0u;
         if (in_args && count <= kArgDescsSmall) {
             DescPack<kArgDescsSmall> pack;
             std::memcpy(pack.d, stage + class_begin[k], (size_t)count * sizeof(L3ImageDesc));
             uint32_t count_arg = (uint32_t)count;
-            uint32_t top_arg = top_below(grid_for((uint64_t)count));
+            uint32_t top_arg = top_below(grid);
             void* kernel_args[9] = {&pack, &gx_arg, &count_arg, &d_status, &crop_w, &crop_h, &top_arg, &table, tail};
-            if (hipLaunchKernel(pick_kernel(kClasses[k], mode).args_small, dim3(grid_for((uint64_t)count)),
+            if (hipLaunchKernel(choice.args_small, dim3(grid),
                                 dim3(kBlockThreads), kernel_args, 0, stream) != hipSuccess)
                 return L3_ERR_DEVICE;
             continue;
@@ -1096,15 +1168,15 @@ l3_status run_batch(l3_ctx* ctx, const l3_item* items, const l3_crop* crops, int
              * (which has kArgDescs spare entries behind the last descriptor), so that the
              * block is copied once, by the launch, and never sits on the stack */
             uint32_t count_arg = (uint32_t)count;
-            uint32_t top_arg = top_below(grid_for((uint64_t)count));
+            uint32_t top_arg = top_below(grid);
             void* kernel_args[9] = {stage + class_begin[k], &gx_arg, &count_arg, &d_status,
                                     &crop_w, &crop_h, &top_arg, &table, tail};
-            if (hipLaunchKernel(pick_kernel(kClasses[k], mode).args, dim3(grid_for((uint64_t)count)),
+            if (hipLaunchKernel(choice.args, dim3(grid),
                                 dim3(kBlockThreads), kernel_args, 0, stream) != hipSuccess)
                 return L3_ERR_DEVICE;
             continue;
         }
-        decode_kernel_t kern = pick_kernel(kClasses[k], mode).table;
+        decode_kernel_t kern = choice.table;
         if (gx > 0x7FFFFF00u) return L3_ERR_UNSUPPORTED;     /* more units in one image than a grid holds */
         const int per_launch = (int)std::min<uint64_t>((uint64_t)count, 0x7FFFFF00ull / gx);
         for (int first = 0; first < count; first += per_launch) {
