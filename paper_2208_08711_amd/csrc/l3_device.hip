@@ -221,7 +221,7 @@ __device__ __forceinline__ StreamPlace locate_stream(const L3ImageDesc& d, const
  * worked out once.  The scalars are pinned in registers: left to itself the compiler reloads them
  * from the argument segment after every barrier, and the wave waits for the scalar load each
  * period. */
-template <int N, int NW, int MODE>
+template <int N, int NW, int MODE, bool PLANAR = false>
 struct RowWriter {
     static constexpr int QW = 64 * NW;
     uint64_t out_base, out_row_stride, out_plane_stride;
@@ -319,12 +319,13 @@ struct RowWriter {
             const uint32_t q = lane + 64 * pass;
             const uint32_t nvalid = word_valid[pass];
             /* interleaved mode: 12 bytes R0 G0 B0 R1 G1 B1 R2 G2 B2 R3 G3 B3 per word q;
-             * planar mode: one word of 4 pixels per channel */
+             * planar modes, and rows parked in planes: one word of 4 pixels per channel */
+            constexpr bool TRIPLES = MODE == L3_MODE_HWC && !PLANAR;
             uint32_t pr = 0, pg = 0, pb = 0;
             if (MODE != L3_MODE_TENSOR) {
-                pr = MODE == L3_MODE_HWC ? src[3 * q] : src[q];
-                pg = MODE == L3_MODE_HWC ? src[3 * q + 1] : src[QW + q];
-                pb = MODE == L3_MODE_HWC ? src[3 * q + 2] : src[2 * QW + q];
+                pr = TRIPLES ? src[3 * q] : src[q];
+                pg = TRIPLES ? src[3 * q + 1] : src[QW + q];
+                pb = TRIPLES ? src[3 * q + 2] : src[2 * QW + q];
             }
             if (MODE == L3_MODE_HWC) {
                 /* row start: scalar arithmetic; the lane's 32-bit column offset goes into the
@@ -333,7 +334,12 @@ struct RowWriter {
                 L3_KEEP_VGPR(word_off[pass]);
                 const uint32_t column = word_off[pass];
                 global_u8* row = reinterpret_cast<global_u8*>((uintptr_t)(out_base + (uint64_t)y * out_row_stride));
-                const uint32_t o0 = pr, o1 = pg, o2 = pb;
+                uint32_t o0 = pr, o1 = pg, o2 = pb;
+                if (PLANAR) {
+                    o0 = __builtin_amdgcn_perm(pb, __builtin_amdgcn_perm(pg, pr, 0x010C0400u), 0x03040100u);   /* R0 G0 B0 R1 */
+                    o1 = __builtin_amdgcn_perm(pr, __builtin_amdgcn_perm(pb, pg, 0x020C0501u), 0x03060100u);   /* G1 B1 R2 G2 */
+                    o2 = __builtin_amdgcn_perm(pg, __builtin_amdgcn_perm(pr, pb, 0x030C0702u), 0x03070100u);   /* B2 R3 G3 B3 */
+                }
                 if (wave_whole || nvalid == 4) {
                     const u32x3 v = {o0, o1, o2};
                     __builtin_nontemporal_store(v, reinterpret_cast<global_u32x3_any*>(row + column));
@@ -793,6 +799,234 @@ __device__ __forceinline__ void decode_unit(const L3ImageDesc& d, const uint32_t
     }
 }
 
+/* ---- the split kernel ------------------------------------------------------- */
+
+/* The same unit of work (three channels of TPW patches) by eight or nine waves instead of three, for
+ * launches that leave the SIMDs with little to do.  There a row costs what its instructions cost one
+ * behind the other in one wave: record -> place of the deltas -> deltas -> pixels -> record of the next
+ * row.  Only two of these chains are really serial, the record walk (a row begins where the one before
+ * ends) and the filter (a row needs the pixels above), and neither needs the other.  So three waves walk
+ * the records of a channel each and turn deltas into values (base + delta), three run the filter over the
+ * values, and two or three write the decoded rows out, each kind a period of P rows behind the one before,
+ * handed over through LDS at one barrier a period.  What bounds it then is the walk, about 260 cycles a row
+ * of one workgroup a CU: five dependent steps and an LDS read, and its share of the LDS, which takes an
+ * instruction of any wave of the CU every four cycles (which is why rows are parked in planes, one write a
+ * lane, and put together by the writing waves: four byte writes a lane cost 4 images of 2048x1024 1.2 us).
+ * One workgroup of three waves against this: split_up_to.  Measured slower: the walk in a wave of its
+ * own for all streams (18.9 -> 23.5 us for those 4 images; a record's way through LDS costs more
+ * than it saves), periods of 3 or 4 rows (24.3 / 19.2), the filter or the walk at a higher priority (23.3 / 21.5
+ * where equal ones gave 21.5). */
+template <int N>
+struct SplitGeom {
+    static constexpr int LPT = N / 4, TPW = 64 / LPT;
+    static constexpr int P = 6;                      /* rows of a period */
+    static constexpr int CHUNK = 8 * N, RING = 16 * N, RING_WORDS = RING / 4 + 4;   /* as in Geom */
+    static constexpr int ROW_MAX = N + 3;
+    /* what is read beyond the first record of a period before the next chance to top the ring up:
+     * P - 1 rows and the record behind them */
+    static constexpr int AHEAD = (P - 1) * ROW_MAX + 12;
+    static constexpr int EARLY = RING - CHUNK - ROW_MAX - 8 - AHEAD;     /* see Geom */
+    static_assert(CHUNK == 2 * LPT * 16, "two granules per lane and refill");
+    static_assert(CHUNK >= P * ROW_MAX, "refill keeps up with the longest rows");
+    static_assert(CHUNK >= 15 + AHEAD, "first chunk lasts until the first top-up");
+    static_assert(EARLY >= 1, "a refill that is due is also allowed");
+};
+template <int MODE> constexpr int split_writers() { return MODE == L3_MODE_TENSOR ? 3 : 2; }
+template <int MODE> constexpr int split_threads() { return 64 * (6 + split_writers<MODE>()); }
+
+template <int N, int MODE>
+__device__ __forceinline__ void decode_unit_split(const L3ImageDesc& d, const uint32_t unit,
+                                                  uint32_t* __restrict__ status, const uint32_t crop_w,
+                                                  const uint32_t crop_h, const uint16_t* __restrict__ lut) {
+    using G = SplitGeom<N>;
+    constexpr int LPT = G::LPT, TPW = G::TPW, P = G::P, CHUNK = G::CHUNK, RING = G::RING;
+    constexpr uint32_t WRITERS = split_writers<MODE>();
+
+    __shared__ __attribute__((aligned(16))) uint32_t rings[3][TPW][G::RING_WORDS];
+    __shared__ u32x2 values[2][P][3][64];              /* [buffer][row][channel][lane]: pixels (0, 2), (1, 3) */
+    constexpr int SPAN = P * 3 * 64 + (MODE == L3_MODE_TENSOR ? 4 : 0);      /* as in decode_unit */
+    __shared__ uint32_t parked[2][SPAN];              /* [buffer][row, channel, lane]: pixels 0 1 2 3 */
+    __shared__ uint16_t s_lut[MODE == L3_MODE_TENSOR ? 768 : 2];
+
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (unit >= d.units) return;                                   /* whole workgroup */
+
+    const uint32_t g = lane / LPT, xl = lane % LPT, xpix = xl * 4;
+    const UnitPlace at = place_unit<N, TPW, MODE>(d, unit, g);
+    const uint32_t y0 = at.ty_base * N;
+    const uint32_t pw = min((uint32_t)N, d.width - at.tx * N);
+    uint32_t ph = min((uint32_t)N, d.height - y0);
+    if (MODE == L3_MODE_TENSOR) ph = min(ph, (uint32_t)d.crop_y0 + crop_h - y0);
+    const uint32_t whole = ph / P, rest = ph - whole * P, periods = whole + (rest ? 1u : 0u);
+
+    if (wave < 3) {
+        /* ---- records and deltas of channel c */
+        const uint32_t c = wave;
+        uint32_t flags = 0;
+        const StreamPlace stream = locate_stream(d, c, at.tx, at.ty, flags);
+        const uint8_t* const origin = stream.origin;
+        const uint32_t limit = stream.limit;
+        uint32_t* const ring = rings[c][g];
+        u32x4 pf[2], first[2];          /* the first two chunks travel together */
+#pragma unroll
+        for (int t = 0; t < 2; ++t) first[t] = load_granule(origin, (t * LPT + xl) * 16, limit);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) pf[t] = load_granule(origin, CHUNK + (t * LPT + xl) * 16, limit);
+        uint32_t fill = xl * 16;        /* this lane's first granule of the next chunk for the ring, as in decode_unit */
+        auto put = [&](const u32x4 (&chunk)[2]) {
+            const uint32_t idx = fill & (RING - 1);
+            uint8_t* const cell = reinterpret_cast<uint8_t*>(ring) + idx;
+            *reinterpret_cast<u32x4*>(cell) = chunk[0];
+            *reinterpret_cast<u32x4*>(cell + CHUNK / 2) = chunk[1];
+            if (idx == 0) *reinterpret_cast<u32x4*>(cell + RING) = chunk[0];
+            fill += CHUNK;
+        };
+        put(first);
+        uint32_t reach = (fill - (G::AHEAD + xl * 16)) * 8;     /* as in decode_unit */
+        wave_lds_fence();
+
+        uint32_t bitpos = stream.bitpos, w, w2, K, base2, xbit, xwhere, hwhere, wmax = 0;
+        const uint32_t ring_lds = lds_address_of(ring), word_bits = ring_word_bits<RING>();
+        uint32_t four = 0x00040004u;
+        L3_KEEP_SGPR(four);
+        auto open_row = [&](RingWords hw) {      /* as in decode_unit */
+            const uint32_t hdr = ring_align(hw, bitpos);
+            w = hdr & 15u;
+            const uint32_t dbit = bitpos + 12;
+            bitpos = dbit + pw * w;
+            hwhere = ring_where(ring_lds, bitpos, word_bits);
+            xbit = dbit + xpix * w;
+            xwhere = ring_where(ring_lds, xbit, word_bits);
+            base2 = low_b16_lshr_twice(four, hdr);
+            w2 = w + w;
+            K = 0xFFFFFFFFu << w;
+        };
+        open_row(ring_fetch(ring_where(ring_lds, bitpos, word_bits)));
+        RingWords hw = ring_fetch(hwhere), xw = ring_fetch(xwhere);
+        /* One row: the next row's record and the open row's deltas have travelled since the step before;
+         * the next row is opened and its words are asked for, first those of the walk, then the open
+         * row is worked on. */
+        auto step = [&](u32x2* out, bool top_up) {
+            const RingWords x = xw;
+            const uint32_t x_bit = xbit, x_w = w, x_w2 = w2, x_K = K, x_base2 = base2;
+            open_row(hw);
+            if (top_up) {
+                /* bitpos is the first record of the next period; otherwise as in decode_unit */
+                if (wave_any(reach < bitpos) && reach < bitpos + 8 * (G::EARLY - 1)) {
+                    put(pf);
+                    reach += 8 * CHUNK;
+                    if (fill < limit)
+                        pf[0] = *reinterpret_cast<global_const_u32x4*>((uintptr_t)(origin + fill));
+                    if (fill + CHUNK / 2 < limit)
+                        pf[1] = *reinterpret_cast<global_const_u32x4*>((uintptr_t)(origin + fill + CHUNK / 2));
+                }
+                wave_lds_fence();
+            }
+            hw = ring_fetch(hwhere);
+            __builtin_amdgcn_sched_barrier(0);
+            xw = ring_fetch(xwhere);
+            __builtin_amdgcn_sched_barrier(0);
+            wmax = max(wmax, x_w);
+            /* the four deltas of the lane as in decode_unit */
+            const uint32_t bits = ring_align(x, x_bit);
+            const uint32_t f01 = __builtin_amdgcn_ubfe(bits, 0, x_w2);
+            const uint32_t f23 = __builtin_amdgcn_ubfe(bits, x_w2, x_w2);
+            const uint32_t Y = f01 | (f23 << 16);
+            const uint32_t B = pk_lshr_b16_by_low(x_w, Y);
+            const uint32_t A = pk_mad_u16_by_low(B, x_K, Y);
+            *out = u32x2{A + x_base2, B + x_base2};
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        uint32_t buf = 0;
+        for (uint32_t k = 0; k < whole; ++k, buf ^= 1u) {      /* whole periods without a test in them */
+            u32x2* const out = &values[buf][0][c][lane];
+            if (k) __syncthreads();
+#pragma unroll
+            for (int i = 0; i < P; ++i) step(out + i * 3 * 64, i == P - 2);
+        }
+        if (rest) {
+            u32x2* const out = &values[buf][0][c][lane];
+            if (whole) __syncthreads();
+            for (uint32_t i = 0; i < rest; ++i) step(out + i * 3 * 64, false);
+        }
+        if (wmax > 8) flags |= L3_STATUS_BAD_WIDTH;
+        /* bitpos is one (non-existent) row past the end: step back over it */
+        if (bitpos - 12 - pw * w > stream.endbit) flags |= L3_STATUS_OVERRUN;
+        if (!at.active) flags = 0;
+        if (d.units > 1) {
+            if (flags && status) atomicOr(&status[d.status_index], flags);
+        } else {
+            /* the only writer of its image's word stores it whole, as in decode_unit: the three
+             * waves' words meet in their own rings, which nothing reads any more */
+            uint32_t word = 0;
+#pragma unroll
+            for (uint32_t bit = L3_STATUS_BAD_WIDTH; bit <= L3_STATUS_BAD_OFFSET; bit <<= 1)
+                word |= wave_any((flags & bit) != 0) ? bit : 0u;
+            wave_lds_fence();
+            if (lane == 0) rings[c][0][0] = word;
+        }
+        __syncthreads();
+        if (d.units == 1 && status && threadIdx.x == 0)
+            status[d.status_index] = rings[0][0][0] | rings[1][0][0] | rings[2][0][0];
+        __syncthreads();
+    } else if (wave < 6) {
+        /* ---- the inverse filter of channel c, a period behind */
+        const uint32_t c = wave - 3;
+        uint32_t least[2], most[2];
+        predict_limits(xpix, pw, least[0], most[0]);
+        predict_limits(xpix + 1, pw, least[1], most[1]);
+        uint32_t pixel_bits = 0x00FF00FFu, pixel_bias = kPixelBias;
+        L3_KEEP_VGPR(pixel_bits);
+        L3_KEEP_SGPR(pixel_bias);
+        uint32_t prev[2] = {kPixelBias, kPixelBias};
+        auto step = [&](u32x2 v, uint32_t buf, uint32_t i) {
+            const uint32_t from_left = dpp_from_lower_lane(prev[1]), from_right = dpp_from_upper_lane(prev[0]);
+            const uint32_t TL[2] = {__builtin_amdgcn_alignbit(prev[1], from_left, 16), prev[0]};
+            const uint32_t TR[2] = {prev[1], __builtin_amdgcn_alignbit(from_right, prev[0], 16)};
+            uint32_t pred[2];
+            predict_pairs_biased<2>(TL, TR, prev, least, most, pred);
+            prev[0] = ((v.x + pred[0]) & pixel_bits) | pixel_bias;
+            prev[1] = ((v.y + pred[1]) & pixel_bits) | pixel_bias;
+            parked[buf][(i * 3 + c) * 64 + lane] = __builtin_amdgcn_perm(prev[1], prev[0], 0x06020400u);
+        };
+        uint32_t buf = 0;
+        for (uint32_t k = 0; k < whole; ++k, buf ^= 1u) {
+            __syncthreads();
+            const u32x2* const in = &values[buf][0][c][lane];
+            u32x2 v[P];
+#pragma unroll
+            for (int i = 0; i < P; ++i) v[i] = in[i * 3 * 64];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < P; ++i) step(v[i], buf, (uint32_t)i);
+        }
+        if (rest) {
+            __syncthreads();
+            const u32x2* const in = &values[buf][0][c][lane];
+            for (uint32_t i = 0; i < rest; ++i) step(in[i * 3 * 64], buf, i);
+        }
+        __syncthreads();
+    } else {
+        /* ---- the write-out, another period behind: the waves take the rows in turn */
+        const uint32_t me = wave - 6;
+        if (MODE == L3_MODE_TENSOR) {
+#pragma unroll
+            for (uint32_t k = 0; k < 768 / (64 * split_writers<L3_MODE_TENSOR>()); ++k) {
+                const uint32_t j = me * 64 + lane + k * 64 * WRITERS;
+                s_lut[j] = lut[j];
+            }
+        }
+        RowWriter<N, 1, MODE, true> writer(d, at, xl, lane, crop_w, crop_h, s_lut);
+        __syncthreads();
+        for (uint32_t k = 0, buf = 0; k < periods; ++k, buf ^= 1u) {
+            __syncthreads();
+            const uint32_t rows = k < whole ? (uint32_t)P : rest;
+            for (uint32_t i = me; i < rows; i += WRITERS) writer.write_row(&parked[buf][i * 3 * 64], y0 + k * P + i);
+        }
+    }
+}
+
 /* How old a workgroup of the launch's last round is among the workgroups of its CU, 0 (oldest)
  * to 7: workgroups are handed out in the order of their numbers, to the XCDs in turn and inside
  * an XCD to its 32 CUs in turn, so the n-th workgroup of an XCD is about the (n / 32)-th of
@@ -840,6 +1074,16 @@ __global__ __launch_bounds__(kBlockThreads) void l3_decode_kernel_args(
     if (!take_work(units_per_image, images, image, unit)) return;
     decode_unit<N, PPL, MODE>(pack.d[image], unit, status, crop_w, crop_h, blockIdx.x < top_priority_below,
                               age_rank_of(top_priority_below), table_of<MODE>(lut, tail));
+}
+
+template <int N, int MODE, int CAP>
+__global__ __launch_bounds__(split_threads<MODE>()) void l3_decode_split_kernel_args(
+    const DescPack<CAP> pack, uint32_t units_per_image, uint32_t images, uint32_t* __restrict__ status,
+    uint32_t crop_w, uint32_t crop_h, uint32_t top_priority_below, const uint16_t* __restrict__ lut,
+    const typename TailFor<MODE>::type tail) {
+    uint32_t image, unit;
+    if (!take_work(units_per_image, images, image, unit)) return;
+    decode_unit_split<N, MODE>(pack.d[image], unit, status, crop_w, crop_h, table_of<MODE>(lut, tail));
 }
 
 /* The table in device memory, for the call that keeps one there. */
@@ -905,6 +1149,9 @@ struct KernelChoice {
     decode_kernel_t table;        /* descriptors in a device table */
     decode_kernel_args_small_t args_small;   /* descriptors in the kernel arguments, up to 32 */
     decode_kernel_args_t args;               /* up to 256 */
+    decode_kernel_args_small_t split_small;  /* decode_unit_split, descriptors in the kernel arguments, up to 32 */
+    decode_kernel_args_t split;              /* up to 256 */
+    uint32_t split_threads;
     int tiles_per_wave;
 };
 
@@ -917,16 +1164,25 @@ KernelChoice choice_for_mode(int mode) {
             k.table = reinterpret_cast<const void*>(&l3_decode_kernel<N, PPL, L3_MODE_HWC>);
             k.args_small = reinterpret_cast<const void*>(&l3_decode_kernel_args<N, PPL, L3_MODE_HWC, kArgDescsSmall>);
             k.args = reinterpret_cast<const void*>(&l3_decode_kernel_args<N, PPL, L3_MODE_HWC, kArgDescs>);
+            k.split_small = reinterpret_cast<const void*>(&l3_decode_split_kernel_args<N, L3_MODE_HWC, kArgDescsSmall>);
+            k.split = reinterpret_cast<const void*>(&l3_decode_split_kernel_args<N, L3_MODE_HWC, kArgDescs>);
+            k.split_threads = split_threads<L3_MODE_HWC>();
             break;
         case L3_MODE_CHW:
             k.table = reinterpret_cast<const void*>(&l3_decode_kernel<N, PPL, L3_MODE_CHW>);
             k.args_small = reinterpret_cast<const void*>(&l3_decode_kernel_args<N, PPL, L3_MODE_CHW, kArgDescsSmall>);
             k.args = reinterpret_cast<const void*>(&l3_decode_kernel_args<N, PPL, L3_MODE_CHW, kArgDescs>);
+            k.split_small = reinterpret_cast<const void*>(&l3_decode_split_kernel_args<N, L3_MODE_CHW, kArgDescsSmall>);
+            k.split = reinterpret_cast<const void*>(&l3_decode_split_kernel_args<N, L3_MODE_CHW, kArgDescs>);
+            k.split_threads = split_threads<L3_MODE_CHW>();
             break;
         default:
             k.table = reinterpret_cast<const void*>(&l3_decode_kernel<N, PPL, L3_MODE_TENSOR>);
             k.args_small = reinterpret_cast<const void*>(&l3_decode_kernel_args<N, PPL, L3_MODE_TENSOR, kArgDescsSmall>);
             k.args = reinterpret_cast<const void*>(&l3_decode_kernel_args<N, PPL, L3_MODE_TENSOR, kArgDescs>);
+            k.split_small = reinterpret_cast<const void*>(&l3_decode_split_kernel_args<N, L3_MODE_TENSOR, kArgDescsSmall>);
+            k.split = reinterpret_cast<const void*>(&l3_decode_split_kernel_args<N, L3_MODE_TENSOR, kArgDescs>);
+            k.split_threads = split_threads<L3_MODE_TENSOR>();
             break;
     }
     return k;
@@ -1001,6 +1257,18 @@ l3_status check_item(const l3_item& it, L3ImageDesc* d) {
     d->header_bytes = (uint32_t)f.header_bytes;
     return L3_OK;
 }
+
+/* Launches of at most two workgroups a CU take the split kernels, as far as their descriptors travel in
+ * the arguments (more than 256 images are more workgroups than that in all but the smallest sizes).
+ * Beyond, the waves of three workgroups fill the SIMDs' issue slots and the hand-over costs more than the
+ * shorter rows give.  One workgroup for all against split, us a call on one card (units of work in brackets):
+ *   interleaved  N = 128, 4 of 2048x1024 (256) 33.2 / 19.5, 8 (512) 37.7 / 31.2, 10 (640) 43.2 / 40.8, 16 (1024) 48.7 / 51.4;
+ *                N = 64, 1 of 1920x1080 (128) 19.6 / 13.0, 4 (512) 21.7 / 17.7, 6 (768) 24.5 / 22.8, 8 (1024) 28.0 / 29.8;
+ *                N = 32, 8 photographs (164) 13.5 / 11.4, 24 (492) 15.8 / 15.1, 32 (656) 16.1 / 15.6, 48 (984) 18.7 / 20.6
+ *   planar       N = 128 (256) 29.5 / 19.2, (512) 34.5 / 31.0, (768) 41.2 / 41.4; N = 64 (512) 21.7 / 18.0, (768) 24.7 / 22.5
+ *   fused        N = 128, 768x768 of 2048x1024 (224) 42.2 / 28.1, (448) 47.1 / 38.2, (672) 53.6 / 55.0;
+ *                N = 64, 512x512 (216) 24.0 / 17.6, (864) 32.7 / 37.0; N = 32, 224x224 (512) 16.3 / 14.7, (768) 18.2 / 20.1 */
+uint32_t split_up_to(const l3_ctx* ctx) { return ctx->resident_workgroups / 4; }
 
 l3_status run_batch(l3_ctx* ctx, const l3_item* items, const l3_crop* crops, int n, int mode,
                     uint32_t crop_w, uint32_t crop_h, const float* mean, const float* stdv,
@@ -1152,14 +1420,15 @@ l3_status run_batch(l3_ctx* ctx, const l3_item* items, const l3_crop* crops, int
         const auto top_below = [last_round](uint32_t grid) { return grid > last_round ? grid - last_round : 0u; };
         const KernelChoice choice = pick_kernel(kClasses[k], mode);
         const uint32_t grid = in_args ? grid_for((uint64_t)count) : 0u;
+        const bool split = in_args && grid <= split_up_to(ctx);
         if (in_args && count <= kArgDescsSmall) {
             DescPack<kArgDescsSmall> pack;
             std::memcpy(pack.d, stage + class_begin[k], (size_t)count * sizeof(L3ImageDesc));
             uint32_t count_arg = (uint32_t)count;
             uint32_t top_arg = top_below(grid);
             void* kernel_args[9] = {&pack, &gx_arg, &count_arg, &d_status, &crop_w, &crop_h, &top_arg, &table, tail};
-            if (hipLaunchKernel(choice.args_small, dim3(grid),
-                                dim3(kBlockThreads), kernel_args, 0, stream) != hipSuccess)
+            if (hipLaunchKernel(split ? choice.split_small : choice.args_small, dim3(grid),
+                                dim3(split ? choice.split_threads : kBlockThreads), kernel_args, 0, stream) != hipSuccess)
                 return L3_ERR_DEVICE;
             continue;
         }
@@ -1171,8 +1440,8 @@ l3_status run_batch(l3_ctx* ctx, const l3_item* items, const l3_crop* crops, int
             uint32_t top_arg = top_below(grid);
             void* kernel_args[9] = {stage + class_begin[k], &gx_arg, &count_arg, &d_status,
                                     &crop_w, &crop_h, &top_arg, &table, tail};
-            if (hipLaunchKernel(choice.args, dim3(grid),
-                                dim3(kBlockThreads), kernel_args, 0, stream) != hipSuccess)
+            if (hipLaunchKernel(split ? choice.split : choice.args, dim3(grid),
+                                dim3(split ? choice.split_threads : kBlockThreads), kernel_args, 0, stream) != hipSuccess)
                 return L3_ERR_DEVICE;
             continue;
         }

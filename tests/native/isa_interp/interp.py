@@ -462,6 +462,7 @@ class Emu:
     def i_s_cmp_eq_i32(self, w, ins, a, m): self._scmp(w, a, lambda x, y: x == y, True)
     def i_s_cmp_lg_i32(self, w, ins, a, m): self._scmp(w, a, lambda x, y: x != y, True)
     def i_s_cmpk_lt_u32(self, w, ins, a, m): w.scc = int(self.rs(w, a[0]) < (parse_int(a[1]) & 0xFFFF))
+    def i_s_cmpk_gt_u32(self, w, ins, a, m): w.scc = int(self.rs(w, a[0]) > (parse_int(a[1]) & 0xFFFF))
     def i_s_bitcmp1_b32(self, w, ins, a, m): w.scc = (self.rs(w, a[0]) >> (self.rs(w, a[1]) & 31)) & 1
     def i_s_bitcmp0_b32(self, w, ins, a, m): w.scc = 1 - ((self.rs(w, a[0]) >> (self.rs(w, a[1]) & 31)) & 1)
     def i_s_cmp_eq_u64(self, w, ins, a, m): w.scc = int(self.rs64(w, a[0]) == self.rs64(w, a[1]))
@@ -778,10 +779,29 @@ class Emu:
             w.v[r][i] = struct.unpack("<I", self.lds_read(int(addr[i]) + o0, 4))[0]
             w.v[r + 1][i] = struct.unpack("<I", self.lds_read(int(addr[i]) + o1, 4))[0]
 
+    def i_ds_read2st64_b64(self, w, ins, a, m):
+        r, _ = self.vreg(a[0])
+        addr = self.rv(w, a[1])
+        offsets = [512 * parse_int(m.get(o, "0")) for o in ("offset0", "offset1")]
+        for i in self._lanes(w):
+            for k, off in enumerate(offsets):
+                ad = int(addr[i]) + off
+                if ad % 8:
+                    raise Fault("misaligned LDS read of 8 bytes at %d" % ad)
+                w.v[r + 2 * k][i], w.v[r + 2 * k + 1][i] = struct.unpack("<2I", self.lds_read(ad, 8))
+
     def i_ds_write2_b32(self, w, ins, a, m):
         addr = self.rv(w, a[0])
         v0, v1 = self.rv(w, a[1]), self.rv(w, a[2])
         o0, o1 = 4 * parse_int(m.get("offset0", "0")), 4 * parse_int(m.get("offset1", "0"))
+        for i in self._lanes(w):
+            self.lds_write(int(addr[i]) + o0, struct.pack("<I", int(v0[i])))
+            self.lds_write(int(addr[i]) + o1, struct.pack("<I", int(v1[i])))
+
+    def i_ds_write2st64_b32(self, w, ins, a, m):
+        addr = self.rv(w, a[0])
+        v0, v1 = self.rv(w, a[1]), self.rv(w, a[2])
+        o0, o1 = 256 * parse_int(m.get("offset0", "0")), 256 * parse_int(m.get("offset1", "0"))
         for i in self._lanes(w):
             self.lds_write(int(addr[i]) + o0, struct.pack("<I", int(v0[i])))
             self.lds_write(int(addr[i]) + o1, struct.pack("<I", int(v1[i])))

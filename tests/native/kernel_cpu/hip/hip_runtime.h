@@ -183,7 +183,13 @@ inline hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 inline hipError_t hipSetDevice(int) { return hipSuccess; }
 inline hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
 enum hipDeviceAttribute_t { hipDeviceAttributeMultiprocessorCount = 63 };
-inline hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 1; return hipSuccess; }   /* one CU: launches of more than 8 workgroups have early rounds */
+/* one CU: launches of more than 8 workgroups have early rounds; with L3CPU_CUS=<n> in the
+ * environment n, so that small launches take the kernels that are for launches of few workgroups a CU */
+inline hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) {
+    const char* e = std::getenv("L3CPU_CUS");
+    *v = e ? std::atoi(e) : 1;
+    return hipSuccess;
+}
 inline hipError_t hipMalloc(void** p, size_t n) {
     *p = std::malloc(n ? n : 1);
     if (*p) l3cpu::regions()[*p] = n;

@@ -33,7 +33,7 @@ void l3_ablation_state_free(L3AblationState*) {}
 namespace {
 
 /* what a recorded launch says about its kernel: patch size, mode, how the descriptors travel
- * (0 device table, 1 up to 32 in the arguments, 2 up to 256), and the sizes of its first and
+ * (0 device table, 1 up to 32 in the arguments, 2 up to 256; 3 and 4 as 1 and 2, the split kernels), and the sizes of its first and
  * last argument (the others are gx, count, status, crop_w, crop_h, top_priority_below, table pointer) */
 struct KernelFacts { int n, mode, kind; size_t first_bytes, tail_bytes; };
 std::map<const void*, KernelFacts> g_facts;
@@ -75,6 +75,19 @@ void record_launch(const char* dir, const void* kernel, dim3 grid, dim3 block, v
     std::fclose(f);
 }
 
+template <int N, int MODE, int CAP>
+void register_split(int kind) {
+    typedef typename TailFor<MODE>::type Tail;
+    const void* kernel = reinterpret_cast<const void*>(&l3_decode_split_kernel_args<N, MODE, CAP>);
+    g_facts[kernel] = {N, MODE, kind, sizeof(DescPack<CAP>), sizeof(Tail)};
+    l3cpu::registry()[kernel] = [](void** a) {
+        l3_decode_split_kernel_args<N, MODE, CAP>(
+            *static_cast<DescPack<CAP>*>(a[0]), *static_cast<uint32_t*>(a[1]), *static_cast<uint32_t*>(a[2]),
+            *static_cast<uint32_t**>(a[3]), *static_cast<uint32_t*>(a[4]), *static_cast<uint32_t*>(a[5]),
+            *static_cast<uint32_t*>(a[6]), *static_cast<const uint16_t**>(a[7]), *static_cast<Tail*>(a[8]));
+    };
+}
+
 template <int N, int MODE>
 void register_kernels() {
     typedef typename TailFor<MODE>::type Tail;
@@ -91,6 +104,8 @@ void register_kernels() {
                                      *static_cast<uint32_t*>(a[6]), *static_cast<const uint16_t**>(a[7]),
                                      *static_cast<Tail*>(a[8]));
     };
+    register_split<N, MODE, kArgDescsSmall>(3);
+    register_split<N, MODE, kArgDescs>(4);
     reg[reinterpret_cast<const void*>(&l3_decode_kernel_args<N, 4, MODE, kArgDescsSmall>)] = [](void** a) {
         l3_decode_kernel_args<N, 4, MODE, kArgDescsSmall>(
             *static_cast<DescPack<kArgDescsSmall>*>(a[0]), *static_cast<uint32_t*>(a[1]),
