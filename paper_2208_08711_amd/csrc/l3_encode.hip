@@ -9,7 +9,7 @@
  * base, minimal width, deltas packed).  Section 4.3: patches concatenated, their
  * offsets recorded in three arrays behind a 13-byte header.
  *
- * Patch sizes 32, 64 and 128 (the ones the paper's rule picks) take two or three kernels:
+ * Patch sizes 32, 64 and 128 (the ones the paper's rule picks) take two or three kernels (few strips: one):
  *   strip    a workgroup of three waves (one per channel) owns a strip of adjacent
  *            patches, 4 pixels per lane as two packed pairs of 16-bit fields: per
  *            four rows it filters, reduces their min and max over the patch's lanes, packs
@@ -21,6 +21,8 @@
  *            addends are all known); only in calls with very many patches or with an image on
  *            the plain route, otherwise the next kernel does this too;
  *   compact  copies every slot to its place in the file.
+ * Calls of few strips take one kernel instead, which shares a strip's rows among waves (the chained
+ * route, if all files have room for the longest stream).
  * Any other patch size up to 128 takes the plain route: measure (one wave per patch
  * and channel walks the rows for the sizes), layout, pack (walks them again and
  * writes the bits).  The forward filter needs no row recurrence: the row above is
@@ -28,6 +30,7 @@
  */
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -261,6 +264,153 @@ __device__ __forceinline__ void rows_to_all_lanes(uint32_t v, uint32_t (&row)[4]
     }
 }
 
+/* What a lane knows of its four pixels, columns 4 xl .. 4 xl + 3 of a patch of pw columns from image
+ * column x0 on (pw = 0: a lane without a patch). */
+struct StripLane {
+    uint32_t xpix, nvalid;          /* the first of the columns; how many exist */
+    /* registers of two 16-bit fields: E = pixels (0, 2), O = pixels (1, 3) */
+    uint32_t validE, validO, keepE, keepO, nowhere;
+    uint32_t least[2], most[2];     /* the predictor's limits: see predict_pairs_biased */
+    /* The lane's 12 bytes of a row.  A lane at the right edge of the image owns fewer than
+     * 4 pixels and must not read past the row: it reads the 12 bytes that END at its last
+     * pixel and shifts them down when it takes them (what then sits above the valid bytes is
+     * masked later).  Only waves with such a lane shift.  A lane without pixels reads the start
+     * of the row, so that no load is conditional.  Images narrower than 4 pixels go byte by
+     * byte; there all pixels are lane 0's. */
+    bool wide, ragged_wave;
+    uint32_t shift, lane_at, row_bytes;
+
+    __device__ __forceinline__ StripLane(uint32_t width, uint32_t x0, uint32_t pw, uint32_t xl) {
+        xpix = 4 * xl;
+        nvalid = pw > xpix ? min(4u, pw - xpix) : 0u;
+        validE = (nvalid > 0 ? 0x0000FFFFu : 0u) | (nvalid > 2 ? 0xFFFF0000u : 0u);
+        validO = (nvalid > 1 ? 0x0000FFFFu : 0u) | (nvalid > 3 ? 0xFFFF0000u : 0u);
+        predict_limits(xpix, pw, least[0], most[0]);
+        predict_limits(xpix + 1, pw, least[1], most[1]);
+        keepE = validE & 0x00FF00FFu;
+        keepO = validO & 0x00FF00FFu;
+        nowhere = ~(validE | validO);       /* fields that neither register has a pixel for */
+        wide = width >= 4;
+        ragged_wave = wide && __builtin_amdgcn_ballot_w64(nvalid != 0 && nvalid != 4) != 0;
+        const uint32_t back = wide && nvalid ? 3 * (4 - nvalid) : 0;              /* bytes to step back: 0, 3, 6, 9 */
+        shift = back;
+        lane_at = nvalid ? (x0 + xpix) * 3 - back : 0u;            /* below 3 * 2^24 */
+        row_bytes = width * 3;
+    }
+
+    /* The residual byte r is looked at as t = r ^ K, K = 0 in the first row (raw,
+     * unsigned) and 0x80 after it (signed byte + 128), so that the unsigned minimum of t
+     * is the row minimum of Section 4.2; what is kept is u = t ^ 0xFF, whose maximum gives
+     * the row minimum.  Fields of pixels that do not exist read 0xFFFF: neither the unsigned
+     * minimum nor the signed maximum takes them.  These are K ^ 0xFF in the fields. */
+    __device__ __forceinline__ void first_row_key(uint32_t& kE, uint32_t& kO) const {
+        kE = ~validE | keepE;
+        kO = ~validO | keepO;
+    }
+    __device__ __forceinline__ void later_row_key(uint32_t& kE, uint32_t& kO) const {
+        kE = ~validE | (keepE & 0x007F007Fu);
+        kO = ~validO | (keepO & 0x007F007Fu);
+    }
+
+    __device__ __forceinline__ u32x3 load(const uint8_t* row) const { return wide ? load_wide(row) : load_narrow(row); }
+    __device__ __forceinline__ u32x3 load_wide(const uint8_t* row) const {
+        uint32_t at = lane_at;
+        L3_KEEP_VGPR(at);      /* stays the load's 32-bit offset */
+        return load_u32x3(reinterpret_cast<global_const_u8*>((uintptr_t)row) + at);
+    }
+    __device__ __forceinline__ u32x3 load_narrow(const uint8_t* row) const {
+        global_const_u8* base = reinterpret_cast<global_const_u8*>((uintptr_t)row);
+        uint32_t b[9];
+#pragma unroll
+        for (uint32_t k = 0; k < 9; ++k) b[k] = base[min(k, row_bytes - 1)];
+        u32x3 v;
+        v.x = b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
+        v.y = b[4] | (b[5] << 8) | (b[6] << 16) | (b[7] << 24);
+        v.z = b[8];
+        return v;
+    }
+    __device__ __forceinline__ void shift_down(u32x3& v) const {
+        const uint32_t words = shift >> 2, bits = (shift & 3u) * 8;
+        const uint32_t a0 = words == 0 ? v.x : (words == 1 ? v.y : v.z);
+        const uint32_t a1 = words == 0 ? v.y : (words == 1 ? v.z : 0u);
+        const uint32_t a2 = words == 0 ? v.z : 0u;
+        v.x = __builtin_amdgcn_alignbit(a1, a0, bits);
+        v.y = __builtin_amdgcn_alignbit(a2, a1, bits);
+        v.z = a2 >> bits;
+    }
+
+    /* Section 4.2 stage 1 on the original row above; leaves u and the lane's own part of the
+     * row's extremes: (minimum of u, ~(maximum of u)), so that both go on as minima. */
+    __device__ __forceinline__ uint32_t filter(const uint32_t (&above)[2], const uint32_t (&cur)[2], uint32_t kE,
+                                               uint32_t kO, uint32_t& uE, uint32_t& uO) const {
+        const uint32_t from_left = dpp_from_lower_lane(above[1]);
+        const uint32_t from_right = dpp_from_upper_lane(above[0]);
+        uint32_t TL[2], TR[2], pred[2];
+        TL[0] = __builtin_amdgcn_alignbit(above[1], from_left, 16);
+        TR[0] = above[1];
+        TL[1] = above[0];
+        TR[1] = __builtin_amdgcn_alignbit(from_right, above[0], 16);
+        predict_pairs_biased<2>(TL, TR, above, least, most, pred);
+        const uint32_t rE = __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, cur[0]) -
+                                                                 __builtin_bit_cast(u16x2, pred[0])));
+        const uint32_t rO = __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, cur[1]) -
+                                                                 __builtin_bit_cast(u16x2, pred[1])));
+        uE = __builtin_amdgcn_bitop3_b32(rE, keepE, kE, 0x6A);           /* (r & keep) ^ k */
+        uO = __builtin_amdgcn_bitop3_b32(rO, keepO, kO, 0x6A);
+        const uint32_t a = pk_min_u16(uE, uO);
+        const uint32_t b = ~pk_max_i16(uE, uO) | nowhere;
+        return pk_min_u16(__builtin_amdgcn_perm(b, a, 0x05040100u),      /* (a.lo, b.lo) */
+                          __builtin_amdgcn_perm(b, a, 0x07060302u));     /* (a.hi, b.hi) */
+    }
+};
+
+/* channel C of pixel i is byte 3 i + C of the lane's 12 bytes; biased as the predictor takes
+ * it (the bias goes again with the subtraction of the prediction) */
+template <int C>
+__device__ __forceinline__ void take_channel(const u32x3 raw, uint32_t pixel_bias, uint32_t (&cur)[2]) {
+    if (C == 0) {
+        cur[0] = __builtin_amdgcn_perm(raw.y, raw.x, 0x0C060C00u);   /* bytes 0, 6 */
+        cur[1] = __builtin_amdgcn_perm(raw.z, raw.x, 0x0C050C03u);   /* bytes 3, 9 */
+    } else if (C == 1) {
+        cur[0] = __builtin_amdgcn_perm(raw.y, raw.x, 0x0C070C01u);   /* bytes 1, 7 */
+        cur[1] = __builtin_amdgcn_perm(raw.z, raw.y, 0x0C060C00u);   /* bytes 4, 10 */
+    } else {
+        cur[0] = __builtin_amdgcn_perm(raw.z, raw.x, 0x0C040C02u);   /* bytes 2, 8 */
+        cur[1] = __builtin_amdgcn_perm(raw.z, raw.y, 0x0C070C01u);   /* bytes 5, 11 */
+    }
+    cur[0] |= pixel_bias;
+    cur[1] |= pixel_bias;
+}
+
+/* Steps 1-2 of stage 2 for four rows at once, from the lanes' parts of their extremes: in every
+ * lane, for row my_row, its largest u in the low half and its width in the high half. */
+template <int LPT>
+__device__ __forceinline__ uint32_t extremes_of_my_row(const uint32_t (&lane_part)[4], uint32_t my_row) {
+    const uint32_t m = patch_min_of_rows<LPT>(lane_part, my_row);
+    const uint32_t umin = m & 0xFFFFu, umax = ((m >> 16) & 0xFFu) ^ 0xFFu;
+    const uint32_t range = (umax - umin) & 0xFFu;        /* masked: lanes without a patch hold no minimum */
+    return umax | (31u - (uint32_t)__builtin_clz(2u * range + 1u)) << 16;
+}
+/* The record of that row: 4-bit width, 8-bit base; K as above. */
+__device__ __forceinline__ uint32_t record_of(uint32_t extremes, uint32_t K) {
+    return (extremes >> 16) | ((((extremes & 0xFFu) ^ 0xFFu) ^ K) << 4);
+}
+
+/* Steps 3-4 of stage 2 for one row, given its largest u in the low half and its width in
+ * the high half: deltas t - tmin = umax - u, 0 where no pixel exists; the lane's four deltas
+ * as one field of 4 w bits.  (d0 | d1 << w, d2 | d3 << w) first, then the lower field moves up to the
+ * upper one (not the upper one down: that takes three instructions more; 32 images of 2048x1024
+ * 172.4 -> 171.6 us with this): the four deltas are then the bits from 16 - 2 w on, below them zeros, and
+ * go to the stream by as much sooner, at bit (xpix + 2) w - 4 behind the start of the row's record, which may be up
+ * to 4 bits ahead of it.  w = 0 shifts a field of zeros. */
+__device__ __forceinline__ uint32_t delta_field(uint32_t extremes, uint32_t uE, uint32_t uO) {
+    const uint32_t w = extremes >> 16;
+    const uint32_t dE = pk_sub_u16_sat_from_low(extremes, uE), dO = pk_sub_u16_sat_from_low(extremes, uO);
+    const uint32_t pair = dE | (dO << w);
+    const uint32_t up_by = (uint32_t)(16 - 2 * (int)w);     /* and nothing in the upper half */
+    return pk_lshl_b16(up_by, pair);
+}
+
 /* One strip: TPW adjacent patches of one patch row, channel C. */
 template <int N, int C>
 __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __restrict__ sizes,
@@ -280,71 +430,21 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
     const uint32_t k = C * patches + ty * d.tiles_x + tx;               /* index in the offset arrays */
     uint8_t* const slot = slots + d.slots_base + (uint64_t)k * G::SLOT;
 
-    /* this lane's 4 pixels: columns 4 xl .. 4 xl + 3 of the patch, nvalid of them exist */
-    const uint32_t xpix = 4 * xl;
-    const uint32_t nvalid = pw > xpix ? min(4u, pw - xpix) : 0u;
+    const StripLane ln(d.width, x0, pw, xl);
     const uint8_t* src = d.rgb + (size_t)y0 * d.row_stride;   /* start of the image row, walks down; scalar */
-
-    /* registers of two 16-bit fields: E = pixels (0, 2), O = pixels (1, 3) */
-    const uint32_t validE = (nvalid > 0 ? 0x0000FFFFu : 0u) | (nvalid > 2 ? 0xFFFF0000u : 0u);
-    const uint32_t validO = (nvalid > 1 ? 0x0000FFFFu : 0u) | (nvalid > 3 ? 0xFFFF0000u : 0u);
-    uint32_t least[2], most[2];              /* the predictor's limits: see predict_pairs_biased */
-    predict_limits(xpix, pw, least[0], most[0]);
-    predict_limits(xpix + 1, pw, least[1], most[1]);
-    const uint32_t keepE = validE & 0x00FF00FFu, keepO = validO & 0x00FF00FFu;
-
-    /* The residual byte r is looked at as t = r ^ K, K = 0 in the first row (raw,
-     * unsigned) and 0x80 after it (signed byte + 128), so that the unsigned minimum of t
-     * is the row minimum of Section 4.2; what is kept is u = t ^ 0xFF, whose maximum gives
-     * the row minimum.  Fields of pixels that do not exist read 0xFFFF: neither the unsigned
-     * minimum nor the signed maximum takes them. */
-    uint32_t kE = ~validE | keepE, kO = ~validO | keepO;                /* K ^ 0xFF = 0xFF */
-    const uint32_t nowhere = ~(validE | validO);    /* fields that neither register has a pixel for */
+    uint32_t kE, kO;
+    ln.first_row_key(kE, kO);
     const uint32_t my_row = reduced_row<LPT>(lane);                     /* see patch_min_of_rows */
     uint32_t krow = my_row == 0 ? 0u : 0x80u;                           /* K of that row in the first period */
 
     uint64_t row_stride = d.row_stride;
     L3_KEEP_SGPR(row_stride);               /* kept in registers, not reloaded every row */
-    /* The lane's 12 bytes of a row.  A lane at the right edge of the image owns fewer than
-     * 4 pixels and must not read past the row: it reads the 12 bytes that END at its last
-     * pixel and shifts them down when it takes them (what then sits above the valid bytes is
-     * masked later).  Only waves with such a lane shift.  A lane without pixels reads the start
-     * of the row, so that no load is conditional.  Images narrower than 4 pixels go byte by
-     * byte; there all pixels are lane 0's. */
-    const bool wide = d.width >= 4;
-    const bool ragged_wave = wide && __builtin_amdgcn_ballot_w64(nvalid != 0 && nvalid != 4) != 0;
-    const uint32_t back = wide && nvalid ? 3 * (4 - nvalid) : 0;              /* bytes to step back: 0, 3, 6, 9 */
-    const uint32_t lane_at = nvalid ? (x0 + xpix) * 3 - back : 0u;            /* below 3 * 2^24 */
-    const uint32_t row_bytes = d.width * 3;
     /* rows first .. first + P - 1 of the patch from `row` on; rows that do not exist (of the
      * last period) repeat the last one */
     u32x3 ahead[P];
     auto load_rows = [&](const uint8_t* row, uint32_t exist) {
 #pragma unroll
-        for (int i = 0; i < P; ++i) {
-            global_const_u8* base = reinterpret_cast<global_const_u8*>((uintptr_t)(row + min((uint32_t)i, exist - 1) * row_stride));
-            if (wide) {
-                uint32_t at = lane_at;
-                L3_KEEP_VGPR(at);      /* stays the load's 32-bit offset */
-                ahead[i] = load_u32x3(base + at);
-            } else {
-                uint32_t b[9];
-#pragma unroll
-                for (uint32_t k = 0; k < 9; ++k) b[k] = base[min(k, row_bytes - 1)];
-                ahead[i].x = b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
-                ahead[i].y = b[4] | (b[5] << 8) | (b[6] << 16) | (b[7] << 24);
-                ahead[i].z = b[8];
-            }
-        }
-    };
-    auto shift_down = [&](u32x3& v) {
-        const uint32_t words = back >> 2, bits = (back & 3u) * 8;
-        const uint32_t a0 = words == 0 ? v.x : (words == 1 ? v.y : v.z);
-        const uint32_t a1 = words == 0 ? v.y : (words == 1 ? v.z : 0u);
-        const uint32_t a2 = words == 0 ? v.z : 0u;
-        v.x = __builtin_amdgcn_alignbit(a1, a0, bits);
-        v.y = __builtin_amdgcn_alignbit(a2, a1, bits);
-        v.z = a2 >> bits;
+        for (int i = 0; i < P; ++i) ahead[i] = ln.load(row + min((uint32_t)i, exist - 1) * row_stride);
     };
 
     uint32_t* const ring = ring_words + g * G::RING_WORDS;
@@ -396,61 +496,12 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
     uint32_t pixel_bias = kPixelBias;
     L3_KEEP_SGPR(pixel_bias);
 
-    /* channel C of pixel i is byte 3 i + C of the lane's 12 bytes; biased as the predictor takes
-     * it (the bias goes again with the subtraction of the prediction) */
-    auto take_channel = [&](const u32x3 raw, uint32_t (&cur)[2]) {
-        if (C == 0) {
-            cur[0] = __builtin_amdgcn_perm(raw.y, raw.x, 0x0C060C00u);   /* bytes 0, 6 */
-            cur[1] = __builtin_amdgcn_perm(raw.z, raw.x, 0x0C050C03u);   /* bytes 3, 9 */
-        } else if (C == 1) {
-            cur[0] = __builtin_amdgcn_perm(raw.y, raw.x, 0x0C070C01u);   /* bytes 1, 7 */
-            cur[1] = __builtin_amdgcn_perm(raw.z, raw.y, 0x0C060C00u);   /* bytes 4, 10 */
-        } else {
-            cur[0] = __builtin_amdgcn_perm(raw.z, raw.x, 0x0C040C02u);   /* bytes 2, 8 */
-            cur[1] = __builtin_amdgcn_perm(raw.z, raw.y, 0x0C070C01u);   /* bytes 5, 11 */
-        }
-        cur[0] |= pixel_bias;
-        cur[1] |= pixel_bias;
-    };
-
-    /* Section 4.2 stage 1 on the original row above; leaves u and the lane's own part of the
-     * row's extremes: (minimum of u, ~(maximum of u)), so that both go on as minima. */
-    auto filter_row = [&](const uint32_t (&above)[2], const uint32_t (&cur)[2], uint32_t& uE, uint32_t& uO) -> uint32_t {
-        const uint32_t from_left = dpp_from_lower_lane(above[1]);
-        const uint32_t from_right = dpp_from_upper_lane(above[0]);
-        uint32_t TL[2], TR[2], pred[2];
-        TL[0] = __builtin_amdgcn_alignbit(above[1], from_left, 16);
-        TR[0] = above[1];
-        TL[1] = above[0];
-        TR[1] = __builtin_amdgcn_alignbit(from_right, above[0], 16);
-        predict_pairs_biased<2>(TL, TR, above, least, most, pred);
-        const uint32_t rE = __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, cur[0]) -
-                                                                 __builtin_bit_cast(u16x2, pred[0])));
-        const uint32_t rO = __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, cur[1]) -
-                                                                 __builtin_bit_cast(u16x2, pred[1])));
-        uE = __builtin_amdgcn_bitop3_b32(rE, keepE, kE, 0x6A);           /* (r & keep) ^ k */
-        uO = __builtin_amdgcn_bitop3_b32(rO, keepO, kO, 0x6A);
-        const uint32_t a = pk_min_u16(uE, uO);
-        const uint32_t b = ~pk_max_i16(uE, uO) | nowhere;
-        return pk_min_u16(__builtin_amdgcn_perm(b, a, 0x05040100u),      /* (a.lo, b.lo) */
-                          __builtin_amdgcn_perm(b, a, 0x07060302u));     /* (a.hi, b.hi) */
-    };
-
-    /* Steps 3-4 of stage 2 for one row, given its largest u in the low half and its width in
-     * the high half: deltas t - tmin = umax - u, 0 where no pixel exists; the lane's four deltas
-     * as one field of 4 w bits into the ring.  Moves rowpos to the next record. */
+    /* packs one row and moves rowpos to the next record */
     auto pack_row = [&](uint32_t extremes, uint32_t uE, uint32_t uO) {
         const uint32_t w = extremes >> 16;
-        const uint32_t dE = pk_sub_u16_sat_from_low(extremes, uE), dO = pk_sub_u16_sat_from_low(extremes, uO);
-        const uint32_t pair = dE | (dO << w);                   /* (d0 | d1 << w, d2 | d3 << w) */
-        /* The lower field moves up to the upper one (not the upper one down: that takes three
-         * instructions more; 32 images of 2048x1024 172.4 -> 171.6 us with this): the four deltas
-         * are then the bits from 16 - 2 w on, below them zeros, and go to the ring by as much
-         * sooner, which may be the word ahead of the stream's first (the ring's last: zeros).
-         * w = 0 shifts a field of zeros. */
-        const uint32_t up_by = (uint32_t)(16 - 2 * (int)w);     /* and nothing in the upper half */
-        const uint32_t group = pk_lshl_b16(up_by, pair);
-        put(group, rowpos - 4 + (xpix + 2) * w); /* lanes without pixels add zeros to their own ring */
+        /* (up to 4 bits ahead of the stream: the ring's last word, zeros)
+         * lanes without pixels add zeros to their own ring */
+        put(delta_field(extremes, uE, uO), rowpos - 4 + (ln.xpix + 2) * w);
         rowpos += 12 + pw * w;
     };
 
@@ -486,13 +537,13 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
             else __builtin_amdgcn_s_setprio(0);
         }
         uint32_t cur[P][2];
-        if (ragged_wave) {
+        if (ln.ragged_wave) {
 #pragma unroll
-            for (int i = 0; i < P; ++i) shift_down(ahead[i]);
+            for (int i = 0; i < P; ++i) ln.shift_down(ahead[i]);
         }
 #pragma unroll
         for (int i = 0; i < P; ++i) {
-            take_channel(ahead[i], cur[i]);
+            take_channel<C>(ahead[i], pixel_bias, cur[i]);
             L3_KEEP_VGPR(cur[i][0]);
             L3_KEEP_VGPR(cur[i][1]);
         }
@@ -502,26 +553,20 @@ __device__ __forceinline__ void encode_strip(const L3EncodeDesc& d, uint32_t* __
         if (r > 0) flush(rowpos >> 7);
 
         uint32_t uE[P], uO[P], lane_part[P], extremes[P];
-        lane_part[0] = filter_row(up, cur[0], uE[0], uO[0]);
-        if (r == 0) {            /* rows after the first are looked at as signed bytes */
-            kE = ~validE | (keepE & 0x007F007Fu);
-            kO = ~validO | (keepO & 0x007F007Fu);
-        }
+        lane_part[0] = ln.filter(up, cur[0], kE, kO, uE[0], uO[0]);
+        if (r == 0) ln.later_row_key(kE, kO);
 #pragma unroll
-        for (int i = 1; i < P; ++i) lane_part[i] = filter_row(cur[i - 1], cur[i], uE[i], uO[i]);
+        for (int i = 1; i < P; ++i) lane_part[i] = ln.filter(cur[i - 1], cur[i], kE, kO, uE[i], uO[i]);
         up[0] = cur[P - 1][0];
         up[1] = cur[P - 1][1];
 
         /* stage 2, steps 1-2, for all rows at once: every lane works on row my_row */
-        const uint32_t m = patch_min_of_rows<LPT>(lane_part, my_row);
-        const uint32_t umin = m & 0xFFFFu, tmin = (m >> 16) & 0xFFu, umax = tmin ^ 0xFFu;
-        const uint32_t range = (umax - umin) & 0xFFu;        /* masked: lanes without a patch hold no minimum */
-        const uint32_t my_w = 31u - (uint32_t)__builtin_clz(2u * range + 1u);
-        const uint32_t my_rec = my_w | ((tmin ^ krow) << 4);
+        const uint32_t mine = extremes_of_my_row<LPT>(lane_part, my_row);
+        const uint32_t my_rec = record_of(mine, krow);
         krow = 0x80u;
         /* a row that does not exist packs nothing: no u is below 0, and its width is 0 */
         const bool exists = my_row < rows;
-        rows_to_all_lanes<LPT>(exists ? umax | (my_w << 16) : 0u, extremes);
+        rows_to_all_lanes<LPT>(exists ? mine : 0u, extremes);
 
         uint32_t my_at = rowpos;
         pack_row(extremes[0], uE[0], uO[0]);
@@ -569,7 +614,18 @@ __global__ __launch_bounds__(192) void l3_encode_strip_kernel_args(const EncodeP
     strip_block<N>(pack.d[blockIdx.y], sizes, slots);
 }
 
-/* The fixed part of the file's header and what the caller is told about the file. */
+/* The fixed part of the file's header. */
+__device__ __forceinline__ void write_fixed_header(const L3EncodeDesc& d) {
+    uint8_t* f = d.file;
+    f[0] = 0x4C; f[1] = 0x33; f[2] = 0x00; f[3] = 0x01;
+    for (int b = 0; b < 4; ++b) {
+        f[4 + b] = (uint8_t)(d.width >> (8 * b));
+        f[8 + b] = (uint8_t)(d.height >> (8 * b));
+    }
+    f[12] = (uint8_t)d.patch;
+}
+
+/* The same where there is room for it, and what the caller is told about the file. */
 __device__ __forceinline__ void write_header(const L3EncodeDesc& d, uint64_t need, uint64_t header,
                                              uint64_t* __restrict__ file_len, uint32_t* __restrict__ status) {
     file_len[d.status_index] = need;
@@ -577,15 +633,7 @@ __device__ __forceinline__ void write_header(const L3EncodeDesc& d, uint64_t nee
     if (need > d.file_cap) st |= 1u;                       /* output capacity too small: nothing packed */
     if (need - header > 0xFFFFFFFFull) st |= 2u;           /* data section beyond 32-bit offsets */
     if (status) status[d.status_index] = st;
-    if (header <= d.file_cap) {
-        uint8_t* f = d.file;
-        f[0] = 0x4C; f[1] = 0x33; f[2] = 0x00; f[3] = 0x01;
-        for (int b = 0; b < 4; ++b) {
-            f[4 + b] = (uint8_t)(d.width >> (8 * b));
-            f[8 + b] = (uint8_t)(d.height >> (8 * b));
-        }
-        f[12] = (uint8_t)d.patch;
-    }
+    if (header <= d.file_cap) write_fixed_header(d);
 }
 
 /* How a workgroup of the compaction shares its slots: a slot of a 128-pixel patch (up to 16.6 KB)
@@ -741,6 +789,357 @@ __global__ __launch_bounds__(256) void l3_encode_compact_kernel_args(const Encod
     compact_block<N, OWN_LAYOUT>(pack.d[blockIdx.y], sizes, slots, file_len, status);
 }
 
+/* ---- the chained route: N in {32, 64, 128}, room for the longest file ---------- */
+
+/* One kernel for calls of few strips whose files all have room for the longest stream there is
+ * (l3_encode_bound).  The strip kernel walks a strip's rows in one wave a channel, which is what such a call
+ * waits for, and the copy behind it waits for all of them.  Here a workgroup encodes one channel of a
+ * strip, that is patches that follow one another in the file: a wave takes R of the strip's rows (the
+ * filter needs the original row above, not a decoded one), keeps their residuals in registers and works out
+ * the rows' widths; with the waves' bit counts in LDS every wave knows where its rows begin and packs them
+ * into the unit's bytes in LDS.  Where those go in the file depends on the sizes of all units ahead of
+ * it in the image: each unit publishes its size as soon as it is known, ahead of packing, and adds up what
+ * the units ahead published (a decoupled look-back, Merrill and Garland 2016), 512 of them a round trip.
+ *
+ * Which image a workgroup works for follows from its number, but the image's units are taken in the
+ * order of a ticket, so that all units that one waits for are already with running workgroups, and those
+ * wait for smaller tickets only: every wait ends, whatever else runs on the GPU.  Images are taken in
+ * the order of workgroups, spread over the XCDs: with an eighth of the images on each as in the other kernels
+ * units look for others that have only just begun (256 photographs 207 us a call instead of 158).
+ *
+ * What bounds it (one image of 1920x1080: 16.6 us, 18.9 and 5.3 before) is a chain of round trips, the
+ * ticket, the rows, the look and the stores, with some 5 us of arithmetic between; the look costs 2 us of
+ * it.  Which calls take it: see chained_pays.  Measured the same or slower: 16 rows a wave at N = 32 and 64 (4
+ * photographs 14.9 us, 11.7 with 8), 8 at N = 128 (32 images of 2048x1024 182 us, 177 with 16), the first look
+ * ahead of all packing instead of in its middle (183 us). */
+template <int N>
+struct UnitGeom {
+    static constexpr int LPT = N / 4;              /* lanes per patch, 4 pixels each */
+    static constexpr int TPW = 64 / LPT;           /* patches of a unit */
+    static constexpr int R = N == 128 ? 16 : 8;    /* rows of a wave */
+    static constexpr int WAVES = N / R, THREADS = 64 * WAVES;
+    static constexpr int Q = R / 4;                /* fours of rows, reduced together */
+    /* the unit's bytes in LDS: from word LEAD on (a lane's field may begin 4 bits ahead of the first
+     * record, with zeros there), and room for the word behind the last */
+    static constexpr int LEAD = 4;
+    static constexpr int WORDS = TPW * (N * (12 + 8 * N) / 8) / 4;
+    static constexpr int ALL_WORDS = (LEAD + WORDS + 2 + 3) / 4 * 4;
+    static_assert(WORDS * 4 == TPW * (N * (12 + 8 * N) / 8), "whole words");
+    static_assert(WAVES <= 16 && R % 4 == 0, "fours of rows, and a workgroup of at most 1024 threads");
+};
+
+/* What a unit tells the others, one 64-bit word (cell) each: the number of the launch, whether the value
+ * includes all units ahead in the image, and a number of bytes.  A cell with another number is from an
+ * earlier launch.  An image's number and its next ticket are one word in device memory, of which the
+ * workgroup that takes the last ticket makes the next launch's: nothing is cleared between launches, and a
+ * recorded launch that is replayed counts on like any other.  The n-th images of all launches share a word
+ * and `stride` cells, so that numbers of different images never meet.  (35 bits: launches 5 us apart
+ * come round after two days, and only a cell that none of them wrote could then be taken for a new one.) */
+constexpr int kCellValueBits = 28;
+constexpr uint64_t kChainMaxBytes = (1ull << kCellValueBits) - 1;
+constexpr uint64_t kCellWhole = 1ull << kCellValueBits;
+constexpr int kNumberShift = kCellValueBits + 1;
+struct __attribute__((aligned(128))) L3ChainWord {      /* many workgroups add to it: a cache line each */
+    uint64_t ticket;                                    /* number << 29 | the image's next unit */
+};
+
+/* Calls that take this route: few units, N = 32 ones counted by two thirds (four waves, not eight).  Every
+ * unit reads all three channels' bytes, and with many in flight those no longer meet in a cache (32 images of
+ * 2048x1024 fetch 591 MB instead of 201), which the strip kernel and the copy then do better; 4 a CU
+ * is where they draw level.  An image of so many patches that they would need the layout kernel
+ * between them (own_layout_pays) is worth it up to 12 a CU.  A call by the strip kernel / by this (units):
+ *   N = 32    1 of 64x64 (6) 16.5 / 11.4 us, 1 photograph (72) 18.7 / 12.1, 16 (1152) 25.3 / 20.9, 4 of 1024x720 (1104) 25.4 / 21.7,
+ *             6 (1656) 28.9 / 27.5, 8 (2208) 29.6 / 32.9, 32 74.6 / 96.2; with the layout kernel 1 of 3840x1500 (2115) 107.7 / 58.3
+ *   N = 64    1 of 1920x1080 (408) 27.0 / 19.6, 2 (816) 32.1 / 27.7, 3 (1224) 32.9 / 33.5, 4 (1632) 38.9 / 40.4, 32 182.8 / 249.5;
+ *             with the layout kernel 1 of 5000x2500 (2400) 92.7 / 69.1
+ *   N = 128   1 of 2048x1024 (192) 39.2 / 16.0, 4 (768) 42.9 / 32.9, 8 (1536) 58.5 / 51.5, 16 (3072) 94.9 / 95.1, 1 of 3840x2160 (765)
+ *             42.7 / 40.3, 2 (1530) 59.8 / 63.7 */
+constexpr uint32_t kMostChainUnits = 3072;
+constexpr bool chained_pays(const uint32_t (&strips)[3], uint64_t images, bool own_layout) {
+    const uint64_t two_thirds = 3 * images * (2ull * strips[0] + 3ull * strips[1] + 3ull * strips[2]);   /* of units, times 3 */
+    return two_thirds <= 3ull * (own_layout ? 1024 : kMostChainUnits) && 3 * images * strips[0] <= kMostChainUnits;
+}
+static_assert(kMostChainUnits * (uint64_t)UnitGeom<128>::WORDS * 4 <= kChainMaxBytes, "an image's bytes fit a cell");
+/* How often a unit looks for the ones ahead before it gives up (each look is a round trip to memory,
+ * about a microsecond: a second in all).  By the order of tickets it cannot happen; if it did, the unit would
+ * not be written and its image's status word would say so. */
+constexpr uint32_t kMaxLooks = 1u << 20;
+constexpr uint32_t kStatusGaveUp = 4u;
+
+/* The cells of the 512 units that end `behind` units ahead of `unit`, in the lanes of a wave; `cell` is
+ * the unit's own, those of the units ahead lie in front of it. */
+struct ChainLook {
+    static constexpr int W = 8;
+    uint64_t c[W];
+    __device__ __forceinline__ void at(const uint64_t* cell, uint32_t unit, uint64_t number, uint32_t lane, uint32_t behind) {
+#pragma unroll
+        for (int j = 0; j < W; ++j) {
+            const uint32_t back = behind + 64 * j + lane;          /* units between this one and that */
+            c[j] = number << kNumberShift | kCellWhole;             /* ahead of the image: nothing, and all of it */
+            if (back < unit) c[j] = agent_load_u64(cell - 1 - back);
+        }
+    }
+};
+/* Bytes of the units ahead, given the first look at them; false if it gave up. */
+__device__ __forceinline__ bool bytes_ahead(ChainLook look, const uint64_t* cell, uint32_t unit, uint64_t number,
+                                            uint32_t lane, uint32_t& ahead) {
+    uint32_t sum = 0, behind = 0, looks = 0;
+    bool whole = false, ok = true;
+    for (;;) {
+        uint32_t part = 0;
+        bool missing = false;
+#pragma unroll
+        for (int j = 0; j < ChainLook::W; ++j) {
+            const bool there = look.c[j] >> kNumberShift == number;
+            const uint64_t have = __builtin_amdgcn_ballot_w64(there);
+            const uint64_t full = __builtin_amdgcn_ballot_w64(there && (look.c[j] & kCellWhole) != 0);
+            const uint64_t upto = full ? full ^ (full - 1) : ~0ull;   /* the nearest that holds all ahead of it, and those nearer */
+            if (!whole && !missing) {
+                missing = (have & upto) != upto;
+                part += upto >> lane & 1u ? (uint32_t)(look.c[j] & kChainMaxBytes) : 0u;
+                whole = !missing && full != 0;
+            }
+        }
+        if (missing) {
+            ok = ++looks < kMaxLooks;
+        } else {
+            sum += part;
+            behind += 64 * ChainLook::W;
+        }
+        if (whole || !ok) break;
+        look.at(cell, unit, number, lane, behind);
+    }
+#pragma unroll
+    for (int step = 32; step >= 1; step >>= 1) sum += (uint32_t)__shfl_xor((int)sum, step);
+    ahead = sum;
+    return ok;
+}
+
+template <int N>
+__device__ __forceinline__ void encode_unit(const L3EncodeDesc& d, const uint32_t unit, const uint32_t units,
+                                            const uint64_t number, uint64_t* __restrict__ cell,
+                                            uint64_t* __restrict__ file_len, uint32_t* __restrict__ status) {
+    using G = UnitGeom<N>;
+    constexpr int LPT = G::LPT, TPW = G::TPW, R = G::R, Q = G::Q, WAVES = G::WAVES;
+    __shared__ __attribute__((aligned(16))) uint32_t stream[G::ALL_WORDS];
+    __shared__ uint32_t wave_bits[WAVES][TPW];
+    __shared__ uint32_t place[2];               /* the unit's offset in the data section; 1: known */
+
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t g = lane / LPT, xl = lane % LPT;
+    const uint32_t channel_units = d.strips_x * d.tiles_y;
+    const uint32_t c = unit / channel_units, in_channel = unit - c * channel_units;
+    const uint32_t ty = in_channel / d.strips_x, strip = in_channel - ty * d.strips_x;
+    const uint32_t tx = strip * TPW + g;
+    const bool active = tx < d.tiles_x;
+    const uint32_t x0 = tx * N, y0 = ty * N;
+    const uint32_t pw = active ? min((uint32_t)N, d.width - x0) : 0u;
+    const uint32_t ph = min((uint32_t)N, d.height - y0);
+    const StripLane ln(d.width, x0, pw, xl);
+
+    /* rows first .. first + R - 1 of the patch and the one above them; rows that do not exist repeat
+     * the last one */
+    const uint32_t first = wave * R;
+    u32x3 raw[R + 1];
+    {
+        const uint8_t* row = d.rgb + (size_t)(y0 + min(first - min(first, 1u), ph - 1)) * d.row_stride;
+        const uint64_t row_stride = d.row_stride;
+        const auto load_all = [&](auto load) {
+#pragma unroll
+            for (int i = 0; i <= R; ++i) {
+                raw[i] = load(row);
+                row += first + i > 0 && first + i < ph ? row_stride : 0;      /* row i + 1 of these is row first + i */
+            }
+        };
+        if (ln.wide) load_all([&](const uint8_t* r) { return ln.load_wide(r); });
+        else load_all([&](const uint8_t* r) { return ln.load_narrow(r); });
+    }
+    {
+        const u32x4 zero = {0, 0, 0, 0};
+        for (uint32_t i = threadIdx.x; i < G::ALL_WORDS / 4; i += G::THREADS) reinterpret_cast<u32x4*>(stream)[i] = zero;
+    }
+    if (ln.ragged_wave) {
+#pragma unroll
+        for (int i = 0; i <= R; ++i) ln.shift_down(raw[i]);
+    }
+    uint32_t cur[R + 1][2], pixel_bias = kPixelBias;
+    L3_KEEP_SGPR(pixel_bias);
+    if (c == 0) {
+#pragma unroll
+        for (int i = 0; i <= R; ++i) take_channel<0>(raw[i], pixel_bias, cur[i]);
+    } else if (c == 1) {
+#pragma unroll
+        for (int i = 0; i <= R; ++i) take_channel<1>(raw[i], pixel_bias, cur[i]);
+    } else {
+#pragma unroll
+        for (int i = 0; i <= R; ++i) take_channel<2>(raw[i], pixel_bias, cur[i]);
+    }
+
+    /* Section 4.2: filter, and the rows' widths, four rows at a time */
+    const uint32_t my_row = reduced_row<LPT>(lane);                 /* see patch_min_of_rows */
+    uint32_t kE, kO, krow = 0x80u;
+    ln.later_row_key(kE, kO);
+    if (wave == 0) {                 /* zeros above the patch's first row predict 0; it is looked at as unsigned */
+        cur[0][0] = cur[0][1] = kPixelBias;
+        ln.first_row_key(kE, kO);
+        krow = my_row == 0 ? 0u : 0x80u;
+    }
+    uint32_t uE[R], uO[R], mine[Q], my_rec[Q], my_widths = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        uint32_t part[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            part[i] = ln.filter(cur[4 * q + i], cur[4 * q + i + 1], kE, kO, uE[4 * q + i], uO[4 * q + i]);
+            if (q == 0 && i == 0) ln.later_row_key(kE, kO);
+        }
+        const uint32_t m = extremes_of_my_row<LPT>(part, my_row);
+        my_rec[q] = record_of(m, krow);
+        krow = 0x80u;
+        /* a row that does not exist packs nothing: no u is below 0, and its width is 0 */
+        mine[q] = first + 4 * q + my_row < ph ? m : 0u;
+        my_widths += mine[q] >> 16;
+    }
+
+    /* how many bits the wave's rows of each patch take, and from the other waves' where they begin */
+    uint32_t widths[4];
+    rows_to_all_lanes<LPT>(my_widths, widths);
+    const uint32_t exist = ph - min(ph, first) < (uint32_t)R ? ph - min(ph, first) : (uint32_t)R;
+    const uint32_t bits = active ? 12 * exist + pw * (widths[0] + widths[1] + widths[2] + widths[3]) : 0u;
+    if (xl == 0) wave_bits[wave][g] = bits;
+    __syncthreads();
+    uint32_t before = 0, patch_bits = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < (uint32_t)WAVES; ++w) {
+        const uint32_t b = wave_bits[w][g];
+        before += w < wave ? b : 0u;
+        patch_bits += b;
+    }
+    const uint32_t patch_bytes = (patch_bits + 7) / 8;
+    uint32_t patch_at = 0, unit_bytes = 0;       /* the patch's first byte in the unit; the unit's bytes */
+#pragma unroll
+    for (int p = 0; p < TPW; ++p) {
+        patch_at = g == (uint32_t)p ? unit_bytes : patch_at;
+        unit_bytes += (uint32_t)__builtin_amdgcn_readlane((int)patch_bytes, p * LPT);
+    }
+    const bool looks_back = wave == WAVES - 1;   /* the wave with the fewest rows */
+    if (looks_back && lane == 0)
+        agent_store_u64(cell, number << kNumberShift | (unit == 0 ? kCellWhole : 0u) | unit_bytes);
+
+    /* the deltas of all rows into the unit's bytes */
+    const uint32_t stream_lds = lds_address_of(stream);
+    auto put = [&](uint32_t value, uint32_t pos) {
+        const uint32_t lo = value << (pos & 31u);
+        const uint32_t hi = (value >> 1) >> (~pos & 31u);
+        lds_or_pair(stream_lds + (pos >> 5) * 4, lo, hi);
+    };
+    uint32_t rowpos = 32 * G::LEAD + 8 * patch_at + before;
+    const bool writes_record = active && (LPT == 32 ? (xl & 14u) == 0 : xl < 4);
+    ChainLook look;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        if (q == Q / 2 && looks_back) look.at(cell, unit, number, lane, 0);
+        uint32_t extremes[4], my_at = rowpos;
+        rows_to_all_lanes<LPT>(mine[q], extremes);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t w = extremes[i] >> 16;
+            if (i) my_at = my_row == (uint32_t)i ? rowpos : my_at;
+            put(delta_field(extremes[i], uE[4 * q + i], uO[4 * q + i]), rowpos - 4 + (ln.xpix + 2) * w);
+            rowpos += 12 + pw * w;
+        }
+        if (writes_record && first + 4 * q + my_row < ph) put(my_rec[q], my_at);
+    }
+
+    if (looks_back) {
+        uint32_t ahead;
+        const bool known = bytes_ahead(look, cell, unit, number, lane, ahead);
+        if (lane == 0) {
+            if (known && unit) agent_store_u64(cell, number << kNumberShift | kCellWhole | (ahead + unit_bytes));
+            place[0] = ahead;
+            place[1] = known;
+        }
+    }
+    __syncthreads();
+    const uint32_t patches = d.tiles_x * d.tiles_y;
+    const uint64_t header = 13 + 12ull * patches;
+    const uint32_t at = place[0];
+    if (!place[1]) {
+        if (threadIdx.x == 0 && status) atomicOr(&status[d.status_index], kStatusGaveUp);
+        return;
+    }
+    if (wave == 0 && xl == 0 && active)          /* Section 4.3, the offset array of channel c */
+        *reinterpret_cast<global_u32_any*>((uintptr_t)(d.file + 13 + 4 * (size_t)(c * patches + ty * d.tiles_x + tx))) = at + patch_at;
+    if (threadIdx.x == 0) {
+        if (unit == 0) {
+            write_fixed_header(d);
+            if (status) status[d.status_index] = 0;
+        }
+        if (unit == units - 1) file_len[d.status_index] = header + at + unit_bytes;
+    }
+    uint8_t* const to = d.file + header + at;
+    const uint32_t whole = unit_bytes / 16, tail = unit_bytes & 15u;
+    const uint32_t* const from = stream + G::LEAD;
+    for (uint32_t i = threadIdx.x; i < whole; i += G::THREADS)
+        *reinterpret_cast<global_u32x4_any*>((uintptr_t)(to + 16 * (size_t)i)) = reinterpret_cast<const u32x4*>(from)[i];
+    if (threadIdx.x < tail)
+        to[16 * (size_t)whole + threadIdx.x] = reinterpret_cast<const uint8_t*>(from)[16 * (size_t)whole + threadIdx.x];
+}
+
+template <int N, class Descs>
+__device__ __forceinline__ void chain_block(const Descs& descs, uint32_t units_per_image,
+                                            L3ChainWord* __restrict__ words, uint64_t* __restrict__ cells, uint32_t stride,
+                                            uint64_t* __restrict__ file_len, uint32_t* __restrict__ status) {
+    const uint32_t image = blockIdx.x / units_per_image;      /* in dispatch order: see encode_unit */
+    /* what the rows' addresses wait for is read while the ticket travels */
+    L3EncodeDesc d = descs[image];
+    L3_KEEP_SGPR(d.rgb);
+    L3_KEEP_SGPR(d.file);
+    L3_KEEP_SGPR(d.row_stride);
+    L3_KEEP_SGPR(d.width);
+    L3_KEEP_SGPR(d.height);
+    L3_KEEP_SGPR(d.tiles_x);
+    L3_KEEP_SGPR(d.tiles_y);
+    L3_KEEP_SGPR(d.strips_x);
+    L3_KEEP_SGPR(d.patch);
+    L3_KEEP_SGPR(d.status_index);
+    L3_KEEP_SGPR(words);
+    __shared__ uint64_t taken;
+    if (threadIdx.x == 0) {
+        const uint64_t t = agent_add_u64(&words[image].ticket, 1);
+        taken = t;
+        if ((t & (kCellWhole * 2 - 1)) == units_per_image - 1)          /* all have theirs */
+            agent_store_u64(&words[image].ticket, ((t >> kNumberShift) + 1) << kNumberShift);
+    }
+    __syncthreads();
+    const uint32_t low = __builtin_amdgcn_readfirstlane((uint32_t)taken);
+    const uint32_t high = __builtin_amdgcn_readfirstlane((uint32_t)(taken >> 32));
+    const uint64_t number = ((uint64_t)high << 32 | low) >> kNumberShift;
+    const uint32_t unit = low & (uint32_t)(kCellWhole * 2 - 1);
+    const uint32_t units = 3 * d.strips_x * d.tiles_y;
+    if (d.patch == N && unit < units)
+        encode_unit<N>(d, unit, units, number, cells + (size_t)image * stride + unit, file_len, status);
+}
+template <int N>
+__global__ __launch_bounds__(UnitGeom<N>::THREADS) void l3_encode_chain_kernel(
+    const L3EncodeDesc* __restrict__ descs, uint32_t units_per_image, L3ChainWord* __restrict__ words,
+    uint64_t* __restrict__ cells, uint32_t stride, uint64_t* __restrict__ file_len, uint32_t* __restrict__ status) {
+    chain_block<N>(descs, units_per_image, words, cells, stride, file_len, status);
+}
+template <int N>
+__global__ __launch_bounds__(UnitGeom<N>::THREADS) void l3_encode_chain_kernel_args(
+    const EncodePack pack, uint32_t units_per_image, L3ChainWord* __restrict__ words,
+    uint64_t* __restrict__ cells, uint32_t stride, uint64_t* __restrict__ file_len, uint32_t* __restrict__ status) {
+    chain_block<N>(pack.d, units_per_image, words, cells, stride, file_len, status);
+}
+/* New words and cells: the first launches have the number 1. */
+__global__ void l3_encode_clear_kernel(L3ChainWord* __restrict__ words, uint32_t images, uint64_t* __restrict__ cells,
+                                       uint32_t n) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < images) words[i].ticket = 1ull << kNumberShift;
+    if (i < n) cells[i] = 0;
+}
+
 /* ---- the plain route: any other N up to 128 -------------------------------- */
 
 __global__ __launch_bounds__(64) void l3_encode_measure_kernel(const L3EncodeDesc* __restrict__ descs,
@@ -840,6 +1239,8 @@ struct L3EncodeState {
     size_t sizes_cap = 0;
     uint8_t* d_slots = nullptr;      /* strip route: one fixed-size slot per patch and channel */
     size_t slots_cap = 0;
+    L3ChainWord* d_words = nullptr;  /* chained route: words of chain_images images, and behind them their cells */
+    uint32_t chain_images = 0, chain_stride = 0;
     hipEvent_t done = nullptr;       /* the last call's kernels have finished */
     bool pending = false;
     hipStream_t last_stream = nullptr;
@@ -855,6 +1256,7 @@ void l3_encode_state_free(L3EncodeState* s) {
     if (s->d_descs) (void)hipFree(s->d_descs);
     if (s->d_sizes) (void)hipFree(s->d_sizes);
     if (s->d_slots) (void)hipFree(s->d_slots);
+    if (s->d_words) (void)hipFree(s->d_words);
     delete s;
 }
 
@@ -871,7 +1273,7 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
     uint32_t strip_units[3] = {0, 0, 0};   /* largest grid of the strip route per N = 32, 64, 128 */
     uint32_t strip_slots[3] = {0, 0, 0};   /* most slots of an image, likewise */
     uint64_t layout_reads = 0;             /* see own_layout_pays */
-    bool any_plain = false;
+    bool any_plain = false, chained = true;
     for (int i = 0; i < n; ++i) {
         const l3_encode_item& it = items[i];
         if (!it.d_rgb || !it.d_file || it.width == 0 || it.height == 0 ||
@@ -893,11 +1295,16 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
             if (3 * p > strip_slots[cls]) strip_slots[cls] = (uint32_t)(3 * p);
             if (3 * p <= kOwnLayoutPatches) layout_reads += own_layout_reads(np, (uint32_t)(3 * p));
             slot_bytes += (size_t)(3 * p) * strip_slot_bytes(np);
+            /* what l3_encode_bound gives: every row at 12 + 8 bits a pixel, a byte of padding a patch */
+            const uint64_t bound = 13 + 12 * p + 3 * ((uint64_t)it.width * it.height + 2 * (uint64_t)it.height * tiles_x + p);
+            chained &= it.file_cap >= bound;
         } else {
             any_plain = true;
         }
     }
     if (total_patches > 0xFFFFFFFFull) return L3_ERR_UNSUPPORTED;
+    const bool own_layout = own_layout_pays(max_patches, layout_reads) && !any_plain;
+    chained &= !any_plain && chained_pays(strip_units, (uint64_t)n, own_layout);
 
     if (!ctx->enc) {
         ctx->enc = new (std::nothrow) L3EncodeState;
@@ -917,7 +1324,6 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
         hipStreamWaitEvent(stream, st->done, 0) != hipSuccess)
         return L3_ERR_DEVICE;
     const bool by_args = n <= kArgDescs && !any_plain;
-    const bool own_layout = own_layout_pays(max_patches, layout_reads) && !any_plain;
     constexpr int kStage = 4;
     int stage = 0;
     if (!by_args) {
@@ -947,7 +1353,25 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
             return L3_ERR_DEVICE;
         st->staged_pending[stage] = false;
     }
-    if (total_patches > st->sizes_cap) {
+    const uint32_t most_units = 3 * std::max(strip_units[0], std::max(strip_units[1], strip_units[2]));
+    if (chained && ((uint32_t)n > st->chain_images || most_units > st->chain_stride)) {
+        if (!wait_previous()) return L3_ERR_DEVICE;
+        /* at most 1024 images of 4096 units, 32 MB (see chained_pays) */
+        uint32_t images = 32, stride = 512;
+        while (images < std::max(st->chain_images, (uint32_t)n)) images *= 2;
+        while (stride < std::max(st->chain_stride, most_units)) stride *= 2;
+        if (st->d_words) (void)hipFree(st->d_words);
+        st->d_words = nullptr;
+        st->chain_images = st->chain_stride = 0;
+        const size_t count = (size_t)images * stride;
+        if (hipMalloc(reinterpret_cast<void**>(&st->d_words), images * sizeof(L3ChainWord) + count * sizeof(uint64_t)) != hipSuccess)
+            return L3_ERR_DEVICE;
+        st->chain_images = images;
+        st->chain_stride = stride;
+        hipLaunchKernelGGL(l3_encode_clear_kernel, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, stream,
+                           st->d_words, images, reinterpret_cast<uint64_t*>(st->d_words + images), (uint32_t)count);
+    }
+    if (!chained && total_patches > st->sizes_cap) {
         if (!wait_previous()) return L3_ERR_DEVICE;
         size_t cap = 4096;
         while (cap < total_patches) cap *= 2;
@@ -958,7 +1382,7 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
             return L3_ERR_DEVICE;
         st->sizes_cap = cap;
     }
-    if (slot_bytes > st->slots_cap) {
+    if (!chained && slot_bytes > st->slots_cap) {
         if (!wait_previous()) return L3_ERR_DEVICE;
         if (st->d_slots) (void)hipFree(st->d_slots);
         st->d_slots = nullptr;
@@ -998,6 +1422,31 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
     }
     if (by_args) {
         for (int i = n; i < kArgDescs; ++i) std::memset(&pack.d[i], 0, sizeof(L3EncodeDesc));
+    } else {
+        if (hipMemcpyAsync(st->d_descs, table, (size_t)n * sizeof(L3EncodeDesc), hipMemcpyHostToDevice,
+                           stream) != hipSuccess ||
+            hipEventRecord(st->staged[stage], stream) != hipSuccess)
+            return L3_ERR_DEVICE;
+        st->staged_pending[stage] = true;
+    }
+    if (chained) {
+        uint64_t* const cells = reinterpret_cast<uint64_t*>(st->d_words + st->chain_images);
+        const auto encode = [&](auto n_tag, uint32_t strips) {
+            constexpr int N = decltype(n_tag)::value;
+            if (!strips) return;
+            const uint32_t units = 3 * strips;
+            const dim3 grid(units * (uint32_t)n);
+            if (by_args)
+                hipLaunchKernelGGL(l3_encode_chain_kernel_args<N>, grid, dim3(UnitGeom<N>::THREADS), 0, stream, pack, units,
+                                   st->d_words, cells, st->chain_stride, d_file_len, d_status);
+            else
+                hipLaunchKernelGGL(l3_encode_chain_kernel<N>, grid, dim3(UnitGeom<N>::THREADS), 0, stream, st->d_descs,
+                                   units, st->d_words, cells, st->chain_stride, d_file_len, d_status);
+        };
+        encode(std::integral_constant<int, 32>(), strip_units[0]);
+        encode(std::integral_constant<int, 64>(), strip_units[1]);
+        encode(std::integral_constant<int, 128>(), strip_units[2]);
+    } else if (by_args) {
         const uint32_t m = (uint32_t)n;
         if (strip_units[0])
             hipLaunchKernelGGL(l3_encode_strip_kernel_args<32>, dim3(strip_units[0], m), dim3(192), 0, stream,
@@ -1025,11 +1474,6 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
         compact(std::integral_constant<int, 64>(), strip_slots[1]);
         compact(std::integral_constant<int, 128>(), strip_slots[2]);
     } else {
-        if (hipMemcpyAsync(st->d_descs, table, (size_t)n * sizeof(L3EncodeDesc), hipMemcpyHostToDevice,
-                           stream) != hipSuccess ||
-            hipEventRecord(st->staged[stage], stream) != hipSuccess)
-            return L3_ERR_DEVICE;
-        st->staged_pending[stage] = true;
         const size_t lds_bytes = ((size_t)max_n * (12 + 8 * (size_t)max_n) + 31) / 32 * 4 + 8;
         for (int first = 0; first < n; first += 65535) {
             const uint32_t m = (uint32_t)(n - first < 65535 ? n - first : 65535);

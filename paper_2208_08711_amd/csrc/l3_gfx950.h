@@ -145,11 +145,30 @@ __device__ __forceinline__ void lds_write_u32x4(uint32_t where, u32x4 v) {
     *reinterpret_cast<__attribute__((address_space(3))) u32x4*>(where) = v;
 }
 
-/* ORs lo and hi into the two consecutive words at LDS address `where`, each atomically among the wave's lanes */
+/* ORs lo and hi into the two consecutive words at LDS address `where`, each atomically among the workgroup's threads */
 __device__ __forceinline__ void lds_or_pair(uint32_t where, uint32_t lo, uint32_t hi) {
     __attribute__((address_space(3))) uint32_t* cell = reinterpret_cast<__attribute__((address_space(3))) uint32_t*>(where);
-    __hip_atomic_fetch_or(cell, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-    __hip_atomic_fetch_or(cell + 1, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __hip_atomic_fetch_or(cell, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_or(cell + 1, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+/* ---- words that workgroups of a launch share -------------------------------- */
+
+/* Each of these is one access that all workgroups of the GPU see alike; none orders other accesses. */
+__device__ __forceinline__ uint64_t agent_load_u64(const uint64_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void agent_store_u64(uint64_t* p, uint64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void agent_store_u32(uint32_t* p, uint32_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t agent_add_u64(uint64_t* p, uint64_t v) {
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t agent_add_u32(uint32_t* p, uint32_t v) {
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 /* LDS of the size that the launch gives */
