@@ -320,24 +320,36 @@ def decode_crop_normalize_batch_prepared(ctx, batch, crop_w, crop_h, out, dtype=
         "l3_decode_crop_normalize_batch")
 
 
+_data_ptr, _numel = operator.methodcaller("data_ptr"), operator.methodcaller("numel")
+
+
 def encode_batch(ctx, images, files, file_len, patch=0, status=None, stream=None, row_strides=None):
     """images: list of uint8 device tensors [H, W, 3] (rows contiguous unless row_strides is
     given); files: list of uint8 device tensors that receive the L3 files; file_len: int64 (or
     uint64) device tensor of len(images) words; patch: one N for all or a list."""
     n = len(images)
-    # integers of any kind (numpy's, a tensor's elements) as Python's own, which the masks below take
-    if isinstance(patch, (list, tuple)):
-        patches = [operator.index(patch[i]) for i in range(n)]
-    else:
-        patches = (operator.index(patch),) * n if n else ()
-    strides = None if row_strides is None else [operator.index(row_strides[i]) for i in range(n)]
-    words = array.array("Q")        # the l3_encode_item array, see _EncodeItem: 6 words of 8 bytes each
-    for i in range(n):
-        shape, out = images[i].shape, files[i]
-        h, w = int(shape[0]), int(shape[1])
-        stride = 3 * w if strides is None else strides[i]
-        words.extend((images[i].data_ptr(), stride & _MASK64,
-                      (w & _MASK32) | (h & _MASK32) << 32, patches[i] & 0xFF, out.data_ptr(), out.numel()))
+    # The l3_encode_item array (see _EncodeItem: 6 words of 8 bytes each) is filled column by column, which
+    # for a batch of small images is a good part of the call (256 photographs
+    # 162 us image by image, 142 so).
+    words = array.array("Q", bytes(48 * n))
+    if n:
+        # integers of any kind (numpy's, a tensor's elements) as Python's own, which the masks below take
+        if isinstance(patch, (list, tuple)):
+            words[3::6] = array.array("Q", [operator.index(patch[i]) & 0xFF for i in range(n)])
+        else:
+            words[3::6] = array.array("Q", (operator.index(patch) & 0xFF,)) * n
+        if len(files) != n:
+            files = [files[i] for i in range(n)]
+        shapes = [im.shape for im in images]
+        widths = [int(s[1]) for s in shapes]
+        words[0::6] = array.array("Q", map(_data_ptr, images))
+        if row_strides is None:
+            words[1::6] = array.array("Q", [3 * w & _MASK64 for w in widths])
+        else:
+            words[1::6] = array.array("Q", [operator.index(row_strides[i]) & _MASK64 for i in range(n)])
+        words[2::6] = array.array("Q", [w & _MASK32 | (int(s[0]) & _MASK32) << 32 for w, s in zip(widths, shapes)])
+        words[4::6] = array.array("Q", map(_data_ptr, files))
+        words[5::6] = array.array("Q", map(_numel, files))
     arr = (_EncodeItem * n).from_buffer(words) if n else (_EncodeItem * 1)()
     _check(_load().l3_encode_batch(ctx.handle, arr, n, ctypes.c_void_p(file_len.data_ptr()),
                                    ctypes.c_void_p(status.data_ptr() if status is not None else None),

@@ -596,10 +596,14 @@ __device__ __forceinline__ void strip_block(const L3EncodeDesc& d, uint32_t* __r
 }
 
 /* Descriptors either in a device table (any batch size) or, for small batches, inside
- * the kernel arguments: no upload to wait for, so consecutive calls run back to back. */
-constexpr int kArgDescs = 32;
-struct EncodePack { L3EncodeDesc d[kArgDescs]; };
-static_assert(sizeof(EncodePack) + 64 <= 4096, "kernel argument segment");
+ * the kernel arguments: no upload to wait for, so consecutive calls run back to back.  Two capacities, so
+ * that small batches do not carry a large argument block.  (Batches of 33 to 256 images went through the
+ * table before; with the arguments marshalled column by column as well, 256 photographs 161 -> 142 us a
+ * call, of which the kernels take 135; the block alone left the call to the host, 162.) */
+constexpr int kArgDescsSmall = 32, kArgDescs = 256;
+template <int CAP>
+struct EncodePack { L3EncodeDesc d[CAP]; };
+static_assert(sizeof(EncodePack<kArgDescs>) + 64 <= 32768, "kernel argument segment");
 
 template <int N>
 __global__ __launch_bounds__(192) void l3_encode_strip_kernel(const L3EncodeDesc* __restrict__ descs,
@@ -607,8 +611,8 @@ __global__ __launch_bounds__(192) void l3_encode_strip_kernel(const L3EncodeDesc
                                                               uint8_t* __restrict__ slots) {
     strip_block<N>(descs[blockIdx.y], sizes, slots);
 }
-template <int N>
-__global__ __launch_bounds__(192) void l3_encode_strip_kernel_args(const EncodePack pack,
+template <int N, int CAP>
+__global__ __launch_bounds__(192) void l3_encode_strip_kernel_args(const EncodePack<CAP> pack,
                                                                    uint32_t* __restrict__ sizes,
                                                                    uint8_t* __restrict__ slots) {
     strip_block<N>(pack.d[blockIdx.y], sizes, slots);
@@ -780,8 +784,8 @@ __global__ __launch_bounds__(256) void l3_encode_compact_kernel(const L3EncodeDe
                                                                 uint32_t* __restrict__ status) {
     compact_block<N, OWN_LAYOUT>(descs[blockIdx.y], sizes, slots, file_len, status);
 }
-template <int N, bool OWN_LAYOUT>
-__global__ __launch_bounds__(256) void l3_encode_compact_kernel_args(const EncodePack pack,
+template <int N, bool OWN_LAYOUT, int CAP>
+__global__ __launch_bounds__(256) void l3_encode_compact_kernel_args(const EncodePack<CAP> pack,
                                                                      const uint32_t* __restrict__ sizes,
                                                                      const uint8_t* __restrict__ slots,
                                                                      uint64_t* __restrict__ file_len,
@@ -1126,9 +1130,9 @@ __global__ __launch_bounds__(UnitGeom<N>::THREADS) void l3_encode_chain_kernel(
     uint64_t* __restrict__ cells, uint32_t stride, uint64_t* __restrict__ file_len, uint32_t* __restrict__ status) {
     chain_block<N>(descs, units_per_image, words, cells, stride, file_len, status);
 }
-template <int N>
+template <int N, int CAP>
 __global__ __launch_bounds__(UnitGeom<N>::THREADS) void l3_encode_chain_kernel_args(
-    const EncodePack pack, uint32_t units_per_image, L3ChainWord* __restrict__ words,
+    const EncodePack<CAP> pack, uint32_t units_per_image, L3ChainWord* __restrict__ words,
     uint64_t* __restrict__ cells, uint32_t stride, uint64_t* __restrict__ file_len, uint32_t* __restrict__ status) {
     chain_block<N>(pack.d, units_per_image, words, cells, stride, file_len, status);
 }
@@ -1190,7 +1194,8 @@ __global__ __launch_bounds__(256) void l3_encode_layout_kernel(const L3EncodeDes
                                                                uint32_t* __restrict__ status) {
     layout_block(descs[blockIdx.x], sizes, file_len, status);
 }
-__global__ __launch_bounds__(256) void l3_encode_layout_kernel_args(const EncodePack pack,
+template <int CAP>
+__global__ __launch_bounds__(256) void l3_encode_layout_kernel_args(const EncodePack<CAP> pack,
                                                                     const uint32_t* __restrict__ sizes,
                                                                     uint64_t* __restrict__ file_len,
                                                                     uint32_t* __restrict__ status) {
@@ -1392,7 +1397,9 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
         st->slots_cap = slot_bytes;
     }
 
-    EncodePack pack;
+    EncodePack<kArgDescs> pack;              /* the first kArgDescsSmall of it are the smaller block */
+    const EncodePack<kArgDescsSmall>& small_pack = reinterpret_cast<const EncodePack<kArgDescsSmall>&>(pack);
+    const bool small = n <= kArgDescsSmall;
     L3EncodeDesc* const table = by_args ? pack.d : st->h_descs + (size_t)stage * st->desc_cap;
     size_t base = 0, slots_base = 0;
     for (int i = 0; i < n; ++i) {
@@ -1421,7 +1428,8 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
         base += 3 * (size_t)d.tiles_x * d.tiles_y;
     }
     if (by_args) {
-        for (int i = n; i < kArgDescs; ++i) std::memset(&pack.d[i], 0, sizeof(L3EncodeDesc));
+        const int block = small ? kArgDescsSmall : kArgDescs;
+        std::memset(&pack.d[n], 0, (size_t)(block - n) * sizeof(L3EncodeDesc));
     } else {
         if (hipMemcpyAsync(st->d_descs, table, (size_t)n * sizeof(L3EncodeDesc), hipMemcpyHostToDevice,
                            stream) != hipSuccess ||
@@ -1436,9 +1444,12 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
             if (!strips) return;
             const uint32_t units = 3 * strips;
             const dim3 grid(units * (uint32_t)n);
-            if (by_args)
-                hipLaunchKernelGGL(l3_encode_chain_kernel_args<N>, grid, dim3(UnitGeom<N>::THREADS), 0, stream, pack, units,
-                                   st->d_words, cells, st->chain_stride, d_file_len, d_status);
+            if (by_args && small)
+                hipLaunchKernelGGL((l3_encode_chain_kernel_args<N, kArgDescsSmall>), grid, dim3(UnitGeom<N>::THREADS), 0, stream,
+                                   small_pack, units, st->d_words, cells, st->chain_stride, d_file_len, d_status);
+            else if (by_args)
+                hipLaunchKernelGGL((l3_encode_chain_kernel_args<N, kArgDescs>), grid, dim3(UnitGeom<N>::THREADS), 0, stream, pack,
+                                   units, st->d_words, cells, st->chain_stride, d_file_len, d_status);
             else
                 hipLaunchKernelGGL(l3_encode_chain_kernel<N>, grid, dim3(UnitGeom<N>::THREADS), 0, stream, st->d_descs,
                                    units, st->d_words, cells, st->chain_stride, d_file_len, d_status);
@@ -1448,31 +1459,36 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
         encode(std::integral_constant<int, 128>(), strip_units[2]);
     } else if (by_args) {
         const uint32_t m = (uint32_t)n;
-        if (strip_units[0])
-            hipLaunchKernelGGL(l3_encode_strip_kernel_args<32>, dim3(strip_units[0], m), dim3(192), 0, stream,
-                               pack, st->d_sizes, st->d_slots);
-        if (strip_units[1])
-            hipLaunchKernelGGL(l3_encode_strip_kernel_args<64>, dim3(strip_units[1], m), dim3(192), 0, stream,
-                               pack, st->d_sizes, st->d_slots);
-        if (strip_units[2])
-            hipLaunchKernelGGL(l3_encode_strip_kernel_args<128>, dim3(strip_units[2], m), dim3(192), 0, stream,
-                               pack, st->d_sizes, st->d_slots);
-        if (!own_layout)
-            hipLaunchKernelGGL(l3_encode_layout_kernel_args, dim3(m), dim3(256), 0, stream, pack, st->d_sizes,
-                               d_file_len, d_status);
-        const auto compact = [&](auto n_tag, uint32_t most) {
-            constexpr int N = decltype(n_tag)::value;
-            const dim3 grid((most + CompactGeom<N>::SLOTS - 1) / CompactGeom<N>::SLOTS, m);
-            if (most && own_layout)
-                hipLaunchKernelGGL((l3_encode_compact_kernel_args<N, true>), grid, dim3(256), 0, stream, pack,
-                                   st->d_sizes, st->d_slots, d_file_len, d_status);
-            else if (most)
-                hipLaunchKernelGGL((l3_encode_compact_kernel_args<N, false>), grid, dim3(256), 0, stream, pack,
-                                   st->d_sizes, st->d_slots, d_file_len, d_status);
+        const auto launch = [&](const auto& descs, auto cap_tag) {
+            constexpr int CAP = decltype(cap_tag)::value;
+            if (strip_units[0])
+                hipLaunchKernelGGL((l3_encode_strip_kernel_args<32, CAP>), dim3(strip_units[0], m), dim3(192), 0, stream,
+                                   descs, st->d_sizes, st->d_slots);
+            if (strip_units[1])
+                hipLaunchKernelGGL((l3_encode_strip_kernel_args<64, CAP>), dim3(strip_units[1], m), dim3(192), 0, stream,
+                                   descs, st->d_sizes, st->d_slots);
+            if (strip_units[2])
+                hipLaunchKernelGGL((l3_encode_strip_kernel_args<128, CAP>), dim3(strip_units[2], m), dim3(192), 0, stream,
+                                   descs, st->d_sizes, st->d_slots);
+            if (!own_layout)
+                hipLaunchKernelGGL(l3_encode_layout_kernel_args<CAP>, dim3(m), dim3(256), 0, stream, descs, st->d_sizes,
+                                   d_file_len, d_status);
+            const auto compact = [&](auto n_tag, uint32_t most) {
+                constexpr int N = decltype(n_tag)::value;
+                const dim3 grid((most + CompactGeom<N>::SLOTS - 1) / CompactGeom<N>::SLOTS, m);
+                if (most && own_layout)
+                    hipLaunchKernelGGL((l3_encode_compact_kernel_args<N, true, CAP>), grid, dim3(256), 0, stream, descs,
+                                       st->d_sizes, st->d_slots, d_file_len, d_status);
+                else if (most)
+                    hipLaunchKernelGGL((l3_encode_compact_kernel_args<N, false, CAP>), grid, dim3(256), 0, stream, descs,
+                                       st->d_sizes, st->d_slots, d_file_len, d_status);
+            };
+            compact(std::integral_constant<int, 32>(), strip_slots[0]);
+            compact(std::integral_constant<int, 64>(), strip_slots[1]);
+            compact(std::integral_constant<int, 128>(), strip_slots[2]);
         };
-        compact(std::integral_constant<int, 32>(), strip_slots[0]);
-        compact(std::integral_constant<int, 64>(), strip_slots[1]);
-        compact(std::integral_constant<int, 128>(), strip_slots[2]);
+        if (small) launch(small_pack, std::integral_constant<int, kArgDescsSmall>());
+        else launch(pack, std::integral_constant<int, kArgDescs>());
     } else {
         const size_t lds_bytes = ((size_t)max_n * (12 + 8 * (size_t)max_n) + 31) / 32 * 4 + 8;
         for (int first = 0; first < n; first += 65535) {
