@@ -835,8 +835,7 @@ struct UnitGeom {
 /* What a unit tells the others, one 64-bit word (cell) each: the number of the launch, whether the value
  * includes all units ahead in the image, and a number of bytes.  A cell with another number is from an
  * earlier launch.  An image's number and its next ticket are one word in device memory, of which the
- * workgroup that takes the last ticket makes the next launch's: nothing is cleared between launches, and a
- * recorded launch that is replayed counts on like any other.  The n-th images of all launches share a word
+ * workgroup that takes the last ticket makes the next launch's: nothing is cleared between launches.  The n-th images of all launches share a word
  * and `stride` cells, so that numbers of different images never meet.  (35 bits: launches 5 us apart
  * come round after two days, and only a cell that none of them wrote could then be taken for a new one.) */
 constexpr int kCellValueBits = 28;
@@ -1358,9 +1357,22 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
             return L3_ERR_DEVICE;
         st->staged_pending[stage] = false;
     }
+    /* The chained kernels count on words that earlier launches left in the workspace.  What a capturing
+     * stream records runs later, or again, or never, and is not seen by `done`: such a call takes the
+     * strip kernels, which find nothing in the workspace but what they wrote themselves.  (Their part of it is
+     * sized by every call, so that a call that has been made once can be captured.) */
+    if (chained) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+            (void)hipGetLastError();
+            chained = false;
+        } else if (capture != hipStreamCaptureStatusNone) {
+            chained = false;
+        }
+    }
     const uint32_t most_units = 3 * std::max(strip_units[0], std::max(strip_units[1], strip_units[2]));
     if (chained && ((uint32_t)n > st->chain_images || most_units > st->chain_stride)) {
-        if (!wait_previous()) return L3_ERR_DEVICE;
+        if (st->d_words && !wait_previous()) return L3_ERR_DEVICE;
         /* at most 1024 images of 4096 units, 32 MB (see chained_pays) */
         uint32_t images = 32, stride = 512;
         while (images < std::max(st->chain_images, (uint32_t)n)) images *= 2;
@@ -1371,12 +1383,16 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
         const size_t count = (size_t)images * stride;
         if (hipMalloc(reinterpret_cast<void**>(&st->d_words), images * sizeof(L3ChainWord) + count * sizeof(uint64_t)) != hipSuccess)
             return L3_ERR_DEVICE;
-        st->chain_images = images;
-        st->chain_stride = stride;
         hipLaunchKernelGGL(l3_encode_clear_kernel, dim3((uint32_t)((count + 255) / 256)), dim3(256), 0, stream,
                            st->d_words, images, reinterpret_cast<uint64_t*>(st->d_words + images), (uint32_t)count);
+        /* from here on every call is ordered behind the clear, whatever becomes of this one */
+        if (hipGetLastError() != hipSuccess || hipEventRecord(st->done, stream) != hipSuccess) return L3_ERR_DEVICE;
+        st->pending = true;
+        st->last_stream = stream;
+        st->chain_images = images;
+        st->chain_stride = stride;
     }
-    if (!chained && total_patches > st->sizes_cap) {
+    if (total_patches > st->sizes_cap) {
         if (!wait_previous()) return L3_ERR_DEVICE;
         size_t cap = 4096;
         while (cap < total_patches) cap *= 2;
@@ -1387,7 +1403,7 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
             return L3_ERR_DEVICE;
         st->sizes_cap = cap;
     }
-    if (!chained && slot_bytes > st->slots_cap) {
+    if (slot_bytes > st->slots_cap) {
         if (!wait_previous()) return L3_ERR_DEVICE;
         if (st->d_slots) (void)hipFree(st->d_slots);
         st->d_slots = nullptr;

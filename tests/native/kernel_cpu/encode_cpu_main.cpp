@@ -7,7 +7,10 @@
  * ends the run; under ThreadSanitizer any two accesses to LDS, the workspace or the files that no
  * barrier orders do.
  *
- * usage: encode_cpu <case file>       (written by tests/test_encoder_cpu_build.py)
+ * usage: encode_cpu <case file> [sequence]      (written by tests/test_encoder_cpu_build.py)
+ * sequence: what each call of the case is, one letter each: e an ordinary call; c a call while the
+ * stream captures (only recorded); r a replay of what was recorded; p a replay of its first workgroup alone, whose
+ * files are not looked at.  Without it all are ordinary.
  * Test infrastructure.
  */
 #include <hip/hip_runtime.h>
@@ -22,6 +25,7 @@
 #include L3_KERNEL_SOURCE
 
 #include <cstdio>
+#include <string>
 
 namespace {
 
@@ -42,7 +46,7 @@ constexpr uint8_t kPoison = 0xA5;
 }  // namespace
 
 int main(int argc, char** argv) {
-    if (argc != 2) return 2;
+    if (argc != 2 && argc != 3) return 2;
     Reader in{std::fopen(argv[1], "rb")};
     if (!in.f) return 2;
     if (in.get<uint32_t>() != 0x4345334Cu) return 2;       /* "L3EC" */
@@ -76,12 +80,23 @@ int main(int argc, char** argv) {
     uint64_t* lengths = static_cast<uint64_t*>(std::malloc(sizeof(uint64_t) * (size_t)n));
     uint32_t* status = static_cast<uint32_t*>(std::malloc(sizeof(uint32_t) * (size_t)n));
     int rc = 0;
-    for (int call = 0; call < calls && rc == 0; ++call) {   /* the workspace of the first call serves the others */
+    const std::string sequence = argc == 3 ? argv[2] : std::string((size_t)calls, 'e');
+    l3cpu_stream captured;
+    for (int call = 0; call < (int)sequence.size() && rc == 0; ++call) {   /* the workspace of the first call serves the others */
         for (int i = 0; i < n; ++i) std::memset(files[(size_t)i], kPoison, items[(size_t)i].file_cap);
         std::memset(lengths, 0xFF, sizeof(uint64_t) * (size_t)n);
         std::memset(status, 0xFF, sizeof(uint32_t) * (size_t)n);
-        const l3_status st = l3_encode_batch(ctx, items.data(), n, lengths, call % 2 ? nullptr : status, nullptr);
+        /* ordinary calls without and with status words in turn */
+        uint32_t* const words = argc == 2 && call % 2 ? nullptr : status;
+        l3_status st = L3_OK;
+        captured.capturing = sequence[(size_t)call] == 'c';
+        if (captured.capturing) captured.kept.clear();
+        if (sequence[(size_t)call] == 'e' || captured.capturing)
+            st = l3_encode_batch(ctx, items.data(), n, lengths, words, argc == 2 ? nullptr : &captured);
+        if (sequence[(size_t)call] == 'r') captured.replay();
+        if (sequence[(size_t)call] == 'p') captured.replay(1);
         if (st != L3_OK) { std::fprintf(stderr, "call failed: %s\n", l3_status_string(st)); rc = 1; }
+        if (sequence[(size_t)call] == 'c' || sequence[(size_t)call] == 'p') continue;
         for (int i = 0; i < n && rc == 0; ++i) {
             const std::vector<uint8_t>& want = expected[(size_t)i];
             const size_t cap = items[(size_t)i].file_cap;
@@ -89,7 +104,7 @@ int main(int argc, char** argv) {
             const size_t header = 13 + 12 * (size_t)((it.width + it.patch - 1) / it.patch) * ((it.height + it.patch - 1) / it.patch);
             const bool fits = want.size() <= cap;
             if (lengths[i] != want.size()) { std::fprintf(stderr, "MISMATCH: length, image %d: %llu\n", i, (unsigned long long)lengths[i]); rc = 1; }
-            if (call % 2 == 0 && status[i] != (fits ? 0u : 1u)) { std::fprintf(stderr, "MISMATCH: status, image %d: %u\n", i, status[i]); rc = 1; }
+            if (words && status[i] != (fits ? 0u : 1u)) { std::fprintf(stderr, "MISMATCH: status, image %d: %u\n", i, status[i]); rc = 1; }
             /* without room for the whole file the header is written if it fits, nothing else */
             const size_t written = fits ? want.size() : (header <= cap ? header : 0);
             for (size_t k = 0; k < cap && rc == 0; ++k)
@@ -105,6 +120,6 @@ int main(int argc, char** argv) {
     for (uint8_t* p : files) std::free(p);
     std::free(lengths);
     std::free(status);
-    if (rc == 0) std::printf("ok: %d images, %d calls\n", n, calls);
+    if (rc == 0) std::printf("ok: %d images, %d calls\n", n, (int)sequence.size());
     return rc;
 }

@@ -18,6 +18,7 @@
 #include <functional>
 #include <map>
 #include <thread>
+#include <tuple>
 #include <vector>
 
 /* ---- language ------------------------------------------------------------- */
@@ -175,8 +176,17 @@ inline int __shfl_down(int v, unsigned by) {
 
 typedef int hipError_t;
 constexpr hipError_t hipSuccess = 0;
-typedef struct l3cpu_stream* hipStream_t;
-typedef struct l3cpu_event* hipEvent_t;
+/* A stream that captures keeps its launches instead of running them; allocations go on as in the
+ * relaxed mode.  A replay runs the workgroups of each kept launch, the first `most` of them if that is
+ * fewer (a replay that something else on the GPU overtakes). */
+struct l3cpu_stream {
+    bool capturing = false;
+    std::vector<std::function<void(unsigned)>> kept;
+    void replay(unsigned most = ~0u) const { for (const auto& launch : kept) launch(most); }
+};
+typedef l3cpu_stream* hipStream_t;
+struct l3cpu_event { bool captured = false; };       /* last recorded by a stream that captured */
+typedef l3cpu_event* hipEvent_t;
 constexpr unsigned hipEventDisableTiming = 2, hipHostMallocDefault = 0;
 
 inline hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
@@ -203,13 +213,17 @@ inline hipError_t hipFree(void* p) {
 inline hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return hipMalloc(p, n); }
 inline hipError_t hipHostFree(void* p) { return hipFree(p); }
 inline hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
-    *e = reinterpret_cast<hipEvent_t>(std::malloc(1));
+    *e = new l3cpu_event;
     return hipSuccess;
 }
-inline hipError_t hipEventDestroy(hipEvent_t e) { std::free(e); return hipSuccess; }
-inline hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }   /* launches are synchronous */
-inline hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+inline hipError_t hipEventDestroy(hipEvent_t e) { delete e; return hipSuccess; }
+/* launches are synchronous; an event that a capture recorded stands for nothing outside captures */
+constexpr hipError_t hipErrorCapturedEvent = 907;
+inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { e->captured = s && s->capturing; return hipSuccess; }
+inline hipError_t hipEventSynchronize(hipEvent_t e) { return e->captured ? hipErrorCapturedEvent : hipSuccess; }
+inline hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+    return e->captured && !(s && s->capturing) ? hipErrorCapturedEvent : hipSuccess;
+}
 enum hipMemcpyKind { hipMemcpyHostToDevice = 1 };
 inline hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind, hipStream_t) {
     std::memcpy(dst, src, n);
@@ -230,7 +244,22 @@ inline hipError_t hipLaunchKernel(const void* kernel, dim3 grid, dim3 block, voi
     l3cpu::launch(grid, block, [call, a] { call(a); });
     return hipSuccess;
 }
+enum hipStreamCaptureStatus { hipStreamCaptureStatusNone = 0, hipStreamCaptureStatusActive = 1 };
+inline hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status) {
+    *status = s && s->capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+namespace l3cpu {
+template <class... P, class... A>
+void launch_on(hipStream_t stream, void (*kernel)(P...), dim3 grid, dim3 block, size_t lds_bytes, const A&... args) {
+    if (!stream || !stream->capturing) return launch(grid, block, [&] { kernel(args...); }, lds_bytes);
+    const std::tuple<P...> kept(args...);            /* the arguments' values now, as a recorded launch keeps them */
+    stream->kept.push_back([=](unsigned most) {
+        launch(dim3(grid.x < most ? grid.x : most, grid.y, grid.z), block, [&] { std::apply(kernel, kept); }, lds_bytes);
+    });
+}
+}  // namespace l3cpu
 #define hipLaunchKernelGGL(kernel, grid, block, shared_bytes, stream, ...) \
-    l3cpu::launch((grid), (block), [&] { kernel(__VA_ARGS__); }, (shared_bytes))
+    l3cpu::launch_on((stream), &kernel, (grid), (block), (shared_bytes), __VA_ARGS__)
 
 #endif

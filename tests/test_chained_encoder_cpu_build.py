@@ -65,6 +65,22 @@ def test_calls_on_one_workspace_that_grows_and_counts_on(exes):  # noqa: F811
     case_run(exes, "asan", "table", [noise(990 + k, 1 + k % 9, 1 + k % 6) for k in range(33)], [64])
 
 
+def sequence_run(exes, name, sequence, *args, **kw):            # noqa: F811
+    case = os.path.join(exes["tmp"], "chained_" + name + ".bin")
+    write_case(case, *args, **kw)
+    r = execute(exes["asan"], case, sequence)
+    assert r.returncode == 0, (sequence, r.stderr[-1500:])
+
+
+@pytest.mark.parametrize("sequence", ["cere", "ecrer", "ecpepre"])
+def test_captured_calls_and_ordinary_ones_of_one_context(exes, sequence):    # noqa: F811
+    """c a call that is only recorded (the first of its context too: what is allocated then has not been
+    cleared by anything that ran), r its replay, p a replay of which only the first workgroup has run yet,
+    e an ordinary call: every file that is looked at is the oracle's."""
+    images = [synth.cosine_field(1040, 70, 40), noise(1041, 300, 9)]
+    sequence_run(exes, "capture_" + sequence, sequence, images, [32])
+
+
 def test_one_file_without_that_room_takes_the_whole_call_to_the_other_kernels(exes):  # noqa: F811
     images = [synth.cosine_field(1000 + k, 70, 12) for k in range(3)]
     case_run(exes, "asan", "room", images, [32], room=lambda k, bound: bound - (k == 1))

@@ -128,3 +128,42 @@ def test_replayed_from_a_captured_graph(l3):                    # noqa: F811
         torch.cuda.synchronize()
         same(other, lens, status, now[:1], 32)
     own.close()
+
+
+@pytest.mark.parametrize("mode", ["global", "relaxed"])
+def test_captured_before_the_workspace_has_served_such_a_call(l3, mode):    # noqa: F811
+    """A small call is captured when its context has served one large call only (the default mode allows no
+    allocation), or none (relaxed mode).  Ordinary small calls ahead of the first replay and between the replays."""
+    own = l3.Context(0)
+    image = synth.cosine_field(3100, 333, 210)
+    dev, files = torch.from_numpy(image).cuda(), room_for(l3, [image], 64)
+    lens, status = torch.zeros(1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    side = torch.cuda.Stream()
+    if mode == "global":
+        many = [noise(3110 + k % 3, 500, 375, 0, 60) for k in range(30)]
+        large, n = room_for(l3, many, 32), len(many)
+        all_lens, all_status = torch.zeros(n, dtype=torch.int64, device="cuda"), torch.zeros(n, dtype=torch.int32, device="cuda")
+        large_dev = [torch.from_numpy(im).cuda() for im in many]
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            l3.encode_batch(own, large_dev, large, all_lens, patch=32, status=all_status)
+        torch.cuda.synchronize()
+        same(large, all_lens, all_status, many, 32)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side, capture_error_mode=mode):
+        l3.encode_batch(own, [dev], files, lens, patch=64, status=status)
+    for rep in range(4):
+        print(f"{mode} {rep}", flush=True)
+        other = room_for(l3, [image], 32)
+        with torch.cuda.stream(side):
+            l3.encode_batch(own, [dev], other, lens, patch=32, status=status)
+        torch.cuda.synchronize()
+        same(other, lens, status, [image], 32)
+        files[0].fill_(0xAB)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            graph.replay()
+        torch.cuda.synchronize()
+        same(files, lens, status, [image], 64)
+    own.close()

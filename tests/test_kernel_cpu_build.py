@@ -75,10 +75,10 @@ def write_case(path, mode, images, patch, crops=None, crop=(0, 0), dtype=0, pad_
             f.write(want)
 
 
-def execute(exe, case):
+def execute(exe, case, *more):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0", UBSAN_OPTIONS="print_stacktrace=1",
                TSAN_OPTIONS="halt_on_error=1")
-    return subprocess.run([exe, case], capture_output=True, text=True, env=env, timeout=900)
+    return subprocess.run([exe, case, *more], capture_output=True, text=True, env=env, timeout=900)
 
 
 def run(exe, case):
