@@ -8,9 +8,11 @@
  * barrier orders do.
  *
  * usage: encode_cpu <case file> [sequence]      (written by tests/test_encoder_cpu_build.py)
- * sequence: what each call of the case is, one letter each: e an ordinary call; c a call while the
+ * sequence: what each call of the case is, one letter each: e an ordinary call; x one
+ * whose files are not looked at; c a call while the
  * stream captures (only recorded); r a replay of what was recorded; p a replay of its first workgroup alone, whose
- * files are not looked at.  Without it all are ordinary.
+ * files are not looked at; d disturbs the words that one-kernel calls take their tickets from; l puts the
+ * number of the context's launches near its end.  Without it all are ordinary.
  * Test infrastructure.
  */
 #include <hip/hip_runtime.h>
@@ -91,12 +93,16 @@ int main(int argc, char** argv) {
         l3_status st = L3_OK;
         captured.capturing = sequence[(size_t)call] == 'c';
         if (captured.capturing) captured.kept.clear();
-        if (sequence[(size_t)call] == 'e' || captured.capturing)
+        if (std::strchr("exc", sequence[(size_t)call]))
             st = l3_encode_batch(ctx, items.data(), n, lengths, words, argc == 2 ? nullptr : &captured);
         if (sequence[(size_t)call] == 'r') captured.replay();
         if (sequence[(size_t)call] == 'p') captured.replay(1);
         if (st != L3_OK) { std::fprintf(stderr, "call failed: %s\n", l3_status_string(st)); rc = 1; }
-        if (sequence[(size_t)call] == 'c' || sequence[(size_t)call] == 'p') continue;
+        if (sequence[(size_t)call] == 'd')
+            for (int i = 0; i < n; ++i)
+                for (int w = 0; w < 2; ++w) reinterpret_cast<uint64_t*>(&ctx->enc->d_words[i])[w] += 2;
+        if (sequence[(size_t)call] == 'l') ctx->enc->chain_number = kLastNumber - 5;
+        if (sequence[(size_t)call] != 'e' && sequence[(size_t)call] != 'r') continue;
         for (int i = 0; i < n && rc == 0; ++i) {
             const std::vector<uint8_t>& want = expected[(size_t)i];
             const size_t cap = items[(size_t)i].file_cap;

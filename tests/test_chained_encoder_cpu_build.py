@@ -81,6 +81,33 @@ def test_captured_calls_and_ordinary_ones_of_one_context(exes, sequence):    # n
     sequence_run(exes, "capture_" + sequence, sequence, images, [32])
 
 
+SOURCE = open(os.path.join(ROOT, "paper_2208_08711_amd", "csrc", "l3_encode.hip")).read()
+
+
+@pytest.fixture(scope="module")
+def few_looks(exes):                                            # noqa: F811
+    """The same with waits that end after 8 looks: a look is slow on host threads."""
+    old = "constexpr uint32_t kMaxLooks = 1u << 20;"
+    assert SOURCE.count(old) == 1
+    path = os.path.join(exes["tmp"], "l3_encode_few_looks.hip")
+    with open(path, "w") as f:
+        f.write(SOURCE.replace(old, "constexpr uint32_t kMaxLooks = 8;"))
+    return dict(exes, asan=build(exes["tmp"], "encode_few_looks", ASAN, kernel_source=path))
+
+
+def test_a_disturbed_word_is_right_again_a_launch_later(few_looks):
+    """d takes tickets as launches that overlapped would; x is the call that finds the word so, and only that one
+    is wrong.  Two patch sizes are two launches a call."""
+    images = [synth.cosine_field(1050, 70, 40), noise(1051, 300, 9), noise(1052, 3, 3)]
+    for sequence, patches in (("edxee", [32]), ("edxedxe", [32, 64, 32])):
+        sequence_run(few_looks, "disturbed_" + sequence, sequence, images, patches)
+
+
+def test_the_numbers_of_launches_begin_again(exes):             # noqa: F811
+    images = [synth.cosine_field(1050, 70, 40), noise(1051, 300, 9), noise(1052, 3, 3)]
+    sequence_run(exes, "last_number", "eleeee", images, [32, 64, 32])
+
+
 def test_one_file_without_that_room_takes_the_whole_call_to_the_other_kernels(exes):  # noqa: F811
     images = [synth.cosine_field(1000 + k, 70, 12) for k in range(3)]
     case_run(exes, "asan", "room", images, [32], room=lambda k, bound: bound - (k == 1))
