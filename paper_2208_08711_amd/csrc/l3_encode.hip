@@ -55,10 +55,7 @@ struct L3EncodeDesc {
     uint32_t sizes_base;     /* first entry of this image in the sizes scratch */
     uint32_t status_index;
     uint32_t strips_x;       /* strip route: wave strips per patch row */
-    union {
-        uint64_t slots_base; /* strip route: byte offset of this image's first slot in the workspace */
-        uint64_t chain_turn; /* chained route: turn of the call's first launch, see L3ChainWord */
-    };
+    uint64_t slots_base;     /* strip route: byte offset of this image's first slot in the workspace */
 };
 
 __device__ __forceinline__ int nearest_upper(int tl, int t, int tr) {
@@ -839,12 +836,12 @@ struct UnitGeom {
  * includes all units ahead in the image, and a number of bytes.  A cell with another number is from an
  * earlier launch.  The host counts a context's launches and passes each its number; the images of a launch
  * have their units' cells one behind the other.
- * Tickets are taken from a word that holds the image's turn, which is how many launches had an image in
- * this place, and the next unit.  An image has two such words in turn, and each launch makes the other one
- * ready for the next: nothing is cleared between launches, and words that anything has disturbed are right
- * again a launch later.  (One word that is raised to the launch's number and then taken from does the same with two
- * accesses a workgroup, which queue up at the word, some 10 ns each: one image of 1920x1080 23.1 us instead of 19.9, one
- * of 3840x1500 at N = 32 77.7 instead of 57.3.)  After 2^35 launches, 5 us apart two days, cells and words are cleared and
+ * Tickets are taken from a word that holds the launch's number and the image's next unit.  An image has two
+ * such words, for even and odd numbers, and each launch makes the other ones ready for the next, also those of
+ * images that it has not itself: nothing is cleared between launches, and words that anything has disturbed are
+ * right again a launch later.  (One word that is raised to the launch's number and then taken from does the same with
+ * two accesses a workgroup, which queue up at the word, some 10 ns each: one image of 1920x1080 23.1 us instead of 19.4, one
+ * of 3840x1500 at N = 32 77.7 instead of 57.0.)  After 2^35 launches, 5 us apart two days, all are cleared and
  * numbers begin again. */
 constexpr int kCellValueBits = 28;
 constexpr uint64_t kChainMaxBytes = (1ull << kCellValueBits) - 1;
@@ -852,7 +849,7 @@ constexpr uint64_t kCellWhole = 1ull << kCellValueBits;
 constexpr int kNumberShift = kCellValueBits + 1;
 constexpr uint64_t kLastNumber = ~0ull >> kNumberShift;
 struct __attribute__((aligned(128))) L3ChainWord {      /* many workgroups add to it: a cache line each */
-    uint64_t ticket[2];                                 /* turn << 29 | the image's next unit; of even and odd turns */
+    uint64_t ticket[2];                                 /* number << 29 | the image's next unit; of even and odd numbers */
 };
 
 /* Calls that take this route: few units, N = 32 ones counted by two thirds (four waves, not eight).  Every
@@ -1101,7 +1098,7 @@ __device__ __forceinline__ void encode_unit(const L3EncodeDesc& d, const uint32_
 
 template <int N, class Descs>
 __device__ __forceinline__ void chain_block(const Descs& descs, uint32_t units_per_image, L3ChainWord* __restrict__ words,
-                                            uint64_t* __restrict__ cells, uint64_t number, uint32_t nth,
+                                            uint64_t* __restrict__ cells, uint64_t number, uint32_t slots,
                                             uint64_t* __restrict__ file_len, uint32_t* __restrict__ status) {
     const uint32_t image = blockIdx.x / units_per_image;      /* in dispatch order: see encode_unit */
     /* what the rows' addresses wait for is read while the ticket travels */
@@ -1118,19 +1115,21 @@ __device__ __forceinline__ void chain_block(const Descs& descs, uint32_t units_p
     L3_KEEP_SGPR(d.status_index);
     L3_KEEP_SGPR(words);
     __shared__ uint64_t taken;
-    const uint64_t turn = d.chain_turn + nth;
     if (threadIdx.x == 0) {
-        if (d.patch == N) taken = agent_add_u64(&words[image].ticket[turn & 1], 1);
+        taken = agent_add_u64(&words[image].ticket[number & 1], 1);
         if (blockIdx.x == image * units_per_image)
-            agent_store_u64(&words[image].ticket[~turn & 1], (turn + 1) << kNumberShift);
+            agent_store_u64(&words[image].ticket[~number & 1], (number + 1) << kNumberShift);
     }
+    if (blockIdx.x == 0)
+        for (uint32_t i = gridDim.x / units_per_image + threadIdx.x; i < slots; i += blockDim.x)
+            agent_store_u64(&words[i].ticket[~number & 1], (number + 1) << kNumberShift);
     if (d.patch != N) return;
     __syncthreads();
     const uint32_t low = __builtin_amdgcn_readfirstlane((uint32_t)taken);
     const uint32_t high = __builtin_amdgcn_readfirstlane((uint32_t)(taken >> 32));
     const uint32_t unit = low & (uint32_t)(kCellWhole * 2 - 1);
     const uint32_t units = 3 * d.strips_x * d.tiles_y;
-    if (((uint64_t)high << 32 | low) >> kNumberShift != turn) {      /* a disturbed word */
+    if (((uint64_t)high << 32 | low) >> kNumberShift != number) {      /* a disturbed word */
         if (threadIdx.x == 0 && status) atomicOr(&status[d.status_index], kStatusGaveUp);
         return;
     }
@@ -1140,20 +1139,23 @@ __device__ __forceinline__ void chain_block(const Descs& descs, uint32_t units_p
 template <int N>
 __global__ __launch_bounds__(UnitGeom<N>::THREADS) void l3_encode_chain_kernel(
     const L3EncodeDesc* __restrict__ descs, uint32_t units_per_image, L3ChainWord* __restrict__ words,
-    uint64_t* __restrict__ cells, uint64_t number, uint32_t nth, uint64_t* __restrict__ file_len,
+    uint64_t* __restrict__ cells, uint64_t number, uint32_t slots, uint64_t* __restrict__ file_len,
     uint32_t* __restrict__ status) {
-    chain_block<N>(descs, units_per_image, words, cells, number, nth, file_len, status);
+    chain_block<N>(descs, units_per_image, words, cells, number, slots, file_len, status);
 }
 template <int N, int CAP>
 __global__ __launch_bounds__(UnitGeom<N>::THREADS) void l3_encode_chain_kernel_args(
     const EncodePack<CAP> pack, uint32_t units_per_image, L3ChainWord* __restrict__ words,
-    uint64_t* __restrict__ cells, uint64_t number, uint32_t nth, uint64_t* __restrict__ file_len,
+    uint64_t* __restrict__ cells, uint64_t number, uint32_t slots, uint64_t* __restrict__ file_len,
     uint32_t* __restrict__ status) {
-    chain_block<N>(pack.d, units_per_image, words, cells, number, nth, file_len, status);
+    chain_block<N>(pack.d, units_per_image, words, cells, number, slots, file_len, status);
 }
 __global__ void l3_encode_clear_kernel(L3ChainWord* __restrict__ words, uint64_t* __restrict__ cells) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < kMostChainImages) words[i].ticket[0] = words[i].ticket[1] = 0;
+    if (i < kMostChainImages) {
+        words[i].ticket[0] = 2ull << kNumberShift;       /* the first launch behind this has the number 2 */
+        words[i].ticket[1] = 0;
+    }
     if (i < kMostChainUnits) cells[i] = 0;
 }
 
@@ -1259,7 +1261,7 @@ struct L3EncodeState {
     size_t slots_cap = 0;
     L3ChainWord* d_words = nullptr;  /* chained route: words of kMostChainImages images, and behind them kMostChainUnits cells */
     uint64_t chain_number = 0;       /* of its last launch; 0: not cleared yet, no launch has it or 1 */
-    uint64_t chain_turns[kMostChainImages] = {};
+    uint32_t chain_slots = 32;       /* images whose words every launch makes ready: the most a call has had, or twice that */
     hipEvent_t done = nullptr;       /* the last call's kernels have finished */
     bool pending = false;
     hipStream_t last_stream = nullptr;
@@ -1389,7 +1391,10 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
             st->d_words = nullptr;
         }
         chained &= ordinary && st->d_words != nullptr;
-        if (ordinary && st->d_words && (st->chain_number == 0 || st->chain_number + 3 > kLastNumber)) {
+        const uint32_t images = chained ? (uint32_t)n : 0u;
+        if (ordinary && st->d_words &&
+            (st->chain_number == 0 || st->chain_number + 3 > kLastNumber || images > st->chain_slots)) {
+            while (st->chain_slots < images) st->chain_slots *= 2;
             st->chain_number = 0;                       /* until the clear is enqueued and all calls are behind it */
             hipLaunchKernelGGL(l3_encode_clear_kernel, dim3((kMostChainUnits + 255) / 256), dim3(256), 0, stream,
                                st->d_words, reinterpret_cast<uint64_t*>(st->d_words + kMostChainImages));
@@ -1397,7 +1402,6 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
             st->pending = true;
             st->last_stream = stream;
             st->chain_number = 1;
-            std::memset(st->chain_turns, 0, sizeof st->chain_turns);
         }
     }
     if (total_patches > st->sizes_cap) {
@@ -1446,8 +1450,7 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
         if (np == 32 || np == 64 || np == 128) {
             const uint32_t tpw = 256 / np;
             d.strips_x = (d.tiles_x + tpw - 1) / tpw;
-            if (chained) d.chain_turn = st->chain_turns[i];
-            else d.slots_base = slots_base;
+            d.slots_base = slots_base;
             slots_base += 3 * (size_t)d.tiles_x * d.tiles_y * strip_slot_bytes(np);
         }
         base += 3 * (size_t)d.tiles_x * d.tiles_y;
@@ -1464,28 +1467,25 @@ extern "C" l3_status l3_encode_batch(l3_ctx* ctx, const l3_encode_item* items, i
     }
     if (chained) {
         uint64_t* const cells = reinterpret_cast<uint64_t*>(st->d_words + kMostChainImages);
-        uint32_t launches = 0;
         const auto encode = [&](auto n_tag, uint32_t strips) {
             constexpr int N = decltype(n_tag)::value;
             if (!strips) return;
             const uint32_t units = 3 * strips;
             const uint64_t number = ++st->chain_number;
-            const uint32_t nth = launches++;
             const dim3 grid(units * (uint32_t)n);
             if (by_args && small)
                 hipLaunchKernelGGL((l3_encode_chain_kernel_args<N, kArgDescsSmall>), grid, dim3(UnitGeom<N>::THREADS), 0, stream,
-                                   small_pack, units, st->d_words, cells, number, nth, d_file_len, d_status);
+                                   small_pack, units, st->d_words, cells, number, st->chain_slots, d_file_len, d_status);
             else if (by_args)
                 hipLaunchKernelGGL((l3_encode_chain_kernel_args<N, kArgDescs>), grid, dim3(UnitGeom<N>::THREADS), 0, stream, pack,
-                                   units, st->d_words, cells, number, nth, d_file_len, d_status);
+                                   units, st->d_words, cells, number, st->chain_slots, d_file_len, d_status);
             else
                 hipLaunchKernelGGL(l3_encode_chain_kernel<N>, grid, dim3(UnitGeom<N>::THREADS), 0, stream, st->d_descs,
-                                   units, st->d_words, cells, number, nth, d_file_len, d_status);
+                                   units, st->d_words, cells, number, st->chain_slots, d_file_len, d_status);
         };
         encode(std::integral_constant<int, 32>(), strip_units[0]);
         encode(std::integral_constant<int, 64>(), strip_units[1]);
         encode(std::integral_constant<int, 128>(), strip_units[2]);
-        for (int i = 0; i < n; ++i) st->chain_turns[i] += launches;
     } else if (by_args) {
         const uint32_t m = (uint32_t)n;
         const auto launch = [&](const auto& descs, auto cap_tag) {
