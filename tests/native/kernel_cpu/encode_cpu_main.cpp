@@ -100,11 +100,11 @@ int main(int argc, char** argv) {
         if (st != L3_OK) { std::fprintf(stderr, "call failed: %s\n", l3_status_string(st)); rc = 1; }
         if (sequence[(size_t)call] == 'd')
             for (int i = 0; i < n; ++i)
-                for (int w = 0; w < 2; ++w) reinterpret_cast<uint64_t*>(&ctx->enc->d_words[i])[w] += 2;
+                for (L3Ticket& ticket : ctx->enc->d_words[i].ticket) ticket.next += 2;
         if (sequence[(size_t)call] == 'l') {
             const uint64_t next = kLastNumber - 4;
             ctx->enc->chain_number = next - 1;
-            for (uint32_t i = 0; i < kMostChainImages; ++i) ctx->enc->d_words[i].ticket[next & 1] = next << kNumberShift;
+            for (uint32_t i = 0; i < kMostChainImages; ++i) ctx->enc->d_words[i].ticket[next & 1].next = next << kNumberShift;
         }
         if (sequence[(size_t)call] != 'e' && sequence[(size_t)call] != 'r') continue;
         for (int i = 0; i < n && rc == 0; ++i) {
