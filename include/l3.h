@@ -227,8 +227,8 @@ typedef struct {
  *               too small (header and offsets are written if they fit, no patch
  *               data; nothing is written beyond file_cap); bit 1 = encoded data
  *               beyond 4 GiB (not representable in the format's 32-bit offsets); bit 2 = part
- *               of the file not written: a wait between workgroups, which lasts microseconds,
- *               had not ended after about a second.
+ *               of the file not written and its length not to be used: a wait between
+ *               workgroups, which lasts microseconds, had not ended after about a second.
  *   stream      a hipStream_t; the call returns after enqueueing.  Calls on one
  *               context share one workspace: on the device a call runs after the
  *               kernels of the previous one, whatever their streams; the host

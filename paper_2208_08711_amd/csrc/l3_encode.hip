@@ -853,6 +853,7 @@ constexpr uint64_t kLastNumber = ~0ull >> kNumberShift;
 struct __attribute__((aligned(128))) L3Ticket { uint64_t next; };   /* number << 29 | the image's next unit */
 struct L3ChainWord {
     L3Ticket ticket[2];                                 /* of even and odd numbers */
+    uint64_t gave_up;                                   /* the last launch in which a unit of the image was not written */
 };
 
 /* Calls that take this route: few units, N = 32 ones counted by two thirds (four waves, not eight).  Every
@@ -878,6 +879,15 @@ constexpr uint32_t kMostChainImages = kMostChainUnits / 3;      /* no image has 
  * not be written and its image's status word would say so. */
 constexpr uint32_t kMaxLooks = 1u << 20;
 constexpr uint32_t kStatusGaveUp = 4u;
+
+/* The status word is cleared by the image's unit 0, which may be the one that the others wait for in vain.  So who
+ * gives up first leaves the launch's number in the image's word and then sets the bit, and unit 0 first clears and
+ * then looks for that number: one of the two sees the other.  Each waits for its first access's answer. */
+__device__ __forceinline__ void give_up(L3ChainWord* word, uint64_t number, uint32_t* status) {
+    uint64_t before = agent_exchange_u64(&word->gave_up, number);
+    L3_WAIT_FOR(before);
+    if (status) atomicOr(status, kStatusGaveUp);
+}
 
 /* The cells of the 512 units that end `behind` units ahead of `unit`, in the lanes of a wave; `cell` is
  * the unit's own, those of the units ahead lie in front of it. */
@@ -930,7 +940,7 @@ __device__ __forceinline__ bool bytes_ahead(ChainLook look, const uint64_t* cell
 
 template <int N>
 __device__ __forceinline__ void encode_unit(const L3EncodeDesc& d, const uint32_t unit, const uint32_t units,
-                                            const uint64_t number, uint64_t* __restrict__ cell,
+                                            const uint64_t number, L3ChainWord* __restrict__ word, uint64_t* __restrict__ cell,
                                             uint64_t* __restrict__ file_len, uint32_t* __restrict__ status) {
     using G = UnitGeom<N>;
     constexpr int LPT = G::LPT, TPW = G::TPW, R = G::R, Q = G::Q, WAVES = G::WAVES;
@@ -1038,6 +1048,9 @@ __device__ __forceinline__ void encode_unit(const L3EncodeDesc& d, const uint32_
     const bool looks_back = wave == WAVES - 1;   /* the wave with the fewest rows */
     if (looks_back && lane == 0)
         agent_store_u64(cell, number << kNumberShift | (unit == 0 ? kCellWhole : 0u) | unit_bytes);
+    /* behind the size that the others wait for */
+    uint32_t cleared = 0;
+    if (unit == 0 && threadIdx.x == 0 && status) cleared = agent_exchange_u32(&status[d.status_index], 0);
 
     /* the deltas of all rows into the unit's bytes */
     const uint32_t stream_lds = lds_address_of(stream);
@@ -1078,16 +1091,16 @@ __device__ __forceinline__ void encode_unit(const L3EncodeDesc& d, const uint32_
     const uint64_t header = 13 + 12ull * patches;
     const uint32_t at = place[0];
     if (!place[1]) {
-        if (threadIdx.x == 0 && status) atomicOr(&status[d.status_index], kStatusGaveUp);
+        if (threadIdx.x == 0) {
+            give_up(word, number, status ? &status[d.status_index] : nullptr);
+            if (unit == units - 1) file_len[d.status_index] = 0;
+        }
         return;
     }
     if (wave == 0 && xl == 0 && active)          /* Section 4.3, the offset array of channel c */
         *reinterpret_cast<global_u32_any*>((uintptr_t)(d.file + 13 + 4 * (size_t)(c * patches + ty * d.tiles_x + tx))) = at + patch_at;
     if (threadIdx.x == 0) {
-        if (unit == 0) {
-            write_fixed_header(d);
-            if (status) status[d.status_index] = 0;
-        }
+        if (unit == 0) write_fixed_header(d);
         if (unit == units - 1) file_len[d.status_index] = header + at + unit_bytes;
     }
     uint8_t* const to = d.file + header + at;
@@ -1097,6 +1110,10 @@ __device__ __forceinline__ void encode_unit(const L3EncodeDesc& d, const uint32_
         *reinterpret_cast<global_u32x4_any*>((uintptr_t)(to + 16 * (size_t)i)) = reinterpret_cast<const u32x4*>(from)[i];
     if (threadIdx.x < tail)
         to[16 * (size_t)whole + threadIdx.x] = reinterpret_cast<const uint8_t*>(from)[16 * (size_t)whole + threadIdx.x];
+    if (unit == 0 && threadIdx.x == 0 && status) {
+        L3_WAIT_FOR(cleared);
+        if (agent_load_u64(&word->gave_up) == number) atomicOr(&status[d.status_index], kStatusGaveUp);
+    }
 }
 
 template <int N, class Descs>
@@ -1133,11 +1150,11 @@ __device__ __forceinline__ void chain_block(const Descs& descs, uint32_t units_p
     const uint32_t unit = low & (uint32_t)(kCellWhole * 2 - 1);
     const uint32_t units = 3 * d.strips_x * d.tiles_y;
     if (((uint64_t)high << 32 | low) >> kNumberShift != number) {      /* a disturbed word */
-        if (threadIdx.x == 0 && status) atomicOr(&status[d.status_index], kStatusGaveUp);
+        if (threadIdx.x == 0) give_up(&words[image], number, status ? &status[d.status_index] : nullptr);
         return;
     }
     if (unit < units)
-        encode_unit<N>(d, unit, units, number, cells + (size_t)image * units_per_image + unit, file_len, status);
+        encode_unit<N>(d, unit, units, number, &words[image], cells + (size_t)image * units_per_image + unit, file_len, status);
 }
 template <int N>
 __global__ __launch_bounds__(UnitGeom<N>::THREADS) void l3_encode_chain_kernel(
@@ -1157,7 +1174,7 @@ __global__ void l3_encode_clear_kernel(L3ChainWord* __restrict__ words, uint64_t
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < kMostChainImages) {
         words[i].ticket[0].next = 2ull << kNumberShift;       /* the first launch behind this has the number 2 */
-        words[i].ticket[1].next = 0;
+        words[i].ticket[1].next = words[i].gave_up = 0;
     }
     if (i < kMostChainUnits) cells[i] = 0;
 }

@@ -164,6 +164,12 @@ __device__ __forceinline__ void agent_store_u64(uint64_t* p, uint64_t v) {
 __device__ __forceinline__ void agent_store_u32(uint32_t* p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ uint32_t agent_exchange_u32(uint32_t* p, uint32_t v) {
+    return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t agent_exchange_u64(uint64_t* p, uint64_t v) {
+    return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ uint64_t agent_add_u64(uint64_t* p, uint64_t v) {
     return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -179,6 +185,8 @@ __device__ __forceinline__ uint32_t agent_add_u32(uint32_t* p, uint32_t v) {
 /* The value becomes opaque to the optimiser and stays in a vector (scalar) register: used
  * where the compiler would otherwise widen, rematerialise or reload it at a bad place. */
 #define L3_KEEP_VGPR(x) asm volatile("" : "+v"(x))
+/* memory accesses behind this follow the one that x comes from */
+#define L3_WAIT_FOR(x) asm volatile("" : "+v"(x) : : "memory")
 #define L3_KEEP_SGPR(x) asm volatile("" : "+s"(x))
 
 __device__ __forceinline__ void wave_lds_fence() {

@@ -222,6 +222,8 @@ inline uint32_t l3cpu_bitop3(uint32_t a, uint32_t b, uint32_t c, uint32_t table)
 inline uint64_t agent_load_u64(const uint64_t* p) { return __atomic_load_n(p, __ATOMIC_RELAXED); }
 inline void agent_store_u64(uint64_t* p, uint64_t v) { __atomic_store_n(p, v, __ATOMIC_RELAXED); }
 inline void agent_store_u32(uint32_t* p, uint32_t v) { __atomic_store_n(p, v, __ATOMIC_RELAXED); }
+inline uint32_t agent_exchange_u32(uint32_t* p, uint32_t v) { return __atomic_exchange_n(p, v, __ATOMIC_RELAXED); }
+inline uint64_t agent_exchange_u64(uint64_t* p, uint64_t v) { return __atomic_exchange_n(p, v, __ATOMIC_RELAXED); }
 inline uint64_t agent_add_u64(uint64_t* p, uint64_t v) { return __atomic_fetch_add(p, v, __ATOMIC_RELAXED); }
 inline uint32_t agent_add_u32(uint32_t* p, uint32_t v) { return __atomic_fetch_add(p, v, __ATOMIC_RELAXED); }
 
@@ -261,6 +263,8 @@ inline void lds_or_pair(uint32_t where, uint32_t lo, uint32_t hi) {
 #define L3_DYNAMIC_LDS(type, name) type* name = reinterpret_cast<type*>(l3cpu::dynamic_lds())
 
 #define L3_KEEP_VGPR(x) asm volatile("" : "+r"(x))
+/* memory accesses behind this follow the one that x comes from */
+#define L3_WAIT_FOR(x) asm volatile("" : "+r"(x) : : "memory")
 #define L3_KEEP_SGPR(x) asm volatile("" : "+r"(x))
 
 /* the lanes of a wave, which are threads here, meet: what one wrote to LDS the others see */

@@ -103,6 +103,23 @@ def test_a_disturbed_word_is_right_again_a_launch_later(few_looks):
         sequence_run(few_looks, "disturbed_" + sequence, sequence, images, patches)
 
 
+def test_a_unit_that_is_not_written_shows_in_the_status_word(exes):    # noqa: F811
+    """A copy of the source with few looks that takes an image's units from the last to the first: all but unit 0
+    wait in vain, and unit 0, which clears the status word, is the last to run."""
+    path = os.path.join(exes["tmp"], "l3_encode_reversed.hip")
+    call = "encode_unit<N>(d, unit, units, number, &words[image], cells + (size_t)image * units_per_image + unit,"
+    assert SOURCE.count(call) == 1
+    with open(path, "w") as f:
+        f.write(SOURCE.replace("constexpr uint32_t kMaxLooks = 1u << 20;", "constexpr uint32_t kMaxLooks = 8;")
+                .replace(call, call.replace(" unit,", " units - 1 - unit,")))
+    exe = build(exes["tmp"], "encode_reversed", ASAN, kernel_source=path)
+    case = os.path.join(exes["tmp"], "chained_reversed.bin")
+    write_case(case, [noise(1060, 300, 9)], [32])
+    r = execute(exe, case)
+    assert r.returncode == 1, r.stderr[-1500:]
+    assert r.stderr.splitlines()[:2] == ["MISMATCH: length, image 0: 0", "MISMATCH: status, image 0: 4"], r.stderr[-1500:]
+
+
 def test_the_numbers_of_launches_begin_again(exes):             # noqa: F811
     images = [synth.cosine_field(1050, 70, 40), noise(1051, 300, 9), noise(1052, 3, 3)]
     sequence_run(exes, "last_number", "eleeee", images, [32, 64, 32])
