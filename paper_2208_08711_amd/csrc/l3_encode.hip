@@ -869,14 +869,24 @@ struct L3ChainWord {
  * 2048x1024 fetch 591 MB instead of 201), which the strip kernel and the copy then do better; 4 a CU
  * is where they draw level.  An image of so many patches that they would need the layout kernel
  * between them (own_layout_pays) is worth it up to 12 a CU.  A call by the strip kernel / by this (units):
- *   N = 32    1 of 64x64 (6) 16.5 / 11.4 us, 1 photograph (72) 18.7 / 12.1, 16 (1152) 25.3 / 20.9, 4 of 1024x720 (1104) 25.4 / 21.7,
- *             6 (1656) 28.9 / 27.5, 8 (2208) 29.6 / 32.9, 32 74.6 / 96.2; with the layout kernel 1 of 3840x1500 (2115) 107.7 / 58.3
- *   N = 64    1 of 1920x1080 (408) 27.0 / 19.6, 2 (816) 32.1 / 27.7, 3 (1224) 32.9 / 33.5, 4 (1632) 38.9 / 40.4, 32 182.8 / 249.5;
- *             with the layout kernel 1 of 5000x2500 (2400) 92.7 / 69.1
- *   N = 128   1 of 2048x1024 (192) 39.2 / 16.0, 4 (768) 42.9 / 32.9, 8 (1536) 58.5 / 51.5, 16 (3072) 94.9 / 95.1, 1 of 3840x2160 (765)
- *             42.7 / 40.3, 2 (1530) 59.8 / 63.7 */
+ *   N = 32    1 of 64x64 (6) 16.5 / 11.4 us, 1 photograph (72) 18.7 / 11.2, 16 (1056) 22.9 / 17.9, 4 of 1024x720 (1104) 24.7 / 20.7;
+ *             with the layout kernel 1 of 3840x1500 (2115) 107.7 / 56.7
+ *   N = 64    1 of 1920x1080 (408) 27.5 / 19.1, 2 (816) 32.4 / 26.2; with the layout kernel 1 of 2816x2048 (1056) 50.9 / 37.7
+ *   N = 128   1 of 2048x1024 (192) 39.3 / 15.8, 4 (768) 42.9 / 32.4, 1 of 3840x2160 (765) 42.7 / 39.5
+ * and beyond the line, measured when this kernel was a few percent slower,
+ *   N = 32    6 of 1024x720 (1656) 28.9 / 27.5, 8 (2208) 29.6 / 32.9, 32 74.6 / 96.2
+ *   N = 64    3 of 1920x1080 (1224) 32.9 / 33.5, 4 (1632) 38.9 / 40.4, 32 182.8 / 249.5
+ *   N = 128   8 of 2048x1024 (1536) 58.5 / 51.5, 16 (3072) 94.9 / 95.1, 2 of 3840x2160 (1530) 59.8 / 63.7 */
 constexpr uint32_t kMostChainUnits = 3072;
+/* The units of one image also wait for one another, at their ticket and in their looks: long images are the
+ * strip kernel's sooner.  (At N = 128, where a unit is twice the work, they are not before the 1024 above.)
+ *   N = 32    1 of 1200x1000 (480) 20.9 / 18.3, 2 of 1000x1300 (984, 492 each) 23.9 / 24.2, 2 of 1100x1150 (1080, 540 each) 23.8 / 25.7
+ *   N = 64    1 of 1920x1408 (528) 25.9 / 23.0, 1 of 2100x1600 (675) 26.9 / 26.9, 1 of 2400x1600 (750) 27.3 / 27.9,
+ *             1 of 2048x2048 (768) 26.1 / 28.7, 1 of 2560x1900 (900) 30.4 / 33.4
+ *   N = 128   1 of 4096x2304 (864) 49.0 / 41.9, 1 of 4096x2560 (960) 49.7 / 44.6 */
+constexpr uint32_t kMostUnitsOfOne[2] = {480, 640};
 constexpr bool chained_pays(const uint32_t (&strips)[3], uint64_t images, bool own_layout) {
+    if (own_layout && (3 * strips[0] > kMostUnitsOfOne[0] || 3 * strips[1] > kMostUnitsOfOne[1])) return false;
     const uint64_t two_thirds = 3 * images * (2ull * strips[0] + 3ull * strips[1] + 3ull * strips[2]);   /* of units, times 3 */
     return two_thirds <= 3ull * (own_layout ? 1024 : kMostChainUnits) && 3 * images * strips[0] <= kMostChainUnits;
 }

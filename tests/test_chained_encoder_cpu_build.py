@@ -86,12 +86,12 @@ SOURCE = open(os.path.join(ROOT, "paper_2208_08711_amd", "csrc", "l3_encode.hip"
 
 @pytest.fixture(scope="module")
 def few_looks(exes):                                            # noqa: F811
-    """The same with waits that end after 8 looks: a look is slow on host threads."""
-    old = "constexpr uint32_t kMaxLooks = 1u << 20;"
-    assert SOURCE.count(old) == 1
+    """The same with waits that end after 8 looks (a look is slow on host threads), for images of any number of units."""
+    old, most = "constexpr uint32_t kMaxLooks = 1u << 20;", "kMostUnitsOfOne[2] = {480, 640};"
+    assert SOURCE.count(old) == 1 and SOURCE.count(most) == 1
     path = os.path.join(exes["tmp"], "l3_encode_few_looks.hip")
     with open(path, "w") as f:
-        f.write(SOURCE.replace(old, "constexpr uint32_t kMaxLooks = 8;"))
+        f.write(SOURCE.replace(old, "constexpr uint32_t kMaxLooks = 8;").replace(most, "kMostUnitsOfOne[2] = {3072, 3072};"))
     return dict(exes, asan=build(exes["tmp"], "encode_few_looks", ASAN, kernel_source=path))
 
 
@@ -130,9 +130,10 @@ def test_one_file_without_that_room_takes_the_whole_call_to_the_other_kernels(ex
     case_run(exes, "asan", "room", images, [32], room=lambda k, bound: bound - (k == 1))
 
 
-def test_more_units_than_one_look_takes_in(exes):               # noqa: F811
-    """520 units of one patch column: the last ones look 512 units back and find a total there or further."""
-    case_run(exes, "asan", "long", [noise(1010, 1, 32 * 173 + 5)], [32])
+def test_more_units_than_one_look_takes_in(few_looks):
+    """522 units of one patch column: the last ones look 512 units back and find a total there or further.  (In a
+    copy of the source that takes images of that many units whatever their patches.)"""
+    case_run(few_looks, "asan", "long", [noise(1010, 1, 32 * 173 + 5)], [32])
 
 
 @pytest.mark.parametrize("patch", [32, 64, 128])

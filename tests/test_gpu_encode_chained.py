@@ -49,6 +49,15 @@ def test_many_units_of_one_image(l3, ctx):                      # noqa: F811
     check(l3, ctx, [noise(2602, 32 * 48, 32 * 100, 0, 9)], patch=32)
 
 
+@pytest.mark.parametrize("patch,strips,most", [(32, 4, 40), (64, 7, 30), (64, 3, 71)])
+def test_both_sides_of_the_rule_for_one_image(l3, ctx, patch, strips, most):    # noqa: F811
+    """Images of at most 480 units at N = 32 and 640 at N = 64 take the one kernel, longer ones the strip kernel, and
+    those of more than 4096 patches the one kernel again."""
+    for rows in (most, most + 1):
+        check(l3, ctx, [noise(2650 + rows, 255 * strips, patch * rows - 3, 0, 30)], patch=patch)
+    check(l3, ctx, [noise(2660, 64 * 40, 64 * 35, 0, 9)], patch=64)
+
+
 @pytest.mark.parametrize("patch,shape,most", [(32, (500, 375), 21), (64, (640, 500), 14), (128, (700, 500), 28)])
 def test_both_sides_of_the_rule(l3, ctx, patch, shape, most):   # noqa: F811
     """`most` images of 72 (N = 32), 72 and 36 units are the last that the rule's 1536 and 1024 units hold."""
