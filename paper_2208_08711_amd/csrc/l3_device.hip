@@ -284,17 +284,16 @@ struct RowWriter {
             /* A lane takes four columns whose elements start at a multiple of 8 bytes in a row of the
              * window, not the four of its own word: no lane's columns lie across the window's edge.
              * The strip's columns ahead of the first such four and behind the last, up to three
-             * each, are taken one a lane, all channels at once.  (Where the window's width is no multiple of
-             * four its rows start at any alignment, and the fours at the strip's first column.)  With the
-             * strip's own words those on the window's edges went element by element, for which a
-             * wave waited in every row with three of four windows: 256 windows of 224x224 32.9 -> 27.2 us a
-             * call, 16 of 768x768 54.1 -> 47.1, 16 of 401x300 at N = 128 48.0 -> 41.6, 8 of 1999x1501 59.9 -> 58.6;
-             * without the alignment 16 of 768x768 took 3 us more.  (20 of 1001x777 at N = 64 went from 41.0 to
-             * 41.4.) */
+             * each, are taken one a lane, all channels at once.  Where the window's width is no multiple of
+             * four its rows start at any alignment, and the fours are the strip's own words.
+             * (With the strip's own words and their edges element by element 256 windows of 224x224 took 32.9 us a call,
+             * 27.2 so, 16 of 768x768 54.1 and 47.1; without the alignment 16 of 768x768 took 3 us more.  Widths of
+             * no multiple of four: fours from the window's first column on, and the single columns behind the fours,
+             * had cost 256 of 225x225 37.4 us and 20 of 1399x999 at N = 64 74.8; own words 35.8 and 74.4, and see write_row.) */
             const int32_t before = win_x0 - (int32_t)at.strip_x0;       /* the window's first column, in the strip */
             const int32_t from = max(before, 0);
             const uint32_t count = (uint32_t)(min(before + (int32_t)crop_w, 256) - from);
-            const uint32_t head = crop_w % 4 ? 0u : min(count, (uint32_t)(before - from) & 3u);
+            const uint32_t head = min(count, (crop_w % 4 ? (uint32_t)-from : (uint32_t)(before - from)) & 3u);
             const uint32_t fours = (count - head) / 4, tail = (count - head) & 3u;
             takes_four = lane < fours;
             strip_at = (uint32_t)from + head + 4 * lane;
@@ -383,6 +382,13 @@ struct RowWriter {
                     /* element (ch, row, 0) of this image; planes are crop_h * crop_w apart: the
                      * planes' rows start at scalar addresses, the lane adds its byte offset */
                     const size_t plane = (size_t)crop_h * crop_w;
+                    /* ahead of the fours, whose stores leave the cache sooner and then find the lines that
+                     * they share with these begun: behind them 256 windows of 225x225 took 35.8 us, so 31.6, 20 of
+                     * 1399x999 at N = 64 74.4 and 70.1, 16 of 768x768 37.9 and 37.3 */
+                    if (lane < singles) {
+                        const uint32_t value = reinterpret_cast<const uint8_t*>(src)[single_at];
+                        *reinterpret_cast<global_u16_any*>(line_of(row, 0) + single_to) = s_lut[single_lut + value];
+                    }
                     if (takes_four) {
                         /* all twelve table reads first, so that they travel together */
                         uint16_t e[3][4];
@@ -404,10 +410,6 @@ struct RowWriter {
 #pragma unroll
                         for (int ch = 0; ch < 3; ++ch)
                             __builtin_nontemporal_store(v[ch], reinterpret_cast<global_u32x2_any*>(line_of(row, ch * plane) + offset_of(tensor_at)));
-                    }
-                    if (lane < singles) {
-                        const uint32_t value = reinterpret_cast<const uint8_t*>(src)[single_at];
-                        *reinterpret_cast<global_u16_any*>(line_of(row, 0) + single_to) = s_lut[single_lut + value];
                     }
                 }
             }
