@@ -59,10 +59,14 @@ def test_longest_and_shortest_streams(exes, patch):             # noqa: F811
 
 def test_calls_on_one_workspace_that_grows_and_counts_on(exes):  # noqa: F811
     """Later calls find the words of earlier ones in the workspace; mixed patch sizes are several launches;
-    more than 32 images go through the descriptor table."""
+    more than 32 images take the larger argument block, and have their words made ready."""
     images = [synth.cosine_field(980 + k, 60 + 9 * k, 40 + k) for k in range(5)]
     case_run(exes, "asan", "mixed", images, [32, 64, 128], calls=2)
-    case_run(exes, "asan", "table", [noise(990 + k, 1 + k % 9, 1 + k % 6) for k in range(33)], [64])
+    case_run(exes, "asan", "block", [noise(990 + k, 1 + k % 9, 1 + k % 6) for k in range(33)], [64])
+
+
+def test_more_than_256_images_go_through_the_descriptor_table(exes):    # noqa: F811
+    case_run(exes, "asan", "table", [noise(4000 + k, 1 + k % 3, 1 + k % 2) for k in range(257)], [32])
 
 
 def sequence_run(exes, name, sequence, *args, **kw):            # noqa: F811

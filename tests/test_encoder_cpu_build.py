@@ -118,10 +118,15 @@ def test_all_patch_sizes_and_both_routes_in_one_call(exes):
     case_run(exes, "asan", "plain", [noise(401, 2, 3), noise(402, 131, 9), noise(403, 100, 101)], [1, 128 - 1, 100])
 
 
-def test_more_than_32_images_go_through_the_descriptor_table(exes):
+def test_more_than_32_images_take_the_larger_argument_block(exes):
     images = [noise(500 + k, 1 + k % 9, 1 + k % 6) for k in range(33)]
-    case_run(exes, "asan", "table", images, 64, calls=2)
+    case_run(exes, "asan", "block", images, 64, calls=2)
     case_run(exes, "asan", "table_plain", images, [(32, 9)[k % 2] for k in range(33)])
+
+
+@pytest.mark.parametrize("patch", [32, 64, 128])
+def test_more_than_256_images_go_through_the_descriptor_table(exes, patch):
+    case_run(exes, "asan", f"table_{patch}", [noise(5000 + k, 1 + k % 3, 1 + k % 2) for k in range(257)], patch)
 
 
 def test_files_without_room_receive_their_header_only(exes):

@@ -176,3 +176,18 @@ def test_captured_before_the_workspace_has_served_such_a_call(l3, mode):    # no
         torch.cuda.synchronize()
         same(files, lens, status, [image], 64)
     own.close()
+
+
+@pytest.mark.parametrize("patch,height", [(32, 30), (64, 40), (128, 40)])
+def test_more_images_than_the_arguments_hold(l3, ctx, patch, height):    # noqa: F811
+    """300 images, whose descriptors come from the table in device memory: with room for the longest stream one
+    kernel, with room for exactly their files the strip and copy kernels."""
+    distinct = [noise(3200 + k, 60 - k, height - k % 3, 0, 30 + 9 * k) for k in range(7)]
+    images = [distinct[k % 7] for k in range(300)]
+    dev = [torch.from_numpy(distinct[k]).cuda() for k in range(7)]
+    exact = [torch.full((len(oracle.encode(distinct[k % 7], patch)),), 0xAB, dtype=torch.uint8, device="cuda") for k in range(300)]
+    for files in (room_for(l3, images, patch), exact):
+        lens, status = torch.zeros(300, dtype=torch.int64, device="cuda"), torch.full((300,), 7, dtype=torch.int32, device="cuda")
+        l3.encode_batch(ctx, [dev[k % 7] for k in range(300)], files, lens, patch=patch, status=status)
+        torch.cuda.synchronize()
+        same(files, lens, status, images, patch)
