@@ -233,7 +233,7 @@ typedef struct {
  *               context share one workspace: on the device a call runs after the
  *               kernels of the previous one, whatever their streams; the host
  *               waits for them only when the workspace has to grow (batches of
- *               more than 32 images, or with a patch size other than 32, 64, 128,
+ *               more than 256 images, or with a patch size other than 32, 64, 128,
  *               go through a ring of four pinned descriptor tables, so the host
  *               can run at most four such calls ahead of the device).
  *               A call of at most 256 images with patch sizes 32, 64 and 128 can be

@@ -37,7 +37,6 @@ typedef __attribute__((address_space(1))) u32x4 global_u32x4;
 typedef __attribute__((address_space(1))) u32x4_any global_u32x4_any;
 typedef __attribute__((address_space(1))) const uint8_t global_const_u8;
 typedef __attribute__((address_space(1))) uint8_t global_u8;
-typedef __attribute__((address_space(1))) uint16_t global_u16;
 typedef uint16_t u16_any __attribute__((aligned(1)));
 typedef __attribute__((address_space(1))) u16_any global_u16_any;
 
@@ -161,9 +160,6 @@ __device__ __forceinline__ uint64_t agent_load_u64(const uint64_t* p) {
 __device__ __forceinline__ void agent_store_u64(uint64_t* p, uint64_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void agent_store_u32(uint32_t* p, uint32_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ uint32_t agent_exchange_u32(uint32_t* p, uint32_t v) {
     return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -171,9 +167,6 @@ __device__ __forceinline__ uint64_t agent_exchange_u64(uint64_t* p, uint64_t v) 
     return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ uint64_t agent_add_u64(uint64_t* p, uint64_t v) {
-    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint32_t agent_add_u32(uint32_t* p, uint32_t v) {
     return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 

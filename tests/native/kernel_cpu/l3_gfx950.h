@@ -37,7 +37,6 @@ typedef u32x4 global_u32x4;
 typedef u32x4_any global_u32x4_any;
 typedef const uint8_t global_const_u8;
 typedef uint8_t global_u8;
-typedef uint16_t global_u16;
 typedef uint16_t u16_any __attribute__((aligned(1)));
 typedef u16_any global_u16_any;
 
@@ -216,16 +215,13 @@ inline uint32_t l3cpu_bitop3(uint32_t a, uint32_t b, uint32_t c, uint32_t table)
 #define __builtin_amdgcn_permlane16_swap l3cpu_permlane16_swap
 #define __builtin_amdgcn_sched_barrier(mask) ((void)0)
 #define __builtin_amdgcn_s_setprio(level) ((void)0)
-#define __builtin_amdgcn_s_sleep(ticks) ((void)0)
 
 /* words that workgroups share */
 inline uint64_t agent_load_u64(const uint64_t* p) { return __atomic_load_n(p, __ATOMIC_RELAXED); }
 inline void agent_store_u64(uint64_t* p, uint64_t v) { __atomic_store_n(p, v, __ATOMIC_RELAXED); }
-inline void agent_store_u32(uint32_t* p, uint32_t v) { __atomic_store_n(p, v, __ATOMIC_RELAXED); }
 inline uint32_t agent_exchange_u32(uint32_t* p, uint32_t v) { return __atomic_exchange_n(p, v, __ATOMIC_RELAXED); }
 inline uint64_t agent_exchange_u64(uint64_t* p, uint64_t v) { return __atomic_exchange_n(p, v, __ATOMIC_RELAXED); }
 inline uint64_t agent_add_u64(uint64_t* p, uint64_t v) { return __atomic_fetch_add(p, v, __ATOMIC_RELAXED); }
-inline uint32_t agent_add_u32(uint32_t* p, uint32_t v) { return __atomic_fetch_add(p, v, __ATOMIC_RELAXED); }
 
 /* LDS is static host memory; its 32-bit addresses are offsets from one of its objects */
 struct LdsPair { uint32_t lo, hi; };
