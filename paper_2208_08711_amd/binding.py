@@ -321,6 +321,7 @@ def decode_crop_normalize_batch_prepared(ctx, batch, crop_w, crop_h, out, dtype=
 
 
 _data_ptr, _numel = operator.methodcaller("data_ptr"), operator.methodcaller("numel")
+_shape = operator.attrgetter("shape")
 
 
 def encode_batch(ctx, images, files, file_len, patch=0, status=None, stream=None, row_strides=None):
@@ -340,14 +341,14 @@ def encode_batch(ctx, images, files, file_len, patch=0, status=None, stream=None
             words[3::6] = array.array("Q", (operator.index(patch) & 0xFF,)) * n
         if len(files) != n:
             files = [files[i] for i in range(n)]
-        shapes = [im.shape for im in images]
-        widths = [int(s[1]) for s in shapes]
+        # (no list of the shapes themselves: as objects that stay they set off the garbage collector)
+        sides = [int(s[1]) & _MASK32 | (int(s[0]) & _MASK32) << 32 for s in map(_shape, images)]
         words[0::6] = array.array("Q", map(_data_ptr, images))
         if row_strides is None:
-            words[1::6] = array.array("Q", [3 * w & _MASK64 for w in widths])
+            words[1::6] = array.array("Q", [3 * (s & _MASK32) for s in sides])
         else:
             words[1::6] = array.array("Q", [operator.index(row_strides[i]) & _MASK64 for i in range(n)])
-        words[2::6] = array.array("Q", [w & _MASK32 | (int(s[0]) & _MASK32) << 32 for w, s in zip(widths, shapes)])
+        words[2::6] = array.array("Q", sides)
         words[4::6] = array.array("Q", map(_data_ptr, files))
         words[5::6] = array.array("Q", map(_numel, files))
     arr = (_EncodeItem * n).from_buffer(words) if n else (_EncodeItem * 1)()

@@ -211,6 +211,42 @@ def test_encode_batch_hands_over_strides_and_patch_sizes_of_every_integer_kind(m
     binding.encode_batch(Context(), [], [], lens, patch=[], row_strides=[])
 
 
+def test_encode_batch_keeps_few_objects_while_it_lists_the_images(monkeypatch):
+    """The list of a large batch is made without hundreds of objects that the garbage collector
+    follows: a call on new tensors would set it off and wait while it walks all of them."""
+    import gc
+    import torch
+    from paper_2208_08711_amd import binding
+
+    class Library:
+        def l3_encode_batch(self, ctx, items, n, *rest):
+            return 0
+
+    class Context:
+        handle = None
+
+    monkeypatch.setattr(binding, "_load", lambda: Library())
+    monkeypatch.setattr(binding, "_stream_ptr", lambda stream: None)
+    images = [torch.empty((3, 4 + k, 3), dtype=torch.uint8) for k in range(256)]
+    files = [torch.empty(100, dtype=torch.uint8) for _ in range(256)]
+    lens, runs, before = torch.empty(256, dtype=torch.int64), [], gc.get_threshold()
+
+    def count(phase, info):
+        runs.append(phase)
+
+    for more in ({"patch": 32}, {"patch": [32] * 256, "row_strides": [1024] * 256}):
+        binding.encode_batch(Context(), images, files, lens, **more)
+        gc.collect()
+        gc.callbacks.append(count)
+        gc.set_threshold(100)
+        try:
+            binding.encode_batch(Context(), images, files, lens, **more)
+        finally:
+            gc.set_threshold(*before)
+            gc.callbacks.remove(count)
+        assert not runs
+
+
 def test_header_is_plain_c99(tmp_path):
     """include/l3.h and include/l3_ablation.h compile as C99 with every warning on (no GPU, no
     HIP header needed): the ABI has no C++ in it."""
