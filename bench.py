@@ -281,7 +281,7 @@ def measure_encode(torch, l3, ctx, images, files, stream, patch):
             "hbm_fraction": (raw + out) / (ms * 1e-3) / 1e9 / HBM_PEAK_GBPS,
             "note": "two kernels per call: strip (filter, row min/max, bit packing into per-patch slots) and "
                     "compact (offsets, slots to the file); with very many patches a third between them "
-                    "works the offsets out"}
+                    "works the offsets out, and calls of few strips take one"}
 
 
 def measure_overlap(torch, step, stream, steps, decode_alone_ms):

@@ -819,7 +819,7 @@ __global__ __launch_bounds__(256) void l3_encode_compact_kernel_args(const Encod
  * the order of workgroups, spread over the XCDs: with an eighth of the images on each as in the other kernels
  * units look for others that have only just begun (256 photographs 207 us a call instead of 158).
  *
- * What bounds it (one image of 1920x1080: 16.6 us, 18.9 and 5.3 before) is a chain of round trips, the
+ * What bounds it (one image of 1920x1080: 15.9 us, 18.9 and 5.3 before) is a chain of round trips, the
  * ticket, the rows, the look and the stores, with some 5 us of arithmetic between; the look costs 2 us of
  * it.  Which calls take it: see chained_pays.  Measured the same or slower: 16 rows a wave at N = 32 and 64 (4
  * photographs 14.9 us, 11.7 with 8), 8 at N = 128 (32 images of 2048x1024 182 us, 177 with 16), the first look
@@ -866,7 +866,7 @@ struct L3ChainWord {
 
 /* Calls that take this route: few units, N = 32 ones counted by two thirds (four waves, not eight).  Every
  * unit reads all three channels' bytes, and with many in flight those no longer meet in a cache (32 images of
- * 2048x1024 fetch 591 MB instead of 201), which the strip kernel and the copy then do better; 4 a CU
+ * 2048x1024 fetch 547 MB instead of 219), which the strip kernel and the copy then do better; 4 a CU
  * is where they draw level.  An image of so many patches that they would need the layout kernel
  * between them (own_layout_pays) is worth it up to 12 a CU.  A call by the strip kernel / by this (units):
  *   N = 32    1 of 64x64 (6) 16.5 / 11.4 us, 1 photograph (72) 18.7 / 11.2, 16 (1056) 22.9 / 17.9, 4 of 1024x720 (1104) 24.7 / 20.7;
