@@ -390,7 +390,7 @@ def main():
     if not torch.cuda.is_available():
         raise SystemExit("bench.py needs a GPU (there is no CPU fallback)")
 
-    # one thread per host core, but never more than the 16 a one-GPU machine grants its jobs
+    # one thread per host core, but never more than the 16 that a one-GPU job is granted
     host_cores = os.cpu_count() or 1
     cores = min(host_cores, 16)
     images, label = make_workload(args.workload, args.batch)
